@@ -21,7 +21,7 @@ LIB = os.path.join(PKG, "libstm.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 
-SOURCES = ["api.cpp", "plan.cpp", "prep.hip", "dp.hip", "unary_bf16.hip", "pruner.hip", "pruner_api.cpp",
+SOURCES = ["api.cpp", "plan.cpp", "prep.hip", "dp.hip", "unary_bf16.hip", "pruner.hip", "pruner_train.hip", "pruner_api.cpp",
            "chains.hip", "noalloc.hip", "trellis.hip", "trellis_api.cpp"]
 HEADERS = [os.path.join(CSRC, "stm_internal.h"), os.path.join(CSRC, "host_common.h"),
            os.path.join(CSRC, "dp_math.h"),

@@ -70,7 +70,7 @@ struct stm_pruner {
   int rule = STM_PRUNE_TIME_NEAREST;
   stmh::DevBuf theta, grad, am, av;
   // per-call scratch
-  stmh::DevBuf groups, labels, node, phi, q, h1, h2, dz1, dz2, ds, loss, scores, part;
+  stmh::DevBuf groups, labels, node, phi, q, h1, dz1, dz2, prefix, gsum, loss, scores, part;
   stmh::DevBuf wa, wb, A, B, xm, xs, norms, cand, count;
   stmh::DevBuf taus, f32, f64, fu, fas, fell;
 };

@@ -1,6 +1,5 @@
-// Learned candidate pruner: features, FP32 training kernels (forward,
-// listwise loss, backward, Adam) and the BF16 inference kernel with top-k
-// selection.  Not part of the paper: it shortens the candidate lists the
+// Learned candidate pruner: features, the Adam step and the BF16 inference
+// kernel with top-k selection (the FP32 training pass is pruner_train.hip).  Not part of the paper: it shortens the candidate lists the
 // exact recursion (Section 2.2) runs on; the exact recursion stays the
 // fallback and the reference for the energy gap.
 //
@@ -104,200 +103,6 @@ __global__ __launch_bounds__(64) void k_group_rows(ModelView m, SceneView s, con
     q[2 * g] = qa;
     q[2 * g + 1] = qb;
   }
-}
-
-// ---- FP32 layer kernels ------------------------------------------------------------
-
-// Row loader of the first layer: x = [f_i, g_n, phi, 0...] gathered on the fly.
-struct GatherX {
-  const float* mdesc;   // [M][D]
-  const int2* groups;   // (tau, i) per group
-  const float* sdesc;   // [S][D]
-  const int32_t* node;  // [rows]
-  const float* phi;     // [rows][8]
-  int D;
-  float scale;          // D, the descriptor input factor
-  __device__ __forceinline__ float operator()(long long r, int c) const {
-    const int n = node[r];
-    if (n < 0) return 0.f;
-    if (c < D) return scale * mdesc[(long long)groups[r >> 6].y * D + c];
-    if (c < 2 * D) return scale * sdesc[(long long)n * D + (c - D)];
-    if (c < 2 * D + 8) return phi[r * 8 + (c - 2 * D)];
-    return 0.f;
-  }
-};
-
-struct PlainX {
-  const float* x;
-  int ld;
-  __device__ __forceinline__ float operator()(long long r, int c) const { return x[r * ld + c]; }
-};
-
-// C[r][o] = act(sum_k A(r, k) B(o, k) + bias[o]) for o < 128, with B(o, k) =
-// W[o * ldw + k] (TRANS = false) or W[k * ldw + o] (TRANS = true); act = relu
-// when `relu`, times [mask[r][o] > 0] when mask is given.  64 rows per block,
-// 256 threads, each 4 rows x 8 columns; K in tiles of 16 through LDS.
-template <class Loader, bool TRANS>
-__global__ __launch_bounds__(256) void k_layer(Loader ld, long long R, int I, const float* __restrict__ W, int ldw,
-                                              const float* __restrict__ bias, const float* __restrict__ mask,
-                                              int relu, float* __restrict__ C) {
-  __shared__ float As[16][64 + 1];
-  __shared__ float Bs[16][H + 1];
-  const int tid = threadIdx.x, tr = tid >> 4, tc = tid & 15;
-  const long long r0 = (long long)blockIdx.x * 64;
-  float acc[4][8];
-#pragma unroll
-  for (int j = 0; j < 4; ++j)
-#pragma unroll
-    for (int c = 0; c < 8; ++c) acc[j][c] = 0.f;
-  for (int k0 = 0; k0 < I; k0 += 16) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int e = tid + 256 * q, row = e >> 4, kk = e & 15;
-      As[kk][row] = (r0 + row < R && k0 + kk < I) ? ld(r0 + row, k0 + kk) : 0.f;
-    }
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const int e = tid + 256 * q, col = e >> 4, kk = e & 15;
-      float v = 0.f;
-      if (k0 + kk < I) v = TRANS ? W[(long long)(k0 + kk) * ldw + col] : W[(long long)col * ldw + k0 + kk];
-      Bs[kk][col] = v;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < 16; ++kk) {
-      float a[4], b[8];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) a[j] = As[kk][tr + 16 * j];
-#pragma unroll
-      for (int c = 0; c < 8; ++c) b[c] = Bs[kk][tc + 16 * c];
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int c = 0; c < 8; ++c) acc[j][c] = fmaf(a[j], b[c], acc[j][c]);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const long long r = r0 + tr + 16 * j;
-    if (r >= R) continue;
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      const int o = tc + 16 * c;
-      float v = acc[j][c] + (bias ? bias[o] : 0.f);
-      if (relu) v = fmaxf(v, 0.f);
-      if (mask && !(mask[r * H + o] > 0.f)) v = 0.f;
-      C[r * H + o] = v;
-    }
-  }
-}
-
-// Weight gradient, partial over a chunk of kWgradRows rows:
-// part[chunk][o][c] = sum_{r in chunk} dZ[r][o] X(r, c), o < 128, c < I.
-constexpr int kWgradRows = 512;
-
-template <class Loader>
-__global__ __launch_bounds__(256) void k_wgrad(const float* __restrict__ dZ, Loader ld, long long R, int I,
-                                              float* __restrict__ part) {
-  __shared__ float Zs[16][H + 1];
-  __shared__ float Xs[16][32 + 1];
-  const int tid = threadIdx.x, to = tid >> 3, tcc = tid & 7;  // o = to + 32 j, c = tcc + 8 q
-  const int c0 = blockIdx.x * 32;
-  const long long rbeg = (long long)blockIdx.y * kWgradRows;
-  const long long rend = rbeg + kWgradRows < R ? rbeg + kWgradRows : R;
-  float acc[4][4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) acc[j][q] = 0.f;
-  for (long long r0 = rbeg; r0 < rend; r0 += 16) {
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const int e = tid + 256 * q, rr = e >> 7, o = e & 127;
-      Zs[rr][o] = r0 + rr < rend ? dZ[(r0 + rr) * H + o] : 0.f;
-    }
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      const int e = tid + 256 * q, rr = e >> 5, c = e & 31;
-      Xs[rr][c] = (r0 + rr < rend && c0 + c < I) ? ld(r0 + rr, c0 + c) : 0.f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int rr = 0; rr < 16; ++rr) {
-      float z[4], x[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) z[j] = Zs[rr][to + 32 * j];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) x[q] = Xs[rr][tcc + 8 * q];
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) acc[j][q] = fmaf(z[j], x[q], acc[j][q]);
-    }
-    __syncthreads();
-  }
-  float* out = part + (long long)blockIdx.y * H * I;
-#pragma unroll
-  for (int j = 0; j < 4; ++j)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int c = c0 + tcc + 8 * q;
-      if (c < I) out[(long long)(to + 32 * j) * I + c] = acc[j][q];
-    }
-}
-
-// Column sums, partial over chunks of rows: part[chunk][c] = sum_r s(r) Y[r][c]
-// (s = 1 when scale is null).
-__global__ __launch_bounds__(256) void k_colsum(const float* __restrict__ Y, int ncol, long long R,
-                                               const float* __restrict__ scale, float* __restrict__ part) {
-  const int c = blockIdx.x * 256 + threadIdx.x;
-  if (c >= ncol) return;
-  const long long rbeg = (long long)blockIdx.y * kWgradRows;
-  const long long rend = rbeg + kWgradRows < R ? rbeg + kWgradRows : R;
-  float acc = 0.f;
-  for (long long r = rbeg; r < rend; ++r) acc = fmaf(scale ? scale[r] : 1.f, Y[r * ncol + c], acc);
-  part[(long long)blockIdx.y * ncol + c] = acc;
-}
-
-// out[j] = sum over chunks of part[chunk][j], in chunk order.
-__global__ __launch_bounds__(256) void k_reduce_chunks(const float* __restrict__ part, int nchunk, long long n,
-                                                      float* __restrict__ out) {
-  const long long j = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (j >= n) return;
-  float acc = 0.f;
-  for (int c = 0; c < nchunk; ++c) acc += part[(long long)c * n + j];
-  out[j] = acc;
-}
-
-// Listwise loss of each group (one 64-lane block): scores s = w3 . h2 + b3,
-// softmax over the valid candidates, loss = -log p[label] with label the slot
-// of node labels[g]; ds = (p - onehot) / G; dZ2 = ds w3 [h2 > 0].
-__global__ __launch_bounds__(64) void k_loss(const float* __restrict__ H2, const float* __restrict__ w3,
-                                            const float* __restrict__ b3, const int32_t* __restrict__ node,
-                                            const int32_t* __restrict__ labels, int G, float* __restrict__ scores,
-                                            float* __restrict__ loss, float* __restrict__ ds,
-                                            float* __restrict__ dZ2) {
-  const int g = blockIdx.x, lane = threadIdx.x;
-  const long long r = (long long)g * 64 + lane;
-  const bool valid = node[r] >= 0;
-  float s = b3[0];
-  for (int k = 0; k < H; ++k) s = fmaf(H2[r * H + k], w3[k], s);
-  if (scores) scores[r] = valid ? s : -__builtin_inff();
-  if (!labels) return;
-  float mx = valid ? s : -__builtin_inff();
-  for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
-  const float e = valid ? expf(s - mx) : 0.f;
-  float z = e;
-  for (int off = 32; off > 0; off >>= 1) z += __shfl_xor(z, off);
-  // the label is a node id; its slot is the lane holding it (none: NaN loss, no gradient)
-  const unsigned long long hit = __ballot(valid && node[r] == labels[g]);
-  const int lab = hit ? __ffsll(static_cast<long long>(hit)) - 1 : -1;
-  const float sl = __shfl(s, lab < 0 ? 0 : lab);
-  if (lane == 0) loss[g] = lab < 0 ? __builtin_nanf("") : -(sl - mx - logf(z));
-  const float d = lab < 0 ? 0.f : ((valid ? e / z : 0.f) - (lane == lab ? 1.f : 0.f)) / static_cast<float>(G);
-  ds[r] = d;
-  for (int k = 0; k < H; ++k) dZ2[r * H + k] = H2[r * H + k] > 0.f ? d * w3[k] : 0.f;
 }
 
 // Adam (Kingma and Ba) on the packed parameters; c1 = 1 - beta1^t, c2 = 1 - beta2^t.
@@ -581,59 +386,6 @@ hipError_t launch_group_rows(const ModelView& m, const SceneView& s, const float
   hipLaunchKernelGGL(k_group_rows, dim3(static_cast<unsigned>(G)), dim3(64), 0, st, m, s, U, us, sp, groups, tau0,
                      node, phi, q);
   return hipGetLastError();
-}
-
-hipError_t launch_pruner_train(const PrunerTrain& t, hipStream_t st) {
-  const long long R = (long long)t.G * 64;
-  const int NI = 2 * t.D + 8;
-  const float* W1 = t.theta;
-  const float* b1 = W1 + (long long)H * NI;
-  const float* W2 = b1 + H;
-  const float* b2 = W2 + H * H;
-  const float* w3 = b2 + H;
-  const float* b3 = w3 + H;
-  float* gW1 = t.grad;
-  float* gb1 = gW1 + (long long)H * NI;
-  float* gW2 = gb1 + H;
-  float* gb2 = gW2 + H * H;
-  float* gw3 = gb2 + H;
-  float* gb3 = gw3 + H;
-  const GatherX gx{t.mdesc, t.groups, t.sdesc, t.node, t.phi, t.D, static_cast<float>(t.D)};
-  const int nb = blocks(R, 64);
-  hipLaunchKernelGGL((k_layer<GatherX, false>), dim3(nb), dim3(256), 0, st, gx, R, NI, W1, NI, b1,
-                     (const float*)nullptr, 1, t.h1);
-  hipLaunchKernelGGL((k_layer<PlainX, false>), dim3(nb), dim3(256), 0, st, PlainX{t.h1, H}, R, H, W2, H, b2,
-                     (const float*)nullptr, 1, t.h2);
-  hipLaunchKernelGGL(k_loss, dim3(t.G), dim3(64), 0, st, t.h2, w3, b3, t.node, t.labels, t.G, t.scores, t.loss,
-                     t.ds, t.dz2);
-  if (!t.labels) return hipGetLastError();
-  const int nch = blocks(R, kWgradRows);
-  // layer 3: dw3 = sum_r ds_r h2_r, db3 = sum_r ds_r
-  hipLaunchKernelGGL(k_colsum, dim3(1, nch), dim3(256), 0, st, t.h2, H, R, t.ds, t.part);
-  hipLaunchKernelGGL(k_reduce_chunks, dim3(1), dim3(256), 0, st, t.part, nch, (long long)H, gw3);
-  hipLaunchKernelGGL(k_colsum, dim3(1, nch), dim3(256), 0, st, t.ds, 1, R, (const float*)nullptr, t.part);
-  hipLaunchKernelGGL(k_reduce_chunks, dim3(1), dim3(256), 0, st, t.part, nch, 1LL, gb3);
-  // layer 2: dW2 = dZ2^T h1, db2 = colsum dZ2, dZ1 = (dZ2 W2) [h1 > 0]
-  hipLaunchKernelGGL(k_wgrad<PlainX>, dim3(H / 32, nch), dim3(256), 0, st, t.dz2, PlainX{t.h1, H}, R, H, t.part);
-  hipLaunchKernelGGL(k_reduce_chunks, dim3(blocks((long long)H * H, 256)), dim3(256), 0, st, t.part, nch,
-                     (long long)H * H, gW2);
-  hipLaunchKernelGGL(k_colsum, dim3(1, nch), dim3(256), 0, st, t.dz2, H, R, (const float*)nullptr, t.part);
-  hipLaunchKernelGGL(k_reduce_chunks, dim3(1), dim3(256), 0, st, t.part, nch, (long long)H, gb2);
-  hipLaunchKernelGGL((k_layer<PlainX, true>), dim3(nb), dim3(256), 0, st, PlainX{t.dz2, H}, R, H, W2, H,
-                     (const float*)nullptr, t.h1, 0, t.dz1);
-  // layer 1: dW1 = dZ1^T X, db1 = colsum dZ1
-  hipLaunchKernelGGL(k_wgrad<GatherX>, dim3(blocks(NI, 32), nch), dim3(256), 0, st, t.dz1, gx, R, NI, t.part);
-  hipLaunchKernelGGL(k_reduce_chunks, dim3(blocks((long long)H * NI, 256)), dim3(256), 0, st, t.part, nch,
-                     (long long)H * NI, gW1);
-  hipLaunchKernelGGL(k_colsum, dim3(1, nch), dim3(256), 0, st, t.dz1, H, R, (const float*)nullptr, t.part);
-  hipLaunchKernelGGL(k_reduce_chunks, dim3(1), dim3(256), 0, st, t.part, nch, (long long)H, gb1);
-  return hipGetLastError();
-}
-
-long long pruner_part_floats(int G, int D) {
-  const long long R = (long long)G * 64;
-  const long long nch = (R + kWgradRows - 1) / kWgradRows;
-  return nch * (long long)H * (2 * D + 8 > H ? 2 * D + 8 : H);
 }
 
 hipError_t launch_adam(float* theta, const float* g, float* m, float* v, long long n, float lr, float beta1,

@@ -80,10 +80,11 @@ int train_pass(stm_pruner* P, const Prepared& pr, int G, bool backward) {
   const size_t R = (size_t)G * kSlots;
   stm_ctx* ctx = P->ctx;
   int rc;
-  DevBuf* rows[] = {&P->h1, &P->h2, &P->dz1, &P->dz2};
+  DevBuf* rows[] = {&P->h1, &P->dz1, &P->dz2};
   for (DevBuf* b : rows)
     if ((rc = grow(ctx, *b, R * H * sizeof(float), pr.st))) return rc;
-  if ((rc = grow(ctx, P->ds, R * sizeof(float), pr.st))) return rc;
+  if ((rc = grow(ctx, P->prefix, (size_t)pr.m.M * H * sizeof(float), pr.st))) return rc;
+  if ((rc = grow(ctx, P->gsum, (size_t)stm::pruner_gsum_floats(G) * sizeof(float), pr.st))) return rc;
   if ((rc = grow(ctx, P->scores, R * sizeof(float), pr.st))) return rc;
   if ((rc = grow(ctx, P->loss, (size_t)G * sizeof(float), pr.st))) return rc;
   if ((rc = grow(ctx, P->part, (size_t)stm::pruner_part_floats(G, P->dim) * sizeof(float), pr.st))) return rc;
@@ -96,13 +97,14 @@ int train_pass(stm_pruner* P, const Prepared& pr, int G, bool backward) {
   t.labels = backward ? as<const int32_t>(P->labels) : nullptr;
   t.D = P->dim;
   t.G = G;
+  t.M = pr.m.M;
   t.theta = as<const float>(P->theta);
   t.grad = as<float>(P->grad);
   t.h1 = as<float>(P->h1);
-  t.h2 = as<float>(P->h2);
   t.dz1 = as<float>(P->dz1);
   t.dz2 = as<float>(P->dz2);
-  t.ds = as<float>(P->ds);
+  t.prefix = as<float>(P->prefix);
+  t.gsum = as<float>(P->gsum);
   t.loss = as<float>(P->loss);
   t.scores = as<float>(P->scores);
   t.part = as<float>(P->part);
@@ -384,7 +386,7 @@ void stm_pruner_destroy(stm_pruner* P) {
     (void)hipDeviceSynchronize();
   }
   DevBuf* bufs[] = {&P->theta, &P->grad, &P->am,  &P->av,    &P->groups, &P->labels, &P->node,  &P->phi,
-                    &P->q,     &P->h1,   &P->h2,  &P->dz1,   &P->dz2,    &P->ds,     &P->loss,  &P->scores,
+                    &P->q,     &P->h1,   &P->dz1, &P->dz2,   &P->prefix, &P->gsum,   &P->loss,  &P->scores,
                     &P->part,  &P->wa,   &P->wb,  &P->A,      &P->B,      &P->xm,    &P->xs,
                     &P->norms, &P->cand, &P->count, &P->taus, &P->f32,   &P->f64,    &P->fu,    &P->fas,
                     &P->fell};

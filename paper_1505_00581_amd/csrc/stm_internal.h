@@ -391,8 +391,8 @@ hipError_t launch_group_rows(const ModelView& m, const SceneView& s, const float
 
 // One FP32 training pass over G groups (rows = 64 G): forward, scores and
 // per-group losses; with labels also the gradient of the mean loss into grad
-// (packed like theta).  Buffers: h1, h2, dz1, dz2 [rows][128], ds [rows],
-// part [pruner_part_floats(G, D)].
+// (packed like theta).  Buffers: h1, dz1, dz2 [rows][128], prefix [M][128],
+// gsum [pruner_gsum_floats(G)], part [pruner_part_floats(G, D)].
 struct PrunerTrain {
   const float* mdesc;
   const float* sdesc;
@@ -400,13 +400,14 @@ struct PrunerTrain {
   const int32_t* node;
   const float* phi;
   const int32_t* labels;  // null: forward only
-  int D, G;
+  int D, G, M;
   const float* theta;
   float* grad;
-  float *h1, *h2, *dz1, *dz2, *ds, *loss, *scores, *part;
+  float *h1, *dz1, *dz2, *prefix, *gsum, *loss, *scores, *part;
 };
 hipError_t launch_pruner_train(const PrunerTrain& t, hipStream_t st);
 long long pruner_part_floats(int G, int D);
+long long pruner_gsum_floats(int G);
 hipError_t launch_adam(float* theta, const float* g, float* m, float* v, long long n, float lr, float beta1,
                        float beta2, float eps, float c1, float c2, hipStream_t st);
 
