@@ -72,65 +72,84 @@ __global__ void k_candidates(ModelView m, SceneView s, SearchParams sp, int32_t 
 }
 
 // ---- unary table U[i][n] = ||f_i - g_n|| in FP32 (Eq. 2) -----------------------
-// One thread per scene point, 16 model rows per block staged in LDS.  The
-// scene rows of the block's 256 points are staged too, 32 dimensions at a
-// time and read from global memory in 128-byte row segments (a thread
-// streaming its own row would touch 64 lines per load across the wave).  Each
-// distance is accumulated over the dimensions in ascending order.
-constexpr int kUnaryRows = 16;
+// A workgroup computes 16 R model rows by 16 N scene points, thread (tr, tn) the
+// R x N distances of rows tr + 16 j and points tn + 16 j, so that a staged value
+// is read once per R or N distances and a thread reads its values four
+// dimensions at a time.  Each distance is accumulated over the dimensions in
+// ascending order.  Tiles of KT dimensions go through LDS, read a tile ahead.
+// Bound by the two VALU instructions per dimension (75 x 31.7k at 162: 31 us
+// against 19.5 of issue; with one point per thread and a row value read per
+// distance, bound by LDS, 63 us) or, for a table of a few tiles, by their
+// latency (20 x 460: 5.5 us, 36 before).
 constexpr int kUnaryMaxDim = 256;
-constexpr int kUnaryTile = 32;
+constexpr int kUnaryFewBlocks = 128;
 
+template <int R, int N, int KT>
 __global__ __launch_bounds__(kBlock) void k_unary_f32(ModelView m, SceneView s, float* __restrict__ U) {
-  __shared__ float fm[kUnaryRows][kUnaryMaxDim];
-  __shared__ float gt[kBlock][kUnaryTile + 1];  // +1: lanes of one column hit distinct banks
-  const int32_t dim = s.dim;
-  const int32_t i0 = blockIdx.y * kUnaryRows;
-  const int32_t rows = min(kUnaryRows, m.M - i0);
-  for (int32_t e = threadIdx.x; e < kUnaryRows * dim; e += blockDim.x) {
-    const int32_t r = e / dim, d = e - r * dim;
-    fm[r][d] = r < rows ? m.desc[(long long)(i0 + r) * dim + d] : 0.0f;
-  }
-  const int32_t n0 = blockIdx.x * kBlock;
-  const int32_t n = n0 + threadIdx.x;
-  float acc[kUnaryRows];
-#pragma unroll
-  for (int r = 0; r < kUnaryRows; ++r) acc[r] = 0.0f;
-  // the scene tile of dimensions [d0, d0 + 32) is read into registers one tile
-  // ahead, so that its global reads overlap the arithmetic of the tile before.
-  // Thread t reads dimension t % 32 of the tile for points t / 32 + 8 j.
-  constexpr int kStride = kBlock / kUnaryTile;
-  const int32_t tdd = threadIdx.x % kUnaryTile, tp = threadIdx.x / kUnaryTile;
-  const float* src = s.desc + (long long)(n0 + tp) * dim + tdd;
-  const long long jstep = (long long)kStride * dim;
-  float pre[kUnaryTile];
+  constexpr int kLd = KT + 4;  // a multiple of 4, odd after division by 4: 16-byte reads of 16 rows hit distinct banks
+  constexpr int kRowsPerPass = kBlock / KT;
+  constexpr int kRows = 16 * R, kPts = 16 * N;
+  constexpr int kRowReads = kRows / kRowsPerPass, kPtReads = kPts / kRowsPerPass;
+  __shared__ __align__(16) float fs[kRows][kLd];
+  __shared__ __align__(16) float gs[kPts][kLd];
+  const int32_t dim = s.dim, tid = threadIdx.x;
+  const int32_t i0 = blockIdx.y * kRows, n0 = blockIdx.x * kPts;
+  const int32_t tr = tid >> 4, tn = tid & 15;
+  const int32_t kk = tid % KT, kr = tid / KT;
+  float fr[kRowReads], gr[kPtReads];
+  // rows and points past the end read the last one (their results are not
+  // stored), dimensions past the end count as 0
   const auto fetch = [&](int32_t d0) {
-    const bool dok = tdd < min(kUnaryTile, dim - d0);
+    const bool dok = d0 + kk < dim;
+    const int32_t d = dok ? d0 + kk : 0;
 #pragma unroll
-    for (int32_t j = 0; j < kUnaryTile; ++j)
-      pre[j] = dok && n0 + tp + kStride * j < s.S ? src[j * jstep + d0] : 0.0f;
+    for (int j = 0; j < kRowReads; ++j) {
+      const float v = m.desc[(long long)min(i0 + kr + kRowsPerPass * j, m.M - 1) * dim + d];
+      fr[j] = dok ? v : 0.f;
+    }
+#pragma unroll
+    for (int j = 0; j < kPtReads; ++j) {
+      const float v = s.desc[(long long)min(n0 + kr + kRowsPerPass * j, s.S - 1) * dim + d];
+      gr[j] = dok ? v : 0.f;
+    }
   };
+  float acc[R][N];
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+#pragma unroll
+    for (int c = 0; c < N; ++c) acc[r][c] = 0.f;
   fetch(0);
-  for (int32_t d0 = 0; d0 < dim; d0 += kUnaryTile) {
-    const int32_t w = min(kUnaryTile, dim - d0);
-    __syncthreads();  // the previous tile is consumed (and fm is written, first time)
+  for (int32_t d0 = 0; d0 < dim; d0 += KT) {
+    __syncthreads();  // the previous tile is consumed
 #pragma unroll
-    for (int32_t j = 0; j < kUnaryTile; ++j) gt[tp + kStride * j][tdd] = pre[j];
+    for (int j = 0; j < kRowReads; ++j) fs[kr + kRowsPerPass * j][kk] = fr[j];
+#pragma unroll
+    for (int j = 0; j < kPtReads; ++j) gs[kr + kRowsPerPass * j][kk] = gr[j];
     __syncthreads();
-    if (d0 + kUnaryTile < dim) fetch(d0 + kUnaryTile);
-    for (int32_t dd = 0; dd < w; ++dd) {
-      const float v = gt[threadIdx.x][dd];
+    if (d0 + KT < dim) fetch(d0 + KT);
+#pragma unroll 2
+    for (int k = 0; k < KT; k += 4) {
+      float4 f[R], g[N];
 #pragma unroll
-      for (int r = 0; r < kUnaryRows; ++r) {
-        const float a0 = fm[r][d0 + dd] - v;
-        acc[r] = fmaf(a0, a0, acc[r]);
-      }
+      for (int r = 0; r < R; ++r) f[r] = *reinterpret_cast<const float4*>(&fs[tr + 16 * r][k]);
+#pragma unroll
+      for (int c = 0; c < N; ++c) g[c] = *reinterpret_cast<const float4*>(&gs[tn + 16 * c][k]);
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int c = 0; c < N; ++c) {
+          const float a0 = f[r].x - g[c].x, a1 = f[r].y - g[c].y, a2 = f[r].z - g[c].z, a3 = f[r].w - g[c].w;
+          acc[r][c] = fmaf(a3, a3, fmaf(a2, a2, fmaf(a1, a1, fmaf(a0, a0, acc[r][c]))));
+        }
     }
   }
-  if (n >= s.S) return;
 #pragma unroll
-  for (int r = 0; r < kUnaryRows; ++r)
-    if (r < rows) U[(long long)(i0 + r) * s.S + n] = sqrtf(acc[r]);
+  for (int r = 0; r < R; ++r)
+#pragma unroll
+    for (int c = 0; c < N; ++c) {
+      const int32_t i = i0 + tr + 16 * r, n = n0 + tn + 16 * c;
+      if (i < m.M && n < s.S) U[(long long)i * s.S + n] = sqrtf(acc[r][c]);
+    }
 }
 
 // ---- model angles of the triangle ending at point i (FP64, then rounded) ------
@@ -239,8 +258,25 @@ hipError_t launch_candidates(const ModelView& m, const SceneView& s, const Searc
 
 hipError_t launch_unary_f32(const ModelView& m, const SceneView& s, float* U, hipStream_t st) {
   if (s.dim > kUnaryMaxDim) return hipErrorInvalidValue;
-  dim3 grid(grid_for(s.S, kBlock), (m.M + kUnaryRows - 1) / kUnaryRows);
-  hipLaunchKernelGGL(k_unary_f32, grid, dim3(kBlock), 0, st, m, s, U);
+  // Few tiles (a short scene, a block of one): 16 x 16 distances per workgroup
+  // and 64 dimensions at a time, since the chain of tiles bounds it, not the
+  // arithmetic.  Otherwise the fewest row tiles times (R + 1): the arithmetic
+  // of a tile grows with R, its reads of the scene do not.
+  const auto blocks = [&](int rows, int pts) { return (long long)((m.M + rows - 1) / rows) * ((s.S + pts - 1) / pts); };
+  int best = 5;
+  const auto cost = [&](int r) { return (long long)((m.M + 16 * r - 1) / (16 * r)) * (r + 1); };
+  for (int r = 4; r >= 1; --r)
+    if (cost(r) < cost(best)) best = r;
+#define STM_UNARY(R, N, KT)                                                                                  \
+  hipLaunchKernelGGL((k_unary_f32<R, N, KT>), dim3((s.S + 16 * N - 1) / (16 * N), (m.M + 16 * R - 1) / (16 * R)), \
+                     dim3(kBlock), 0, st, m, s, U)
+  if (blocks(16 * best, 64) < kUnaryFewBlocks) STM_UNARY(1, 1, 64);
+  else if (best == 5) STM_UNARY(5, 4, 32);
+  else if (best == 4) STM_UNARY(4, 4, 32);
+  else if (best == 3) STM_UNARY(3, 4, 32);
+  else if (best == 2) STM_UNARY(2, 4, 32);
+  else STM_UNARY(1, 4, 32);
+#undef STM_UNARY
   return hipGetLastError();
 }
 
