@@ -317,6 +317,11 @@ constexpr int kTrellisTileRows = 64;
 constexpr int kTrellisTileCols = 128;
 constexpr int kTrellisTileCells = 1024;
 constexpr int kTrellisSmallTileCells = 256;  // tiles of launches with few workgroups
+// How a band's steps are tiled: rows by columns of at most 1024 or (launches of
+// few workgroups) 256 cells with staged predecessors; or for wide bands 8 rows
+// or (few workgroups) 4 rows by 64 columns.
+enum class TrellisTiling : int32_t { kCells1024, kCells256, kWide8, kWide4 };
+constexpr int kTrellisWideCols = 64;
 struct TrellisTile {
   int32_t r0, r1, c0, c1, k0, k1, ncell, pad;
 };
@@ -331,6 +336,7 @@ struct TrellisTile {
 struct TrellisBand {
   int32_t *s_lo, *s_hi, *p_lo, *p_hi, *q_lo, *q_hi;
   long long *rowoff, *qoff;
+  long long* base;  // [n][2] (rowoff - s_lo, qoff - q_lo)
   float *A, *C;
 };
 
@@ -370,9 +376,9 @@ hipError_t launch_trellis_dirs(const TrellisBand& b, int32_t n, const float2* xy
                                int32_t* flag, hipStream_t st);
 // Steps 1..M-1 of every model, then the optimum and backtracking (degen: the
 // variant that handles coincident points; fused: every step in one workgroup
-// per model, for bands that trellis_fits_fused accepts; tile_cells: the cell
-// cap the tiles were cut with, kTrellisTileCells or kTrellisSmallTileCells).
-hipError_t launch_trellis_run(const TrellisRun& a, int32_t n_tiles, int32_t tile_cells, int32_t m_max, bool degen,
+// per model, for bands that trellis_fits_fused accepts; tiling: how the tiles
+// were cut).
+hipError_t launch_trellis_run(const TrellisRun& a, int32_t n_tiles, TrellisTiling tiling, int32_t m_max, bool degen,
                               bool fused, hipStream_t st);
 // Whether a band of n nodes, Q cells and QC two-step pairs fits one
 // workgroup's LDS for the fused run.

@@ -15,8 +15,9 @@
 // its terms out of every minimum.  The band and both direction tables depend
 // on the scene block only and are built once.
 //
-// One launch per step i computes V_i from V_{i-1} for every model: a
-// workgroup takes one tile, a rectangle of rows [r0, r1) by columns [c0, c1)
+// One launch per step i computes V_i from V_{i-1} for every model.  Wide bands
+// and launches of few workgroups run k_trellis_wide (operands in registers).
+// Otherwise a workgroup takes one tile, a rectangle of rows [r0, r1) by columns [c0, c1)
 // holding at most 1024 cells (narrow bands: up to 64 consecutive rows whose
 // successors span at most 128 nodes; wide bands: 32 rows by a 32-column
 // window, so that a staged predecessor serves 32 rows and 32 columns), or at
@@ -40,11 +41,10 @@ namespace stm {
 namespace {
 
 constexpr int kThreads = 256;                    // threads of a step workgroup
-// Predecessors staged in LDS at a time and the occupancy target of a step
+// Predecessors staged in LDS at a time and the occupancy target of a staged step
 // launch: launches of many workgroups (several per CU) take 20 at a time at six
-// waves per SIMD (80 registers), smaller ones 24 at five; on the whole video
-// without a closeness limit 40.2 ms for 50 models against 42.6 (24) and 47.5
-// (32 at four waves), and 7.8 ms for one model against 8.5 (20 at six).
+// waves per SIMD (80 registers), smaller ones 24 at five (50 models, rows of 376
+// cells: 40.2 ms against 42.6 with 24 and 47.5 with 32 at four waves).
 constexpr int kChunkWide = 20, kWavesWide = 6;    // launches of >= kManyTiles workgroups
 constexpr int kChunkSmall = 24, kWavesSmall = 5;
 constexpr int kManyTiles = 1024;
@@ -118,6 +118,15 @@ __global__ __launch_bounds__(1024) void k_scan64(long long* __restrict__ a, int3
     if (tid == 1023) carry = pre + v;
     __syncthreads();
   }
+}
+
+// Bases of the rows in the value and direction tables: cell (k, r) is base[2 k]
+// + r, pair (k, c) is base[2 k + 1] + c.
+__global__ __launch_bounds__(256) void k_trellis_bases(TrellisBand b, int32_t n) {
+  const int32_t k = blockIdx.x * 256 + threadIdx.x;
+  if (k >= n) return;
+  b.base[2LL * k] = b.rowoff[k] - b.s_lo[k];
+  b.base[2LL * k + 1] = b.qoff[k] - b.q_lo[k];
 }
 
 // Directions of the block: A (blockIdx.y = 0) over the cells of row r =
@@ -372,6 +381,138 @@ void k_trellis_step(TrellisRun a, int32_t i) {
   }
 }
 
+// ---- wide bands: every operand of a term in registers ------------------------------
+// Where a step has many cells per row (no closeness limit, or many points per
+// frame), a workgroup takes R rows by 64 columns, lane = column, and its NW waves
+// split the predecessors.  For a predecessor k the values V_{i-1}(k, r) and A(k,
+// r) of the R rows are wave-uniform and adjacent in the band, so they are scalar
+// loads, and a lane reads one C(k, c) for its R cells: nothing is staged, and a
+// relaxation is its arithmetic.  The waves' minima meet in LDS.  Predecessors of
+// some of the rows only (at the ends of the range) take a second loop that tests
+// each row.  Scalar loads of R values stay inside the band: a predecessor of all R
+// rows has all R cells.
+template <bool DEGEN, int R, int NW>
+__global__ __launch_bounds__(NW * 64) void k_trellis_wide(TrellisRun a, int32_t i) {
+  __shared__ float part[NW][R][64];
+  const TrellisModel md = a.models[blockIdx.y];
+  const int32_t M = md.m.M;
+  if (i >= M) return;
+  const TrellisTile tl = a.tiles[blockIdx.x];
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const TrellisBand& b = a.band;
+  const float* Vp = md.V + (long long)(i - 2) * a.Q;  // V_{i-1}
+  const int32_t c = min(tl.c0 + lane, tl.c1 - 1);
+  const float2 th = md.theta[i];
+  const float w = a.w;
+  const float2 xc = a.xy[c];
+  float bm[R], be[R], best[R];
+  bool same[R];
+#pragma unroll
+  for (int j = 0; j < R; ++j) {
+    const int32_t r = min(tl.r0 + j, tl.r1 - 1);
+    // a lane whose column is no successor of r reads another cell's direction
+    const long long q = ro(b.base + 2LL * r) + c;
+    cell_brackets(th, -b.A[min(max(q, 0LL), a.Q - 1)], bm[j], be[j]);
+    const float2 xr = ro(a.xy + r);
+    same[j] = xr.x == xc.x && xr.y == xc.y;
+    best[j] = __builtin_inff();
+  }
+  // this wave's predecessors [kb, ke), of which [mb, me) precede all R rows
+  const int32_t seg = (tl.k1 - tl.k0 + NW - 1) / NW;
+  const int32_t kb = min(tl.k0 + wv * seg, tl.k1), ke = min(kb + seg, tl.k1);
+  const int32_t cb = ro(b.p_lo + (tl.r1 - 1)), ce = ro(b.p_hi + tl.r0);
+  const bool all = tl.r1 - tl.r0 == R && cb < ce;
+  const int32_t mb = all ? min(max(kb, cb), ke) : ke;
+  const int32_t me = all ? mb + (max(min(ke, ce) - mb, 0) & ~1) : ke;  // an even count: two per trip
+  // The operands of the next predecessor are read while the current one is
+  // relaxed.  Scalar loads return in any order, so a wave can only wait for all
+  // of them: the current operands are waited for (`arrived`) before the next
+  // ones are asked for.
+  struct Operands {
+    float v[R], ar[R], c;
+  };
+  struct Bases {
+    long long v, c;
+  };
+  const auto bases = [&](int32_t k) {
+    const long long* p = b.base + 2LL * min(k, me - 1);
+    return Bases{ro(p), ro(p + 1)};
+  };
+  const auto load = [&](const Bases& y) {
+    Operands t;
+    t.c = (b.C + y.c)[c];
+    const float* pv = Vp + (y.v + tl.r0);
+    const float* pa = b.A + (y.v + tl.r0);
+#pragma unroll
+    for (int j = 0; j < R; ++j) t.v[j] = ro(pv + j);
+#pragma unroll
+    for (int j = 0; j < R; ++j) t.ar[j] = ro(pa + j);
+    return t;
+  };
+  const auto arrived = [&](const Operands& t, const Bases& y) {
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < R; ++j) asm volatile("" ::"s"(t.v[j]), "s"(t.ar[j]));
+    asm volatile("" ::"s"(y.v), "s"(y.c));
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  float wl = w;  // in a vector register: a term's fma takes V from a scalar one
+  asm volatile("" : "+v"(wl));
+  if (mb < me) {
+    Bases y = bases(mb);
+    Operands t0 = load(y), t1;
+    y = bases(mb + 1);
+    for (int32_t k = mb; k < me; k += 2) {
+      float s0[R];
+      arrived(t0, y);
+      t1 = load(y);
+      y = bases(k + 2);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int j = 0; j < R; ++j) s0[j] = relax<DEGEN>(t0.v[j], t0.ar[j], t0.c, bm[j], be[j], th, same[j], wl);
+      arrived(t1, y);
+      t0 = load(y);
+      y = bases(k + 3);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int j = 0; j < R; ++j)
+        best[j] = fminf(fminf(best[j], s0[j]), relax<DEGEN>(t1.v[j], t1.ar[j], t1.c, bm[j], be[j], th, same[j], wl));
+    }
+  }
+  const auto some_rows = [&](int32_t from, int32_t to) {
+    for (int32_t k = from; k < to; ++k) {
+      const int32_t ql = ro(b.q_lo + k), qh = ro(b.q_hi + k);
+      if (ql >= qh) continue;  // no two-step pair: no admissible triple
+      const float ck = b.C[ro(b.base + (2LL * k + 1)) + min(max(c, ql), qh - 1)];
+#pragma unroll
+      for (int j = 0; j < R; ++j) {
+        const int32_t r = tl.r0 + j;
+        if (r < tl.r1 && k >= ro(b.p_lo + r) && k < ro(b.p_hi + r)) {
+          const long long vo = ro(b.base + 2LL * k) + r;
+          best[j] = fminf(best[j], relax<DEGEN>(ro(Vp + vo), ro(b.A + vo), ck, bm[j], be[j], th, same[j], w));
+        }
+      }
+    }
+  };
+  some_rows(kb, mb);
+  some_rows(me, ke);
+#pragma unroll
+  for (int j = 0; j < R; ++j) part[wv][j][lane] = best[j];
+  __syncthreads();
+  float* Vi = md.V + (long long)(i - 1) * a.Q;
+  const int32_t dtm = md.m.t[i] - md.m.t[i - 1];
+  const float qw = a.lambda2 * (i <= M - 2 ? 2.f : 1.f);
+  const float cu = __fmul_rn(a.lambda1, md.U[(long long)i * a.n + c]);
+  for (int j = wv; j < tl.r1 - tl.r0; j += NW) {
+    const int32_t r = tl.r0 + j, lo = b.s_lo[r], hi = b.s_hi[r];
+    float m = part[0][j][lane];
+#pragma unroll
+    for (int q = 1; q < NW; ++q) m = fminf(m, part[q][j][lane]);
+    if (tl.c0 + lane < tl.c1 && c >= lo && c < hi)
+      Vi[b.rowoff[r] + (c - lo)] = step_value(cu, qw, dtm, a.t[c] - a.t[r], m);
+  }
+}
+
 // ---- small bands: every step in one workgroup per model ---------------------------
 // When the band's cells, the two-step pairs and the per-node offsets fit one
 // workgroup's LDS (the whole video at T = 10: 7.5k cells, 14k pairs), one
@@ -485,22 +626,42 @@ __global__ __launch_bounds__(kFusedThreads) void k_trellis_fused(TrellisRun a) {
 }
 
 // ---- optimum and backtracking, one workgroup per model ---------------------------
+// Backtracking is a chain of dependent reads, one per step: the nodes' ranges and
+// bases are held in LDS (up to kFinalNodes nodes), a cell's own direction comes
+// from the lane that chose it, and only the predecessors' values and directions
+// are read from memory.  One wave walks bands of at most 64 predecessors per
+// node; wider ones are split over the workgroup's waves (one model on the whole
+// video without a closeness limit: 378 -> 75 us; 50 models at T = 10: 53 -> 27).
+constexpr int kFinalThreads = 1024;
+constexpr int kFinalNodes = 4096;
+
 template <bool DEGEN>
-__global__ __launch_bounds__(256) void k_trellis_final(TrellisRun a) {
-  __shared__ float red_v[4];
-  __shared__ long long red_i[4];
-  __shared__ float res_v;
-  __shared__ long long res_i;
+__global__ __launch_bounds__(kFinalThreads) void k_trellis_final(TrellisRun a) {
+  constexpr int kWaves = kFinalThreads / 64;
+  __shared__ int4 nodes[kFinalNodes];  // value base, direction base, predecessors [z, w) of a node
+  __shared__ float red_v[2][kWaves], red_a[2][kWaves];
+  __shared__ long long red_i[kWaves];
+  __shared__ int32_t red_k[2][kWaves];
+  __shared__ int32_t row_sh;
   const int32_t q = blockIdx.x;
   const TrellisModel md = a.models[q];
   const int32_t M = md.m.M;
   const TrellisBand& b = a.band;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const float INF = __builtin_inff();
-  const float* VM = md.V + (long long)(M - 2) * a.Q;  // V_{M-1}
+  const bool in_lds = a.n <= kFinalNodes;  // (then bases fit 32 bits: at most n^2 / 2 cells)
+  int wide = 0;
+  for (int32_t k = tid; k < a.n; k += kFinalThreads) {
+    const int32_t lo = b.p_lo[k], hi = b.p_hi[k];
+    wide |= hi - lo > 64;
+    if (in_lds) nodes[k] = make_int4(static_cast<int32_t>(b.base[2LL * k]), static_cast<int32_t>(b.base[2LL * k + 1]), lo, hi);
+  }
+  // the first row-major minimum of V_{M-1}
+  const float* VM = md.V + (long long)(M - 2) * a.Q;
   float bv = INF;
   long long bi = 0x7fffffffffffffffLL;
-  for (long long x = tid; x < a.Q; x += 256) {
+#pragma unroll 8
+  for (long long x = tid; x < a.Q; x += kFinalThreads) {
     const float v = VM[x];
     if (v < bv) { bv = v; bi = x; }  // x ascends: the first minimum of this thread
   }
@@ -509,66 +670,91 @@ __global__ __launch_bounds__(256) void k_trellis_final(TrellisRun a) {
     const long long oi = __shfl_xor(bi, off);
     if (ov < bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
   }
-  if (lane == 0) { red_v[wv] = bv; red_i[wv] = bi; }
-  __syncthreads();
-  if (tid == 0) {
-    for (int w2 = 1; w2 < 4; ++w2)
-      if (red_v[w2] < bv || (red_v[w2] == bv && red_i[w2] < bi)) { bv = red_v[w2]; bi = red_i[w2]; }
-    res_v = bv;
-    res_i = bi;
-    a.e32[q] = bv;
-  }
-  __syncthreads();
-  if (wv != 0) return;
+  if (lane == 0) { red_v[0][wv] = bv; red_i[wv] = bi; }
+  wide = __syncthreads_or(wide);
+  for (int w2 = 0; w2 < kWaves; ++w2)
+    if (red_v[0][w2] < bv || (red_v[0][w2] == bv && red_i[w2] < bi)) { bv = red_v[0][w2]; bi = red_i[w2]; }
+  if (tid == 0) a.e32[q] = bv;
   int32_t* out = a.assign + md.assign0;
-  if (!(res_v < INF)) {
-    for (int i = lane; i < M; i += 64) out[i] = -1;
+  if (!(bv < INF)) {
+    for (int i = tid; i < M; i += kFinalThreads) out[i] = -1;
     return;
   }
-  // the optimal final cell: row = last r with rowoff[r] <= index
-  const long long idx = res_i;
-  int32_t lo = 0, hi = a.n;  // rowoff[lo] <= idx < rowoff[hi]
-  while (hi - lo > 1) {
-    const int32_t mid = (lo + hi) >> 1;
-    if (b.rowoff[mid] <= idx) lo = mid; else hi = mid;
-  }
-  int32_t r = lo, c = b.s_lo[lo] + static_cast<int32_t>(idx - b.rowoff[lo]);
-  if (lane == 0) {
+  // the optimal final cell: the row whose cells hold the index
+  for (int32_t k = tid; k < a.n; k += kFinalThreads)
+    if (b.rowoff[k] <= bi && bi < b.rowoff[k + 1]) row_sh = k;
+  __syncthreads();
+  if (!wide && wv != 0) return;
+  int32_t r = row_sh, c = b.s_lo[r] + static_cast<int32_t>(bi - b.rowoff[r]);
+  float arc = b.A[bi];  // the direction of cell (r, c)
+  if (tid == 0) {
     out[M - 1] = a.node0 + c;
     out[M - 2] = a.node0 + r;
   }
+  const auto node = [&](int32_t k, long long& vb, long long& cb, int32_t& lo, int32_t& hi) {
+    if (in_lds) {
+      const int4 x = nodes[k];
+      vb = x.x;
+      cb = x.y;
+      lo = x.z;
+      hi = x.w;
+    } else {
+      vb = b.base[2LL * k];
+      cb = b.base[2LL * k + 1];
+      lo = b.p_lo[k];
+      hi = b.p_hi[k];
+    }
+  };
   const int32_t TS = a.span_lim;
+  float2 th = md.theta[M - 1];
   for (int32_t i = M - 1; i >= 2; --i) {
+    const float2 th_next = md.theta[i - 1];
     const float* Vp = md.V + (long long)(i - 2) * a.Q;  // V_{i-1}
-    const float2 th = md.theta[i];
-    const float arc = b.A[b.rowoff[r] + (c - b.s_lo[r])];
     float bm, be;
     cell_brackets(th, -arc, bm, be);
-    const float2 xr = a.xy[r], xc = a.xy[c];
-    const bool same = xr.x == xc.x && xr.y == xc.y;
-    const int32_t tcv = a.t[c];
-    float tot = INF;
-    int32_t bk = 0x7fffffff;
-    for (int32_t k0 = b.p_lo[r]; k0 < b.p_hi[r]; k0 += 64) {
-      const int32_t k = k0 + lane;
-      if (k < b.p_hi[r] && span_ok(a.t[k], tcv, TS)) {
-        const long long off = b.rowoff[k] + (r - b.s_lo[k]);
-        const float v = relax<DEGEN>(Vp[off], b.A[off], b.C[b.qoff[k] + (c - b.q_lo[k])], bm, be, th, same, a.w);
-        if (v < tot) { tot = v; bk = k; }  // k ascends: the lowest k of this lane's minimum
-      }
+    bool same = false;
+    if (DEGEN) {
+      const float2 xr = a.xy[r], xc = a.xy[c];
+      same = xr.x == xc.x && xr.y == xc.y;
     }
-    for (int off = 32; off > 0; off >>= 1) {
-      const float ot = __shfl_xor(tot, off);
-      const int32_t ok = __shfl_xor(bk, off);
-      if (ot < tot || (ot == tot && ok < bk)) { tot = ot; bk = ok; }
+    const int32_t tcv = TS > 0 ? a.t[c] : 0;
+    long long rvb, rcb;
+    int32_t lo, hi;
+    node(r, rvb, rcb, lo, hi);
+    float tot = INF, ta = 0.f;  // this lane's minimum and the direction of its cell (k, r)
+    int32_t bk = 0x7fffffff;
+    for (int32_t k = lo + (wide ? tid : lane); k < hi; k += wide ? kFinalThreads : 64) {
+      if (!span_ok(TS > 0 ? a.t[k] : 0, tcv, TS)) continue;
+      long long vb, cb;
+      int32_t l2, h2;
+      node(k, vb, cb, l2, h2);
+      const float av = b.A[vb + r];
+      const float v = relax<DEGEN>(Vp[vb + r], av, b.C[cb + c], bm, be, th, same, a.w);
+      if (v < tot) { tot = v; bk = k; ta = av; }  // k ascends: the lowest k of this lane's minimum
+    }
+    const auto meet = [&](float ov, int32_t ok, float oa) {
+      if (ov < tot || (ov == tot && ok < bk)) { tot = ov; bk = ok; ta = oa; }
+    };
+    for (int off = 32; off > 0; off >>= 1) meet(__shfl_xor(tot, off), __shfl_xor(bk, off), __shfl_xor(ta, off));
+    if (wide) {
+      const int s = i & 1;  // the buffers alternate: one barrier a step
+      if (lane == 0) {
+        red_v[s][wv] = tot;
+        red_k[s][wv] = bk;
+        red_a[s][wv] = ta;
+      }
+      __syncthreads();
+      for (int w2 = 0; w2 < kWaves; ++w2) meet(red_v[s][w2], red_k[s][w2], red_a[s][w2]);
     }
     if (bk == 0x7fffffff) {  // no predecessor: cannot happen on a finite optimum
-      for (int j = lane; j < M; j += 64) out[j] = -1;
+      for (int j = lane; j < M && wv == 0; j += 64) out[j] = -1;
       return;
     }
-    if (lane == 0) out[i - 2] = a.node0 + bk;
+    if (tid == 0) out[i - 2] = a.node0 + bk;
     c = r;
     r = bk;
+    arc = ta;
+    th = th_next;
   }
 }
 
@@ -583,6 +769,8 @@ hipError_t launch_trellis_band(const int32_t* t, int32_t n, const SearchParams& 
   hipLaunchKernelGGL(k_scan64, dim3(1), dim3(1024), 0, st, b.rowoff, n);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   hipLaunchKernelGGL(k_scan64, dim3(1), dim3(1024), 0, st, b.qoff, n);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  hipLaunchKernelGGL(k_trellis_bases, dim3((n + 255) / 256), dim3(256), 0, st, b, n);
   return hipGetLastError();
 }
 
@@ -597,47 +785,52 @@ bool trellis_fits_fused(long long Q, long long QC, int32_t n) {
   return Q > 0 && Q <= (long long)kFusedThreads * kFusedSlots && n <= 32767 && fused_bytes(Q, QC, n) <= kFusedLds;
 }
 
-hipError_t launch_trellis_run(const TrellisRun& a, int32_t n_tiles, int32_t tile_cells, int32_t m_max, bool degen,
+namespace {
+
+template <bool DEGEN>
+void launch_step(const TrellisRun& a, int32_t n_tiles, TrellisTiling tiling, int32_t i, hipStream_t st) {
+  const dim3 grid(n_tiles, a.n_models);
+  // (1024-cell tiles are cut only for launches of many workgroups)
+  const bool many = (long long)n_tiles * a.n_models >= kManyTiles;
+  constexpr int kS = kTrellisSmallTileCells / kThreads, kL = kTrellisTileCells / kThreads;
+  if (tiling == TrellisTiling::kWide8)
+    hipLaunchKernelGGL((k_trellis_wide<DEGEN, 8, 4>), grid, dim3(4 * 64), 0, st, a, i);
+  else if (tiling == TrellisTiling::kWide4)
+    hipLaunchKernelGGL((k_trellis_wide<DEGEN, 4, 8>), grid, dim3(8 * 64), 0, st, a, i);
+  else if (tiling == TrellisTiling::kCells1024)
+    hipLaunchKernelGGL((k_trellis_step<DEGEN, kChunkWide, kWavesWide, kL>), grid, dim3(kThreads), 0, st, a, i);
+  else if (many)
+    hipLaunchKernelGGL((k_trellis_step<DEGEN, kChunkWide, kWavesWide, kS>), grid, dim3(kThreads), 0, st, a, i);
+  else
+    hipLaunchKernelGGL((k_trellis_step<DEGEN, kChunkSmall, kWavesSmall, kS>), grid, dim3(kThreads), 0, st, a, i);
+}
+
+}  // namespace
+
+hipError_t launch_trellis_run(const TrellisRun& a, int32_t n_tiles, TrellisTiling tiling, int32_t m_max, bool degen,
                               bool fused, hipStream_t st) {
   if (a.n_models <= 0) return hipSuccess;
+  hipError_t e;
   if (fused) {
     if (!trellis_fits_fused(a.Q, a.QC, a.n)) return hipErrorInvalidValue;
     if (degen)
       hipLaunchKernelGGL(k_trellis_fused<true>, dim3(a.n_models), dim3(kFusedThreads), 0, st, a);
     else
       hipLaunchKernelGGL(k_trellis_fused<false>, dim3(a.n_models), dim3(kFusedThreads), 0, st, a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    if ((e = hipGetLastError()) != hipSuccess) return e;
   } else if (a.Q > 0) {
     hipLaunchKernelGGL(k_trellis_first, dim3(a.n, a.n_models), dim3(64), 0, st, a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    if (tile_cells != kTrellisTileCells && tile_cells != kTrellisSmallTileCells) return hipErrorInvalidValue;
-    const bool small_tiles = tile_cells == kTrellisSmallTileCells;
+    if ((e = hipGetLastError()) != hipSuccess) return e;
     for (int32_t i = 2; i < m_max && n_tiles > 0; ++i) {
-      const dim3 grid(n_tiles, a.n_models);
-      // (1024-cell tiles are cut only for launches of many workgroups)
-      const bool many = (long long)n_tiles * a.n_models >= kManyTiles;
-      constexpr int kS = kTrellisSmallTileCells / kThreads, kL = kTrellisTileCells / kThreads;
-      if (degen && !small_tiles)
-        hipLaunchKernelGGL((k_trellis_step<true, kChunkWide, kWavesWide, kL>), grid, dim3(kThreads), 0, st, a, i);
-      else if (degen && many)
-        hipLaunchKernelGGL((k_trellis_step<true, kChunkWide, kWavesWide, kS>), grid, dim3(kThreads), 0, st, a, i);
-      else if (degen)
-        hipLaunchKernelGGL((k_trellis_step<true, kChunkSmall, kWavesSmall, kS>), grid, dim3(kThreads), 0, st, a, i);
-      else if (!small_tiles)
-        hipLaunchKernelGGL((k_trellis_step<false, kChunkWide, kWavesWide, kL>), grid, dim3(kThreads), 0, st, a, i);
-      else if (many)
-        hipLaunchKernelGGL((k_trellis_step<false, kChunkWide, kWavesWide, kS>), grid, dim3(kThreads), 0, st, a, i);
-      else
-        hipLaunchKernelGGL((k_trellis_step<false, kChunkSmall, kWavesSmall, kS>), grid, dim3(kThreads), 0, st, a, i);
+      if (degen) launch_step<true>(a, n_tiles, tiling, i, st);
+      else launch_step<false>(a, n_tiles, tiling, i, st);
       if ((e = hipGetLastError()) != hipSuccess) return e;
     }
   }
   if (degen)
-    hipLaunchKernelGGL(k_trellis_final<true>, dim3(a.n_models), dim3(256), 0, st, a);
+    hipLaunchKernelGGL(k_trellis_final<true>, dim3(a.n_models), dim3(kFinalThreads), 0, st, a);
   else
-    hipLaunchKernelGGL(k_trellis_final<false>, dim3(a.n_models), dim3(256), 0, st, a);
+    hipLaunchKernelGGL(k_trellis_final<false>, dim3(a.n_models), dim3(kFinalThreads), 0, st, a);
   return hipGetLastError();
 }
 

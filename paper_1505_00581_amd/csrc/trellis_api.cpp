@@ -30,7 +30,8 @@ struct stm_trellis {
   stm::TrellisBand band{};
   long long Q = 0, QC = 0;
   stm::TrellisTile* tiles = nullptr;
-  int32_t n_tiles = 0, tile_cells = 0;
+  int32_t n_tiles = 0;
+  stm::TrellisTiling tiling = stm::TrellisTiling::kCells1024;
   stm::TrellisModel* models_dev = nullptr;
   stm::PairDev* pairs_dev = nullptr;
   int2* items_dev = nullptr;
@@ -41,12 +42,14 @@ struct stm_trellis {
   double* o_e64 = nullptr;
   double* o_eu = nullptr;
   int32_t* o_asg = nullptr;
-  // a run is captured once as a HIP graph on the object's stream and replayed
+  // a run into the outputs of the run before is captured as a HIP graph on the
+  // object's stream and replayed from then on
   hipStream_t stream = nullptr;
   hipEvent_t ev_in = nullptr, ev_out = nullptr, ev_k0 = nullptr, ev_k1 = nullptr;
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
   const void* cap_out[4] = {nullptr, nullptr, nullptr, nullptr};
+  const void* last_out[4] = {nullptr, nullptr, nullptr, nullptr};
 };
 
 namespace {
@@ -107,7 +110,7 @@ int tr_enqueue(stm_trellis* p, float* e32, double* e64, double* eu, int32_t* as,
   a.e32 = e32;
   a.assign = as;
   if (timed) STM_HIP(hipEventRecord(p->ev_k0, st));
-  STM_HIP(stm::launch_trellis_run(a, p->n_tiles, p->tile_cells, p->m_max, p->degen, p->fused, st));
+  STM_HIP(stm::launch_trellis_run(a, p->n_tiles, p->tiling, p->m_max, p->degen, p->fused, st));
   if (timed) STM_HIP(hipEventRecord(p->ev_k1, st));
   STM_HIP(stm::launch_rescore_batch(p->pairs_dev, p->items_dev, p->n_models, p->sp, p->params.lambda1,
                                     p->params.lambda2, p->params.lambda3, 0.0, as, e64, eu, st));
@@ -158,6 +161,28 @@ std::vector<stm::TrellisTile> make_tiles(const std::vector<int32_t>& slo, const 
     if (cells > 0) out.push_back({r0, r1, slo[r0], std::max(chi, slo[r0] + 1), plo[r0], phi[r1 - 1], cells, 0});
     r0 = r1;
   }
+  return out;
+}
+
+// Tiles of a wide band: `rows` rows by 64 columns, the costliest first (a step
+// launch is as long as its last tiles).  Tiles without cells are left out.
+std::vector<stm::TrellisTile> make_wide_tiles(const std::vector<int32_t>& slo, const std::vector<int32_t>& shi,
+                                              const std::vector<int32_t>& plo, const std::vector<int32_t>& phi,
+                                              int rows) {
+  std::vector<stm::TrellisTile> out;
+  const int32_t n = static_cast<int32_t>(slo.size());
+  for (int32_t r0 = 0; r0 < n; r0 += rows) {
+    const int32_t r1 = std::min(n, r0 + rows);
+    for (int32_t c0 = slo[r0]; c0 < shi[r1 - 1]; c0 += stm::kTrellisWideCols) {
+      const int32_t c1 = std::min(shi[r1 - 1], c0 + stm::kTrellisWideCols);
+      int32_t cells = 0;
+      for (int32_t r = r0; r < r1; ++r) cells += std::max(0, std::min(shi[r], c1) - std::max(slo[r], c0));
+      if (cells > 0) out.push_back({r0, r1, c0, c1, plo[r0], phi[r1 - 1], cells, 0});
+    }
+  }
+  std::stable_sort(out.begin(), out.end(), [](const stm::TrellisTile& x, const stm::TrellisTile& y) {
+    return x.k1 - x.k0 > y.k1 - y.k0;
+  });
   return out;
 }
 
@@ -288,6 +313,7 @@ int stm_trellis_create(stm_ctx* ctx, const stm_points* models, int32_t n_models,
   TR_ALLOC(b.q_hi, int32_t, n);
   TR_ALLOC(b.rowoff, long long, (size_t)n + 1);
   TR_ALLOC(b.qoff, long long, (size_t)n + 1);
+  TR_ALLOC(b.base, long long, 2 * (size_t)n);
   TR_HIP(stm::launch_trellis_band(bt, n, p->sp, b, st));
   std::vector<int32_t> slo(n), shi(n), plo(n), phi(n), th(n);
   long long ends[2] = {0, 0};
@@ -302,19 +328,41 @@ int stm_trellis_create(stm_ctx* ctx, const stm_points* models, int32_t n_models,
   p->Q = ends[0];
   p->QC = ends[1];
   p->fused = !(params->flags & STM_TRELLIS_STEPWISE) && stm::trellis_fits_fused(p->Q, p->QC, n);
-  // Tiles of 1024 cells, or of 256 when a step launch would have fewer than
-  // kFewTiles workgroups: one workgroup per CU leaves its waves' latency
-  // exposed, more and smaller tiles hide it at the price of staging each
-  // predecessor for fewer cells (and with one cell per thread the step kernel
-  // has the registers to issue a chunk's reads in one round).
-  constexpr long long kFewTiles = 1024;
-  int tile_cells = stm::kTrellisTileCells;
-  std::vector<stm::TrellisTile> tiles = make_tiles(slo, shi, plo, phi, tile_cells);
-  if ((long long)tiles.size() * n_models < kFewTiles) {
-    tile_cells = stm::kTrellisSmallTileCells;
-    tiles = make_tiles(slo, shi, plo, phi, tile_cells);
+  // Tiling of the step launches (us per run of M = 30 models on the 754-node
+  // video or its first 200 nodes, staged cells / 8 rows / 4 rows by 64 columns):
+  //  * launches of few workgroups wait for the staging, whatever the width: 4 x
+  //    64 tiles split the predecessors over 8 waves (1 model, no limit 3710 /
+  //    3842 / 2281; T = 10 426 / 472 / 297; 8 models, 200 nodes, T = 40 721 / 868
+  //    / 503);
+  //  * rows of 128 and more successors fill the 64 columns: 36225 / 33880 / 39067
+  //    (50 models, no limit), 9766 / 8191 / 7377 (8 models, which still want the
+  //    shorter tiles); rows of 64 only while the chip is not full (200 nodes, 50
+  //    models, T = 100: 2073 / 1650 / 1929; 754 nodes: 5038 / 6054 / 7815);
+  //  * narrower rows leave lanes without a cell: staged cells (T = 20, 50 models
+  //    1020 / 1734 / 2095), in tiles of 1024, or of 256 when a step launch would
+  //    have fewer than kFewTiles workgroups: one workgroup per CU leaves its
+  //    waves' latency exposed, more and smaller tiles hide it at the price of
+  //    staging each predecessor for fewer cells (and with one cell per thread the
+  //    step kernel has the registers to issue a chunk's reads in one round).
+  constexpr long long kFewTiles = 1024, kFewWide = 1280;
+  using stm::TrellisTiling;
+  const std::vector<stm::TrellisTile> tall = make_wide_tiles(slo, shi, plo, phi, 8);
+  std::vector<stm::TrellisTile> tiles = make_wide_tiles(slo, shi, plo, phi, 4);
+  const long long n_tall = (long long)tall.size() * n_models, n_flat = (long long)tiles.size() * n_models;
+  const bool full_rows = p->Q >= 128LL * n;
+  if (n_flat < kFewWide) {
+    p->tiling = TrellisTiling::kWide4;
+  } else if (full_rows || (p->Q >= 64LL * n && n_tall < 4096)) {
+    p->tiling = n_tall < (full_rows ? 8192 : 2048) ? TrellisTiling::kWide4 : TrellisTiling::kWide8;
+    if (p->tiling == TrellisTiling::kWide8) tiles = tall;
+  } else {
+    p->tiling = TrellisTiling::kCells1024;
+    tiles = make_tiles(slo, shi, plo, phi, stm::kTrellisTileCells);
+    if ((long long)tiles.size() * n_models < kFewTiles) {
+      p->tiling = TrellisTiling::kCells256;
+      tiles = make_tiles(slo, shi, plo, phi, stm::kTrellisSmallTileCells);
+    }
   }
-  p->tile_cells = tile_cells;
   p->n_tiles = static_cast<int32_t>(tiles.size());
   TR_ALLOC(p->tiles, stm::TrellisTile, std::max<size_t>(1, tiles.size()));
   if (!tiles.empty())
@@ -435,10 +483,15 @@ int stm_trellis_run(stm_trellis* p, float* energy32, double* energy64, double* e
   int32_t* as = p->device ? assign : p->o_asg;
   const void* outs[4] = {e32, e64, eu, as};
   // timed runs launch the kernels directly, with two events around the
-  // recursion (HIP cannot time events inside a graph); other runs replay the
-  // graph captured for these outputs
+  // recursion (HIP cannot time events inside a graph); so do runs into outputs
+  // that the run before did not use (capturing costs more than it saves once:
+  // 0.4 ms for the 32 launches of 30 points); other runs replay the graph
+  // captured for these outputs
   const bool timed = p->ctx->prof;
-  if (!timed && (!p->exec || !std::equal(outs, outs + 4, p->cap_out))) {
+  const bool captured = p->exec && std::equal(outs, outs + 4, p->cap_out);
+  const bool direct = timed || (!captured && !std::equal(outs, outs + 4, p->last_out));
+  std::copy(outs, outs + 4, p->last_out);
+  if (!direct && !captured) {
     tr_drop_graph(p);
     STM_HIP(hipStreamBeginCapture(p->stream, hipStreamCaptureModeThreadLocal));
     const int rc = tr_enqueue(p, e32, e64, eu, as, p->stream, false);
@@ -456,8 +509,8 @@ int stm_trellis_run(stm_trellis* p, float* energy32, double* energy64, double* e
   // order: caller's stream -> the object's stream -> caller's stream
   STM_HIP(hipEventRecord(p->ev_in, user));
   STM_HIP(hipStreamWaitEvent(p->stream, p->ev_in, 0));
-  if (timed) {
-    const int rc = tr_enqueue(p, e32, e64, eu, as, p->stream, true);
+  if (direct) {
+    const int rc = tr_enqueue(p, e32, e64, eu, as, p->stream, timed);
     if (rc) return rc;
   } else {
     STM_HIP(hipGraphLaunch(p->exec, p->stream));
