@@ -340,6 +340,20 @@ struct TrellisBand {
   float *A, *C;
 };
 
+// The band by column, for runs of every step in one launch: cells (k, c) of
+// column c at pb[c] + k - p_lo[c], two-step pairs at qb[c] + k - qp_lo[c], their
+// directions At and Ct.  The columns are split into parts; part x owns [own[x].x,
+// own[x].y) and needs, d steps before the last, the columns from lim[x *
+// lim_stride + d] on.
+struct TrellisColumns {
+  const int32_t *pb, *qb, *qp_lo;  // [n + 1], [n + 1], [n]
+  const int32_t* row;              // [Q] row of every cell of the band
+  float *At, *Ct;
+  const int2* own;
+  const int32_t* lim;
+  int32_t parts, lim_stride;
+};
+
 // One model of a trellis run: U [M][n] raw distances to the block's nodes,
 // V [(M - 1)][Q] the value tables of steps 1..M-1, assignments from
 // assign + assign0.
@@ -355,6 +369,7 @@ struct TrellisRun {
   const TrellisModel* models;
   int32_t n_models;
   TrellisBand band;
+  TrellisColumns cols;
   const TrellisTile* tiles;
   const int32_t* t;     // [n] the block's frames
   const float2* xy;     // [n] the block's coordinates
@@ -375,14 +390,16 @@ hipError_t launch_trellis_band(const int32_t* t, int32_t n, const SearchParams& 
 hipError_t launch_trellis_dirs(const TrellisBand& b, int32_t n, const float2* xy, const int32_t* t, int32_t span_lim,
                                int32_t* flag, hipStream_t st);
 // Steps 1..M-1 of every model, then the optimum and backtracking (degen: the
-// variant that handles coincident points; fused: every step in one workgroup
-// per model, for bands that trellis_fits_fused accepts; tiling: how the tiles
-// were cut).
+// variant that handles coincident points; fused: every step in one launch, for
+// bands that trellis_fits_fused accepts, with a.cols; tiling: how the tiles were
+// cut).
 hipError_t launch_trellis_run(const TrellisRun& a, int32_t n_tiles, TrellisTiling tiling, int32_t m_max, bool degen,
                               bool fused, hipStream_t st);
-// Whether a band of n nodes, Q cells and QC two-step pairs fits one
-// workgroup's LDS for the fused run.
-bool trellis_fits_fused(long long Q, long long QC, int32_t n);
+// Whether a band of Q cells and QC two-step pairs, and the steps of m_max points,
+// fit one workgroup's LDS for the fused run.
+bool trellis_fits_fused(long long Q, long long QC, int32_t m_max);
+// The direction tables by column (At, Ct) from the band's.
+hipError_t launch_trellis_columns(const TrellisBand& b, const TrellisColumns& c, int32_t n, hipStream_t st);
 
 // ---- learned candidate pruner -------------------------------------------------------
 

@@ -513,115 +513,167 @@ __global__ __launch_bounds__(NW * 64) void k_trellis_wide(TrellisRun a, int32_t 
   }
 }
 
-// ---- small bands: every step in one workgroup per model ---------------------------
-// When the band's cells, the two-step pairs and the per-node offsets fit one
-// workgroup's LDS (the whole video at T = 10: 7.5k cells, 14k pairs), one
-// workgroup per model runs steps 1..M-1 with V_{i-1}, A, C and the offsets in
-// LDS and a workgroup barrier between steps, instead of a launch per step whose
-// dependent global reads make up most of its time.  Every term, and the order
-// of the operations that form a cell's value, is that of k_trellis_first and
-// k_trellis_step, so both give the same bits.
+// ---- small bands: every step in one launch ------------------------------------------
+// When the band's cells and two-step pairs fit one workgroup's LDS (the whole
+// video at T = 10: 7.5k cells, 14k pairs), one launch runs steps 1..M-1 with
+// V_{i-1}, A and C in LDS and a workgroup barrier between steps, instead of a
+// launch per step whose dependent global reads make up most of its time.
+//
+// A model is split into parts by the second node c of a cell: a part owns columns
+// [c0, c1) and, since V_i(r, c) needs V_{i-1}(k, r) of its predecessors r only,
+// computes at step i the columns [lim_i, c1) with lim_{M-1} = c0 and lim_{i-1} the
+// first predecessor of lim_i.  The columns before c0 are computed by several
+// parts, but no part waits for another: the launch needs no barrier across
+// workgroups and a few models fill the chip.  In LDS the cells lie by column, so
+// that the columns of a part are one slice and the predecessors of a node are
+// adjacent: a term is two LDS reads at running addresses and its arithmetic.  The
+// threads take the cells by row, as the value tables hold them: the lanes of one
+// row read the same V and A (by column, the reads met in a quarter of the banks:
+// 198 us).  Bound by the VALU of a part's CU (the whole video
+// at T = 10, 50 models in 5 parts: FUSED_US us against 336 with one part, cells by row
+// and an offset table read per term).
 constexpr int kFusedThreads = 1024;
 constexpr int kFusedSlots = 8;                                   // cells per thread
 constexpr int kFusedLds = 160 * 1024 - 512;                      // bytes of the LDS pool
 
-constexpr long long fused_bytes(long long Q, long long QC, long long n) {
-  return 8 * n + 8 * n + 4 * Q + 4 * Q + 4 * QC + 2 * Q;
-}
+constexpr long long fused_bytes(long long Q, long long QC, long long m_max) { return 8 * Q + 4 * QC + 16 * (m_max + 1); }
+
+// A barrier for data exchanged through LDS only: __syncthreads() would also wait
+// for the value tables' stores, which no wave of the launch reads.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 template <bool DEGEN>
 __global__ __launch_bounds__(kFusedThreads) void k_trellis_fused(TrellisRun a) {
   __shared__ __align__(16) unsigned char pool[kFusedLds];
-  const TrellisModel md = a.models[blockIdx.x];
+  const TrellisModel md = a.models[blockIdx.y];
   const int32_t M = md.m.M;
   const TrellisBand& b = a.band;
-  const int32_t n = a.n, Q = static_cast<int32_t>(a.Q), QC = static_cast<int32_t>(a.QC);
+  const TrellisColumns& cb = a.cols;
+  const int2 own = cb.own[blockIdx.x];
+  const int32_t* lim = cb.lim + (long long)blockIdx.x * cb.lim_stride;  // lim[d] = lim_{M-1-d}
+  const int32_t cmin = lim[M - 2], c1 = own.y, rmin = b.p_lo[cmin];
+  const int32_t q0 = cb.pb[cmin], x0 = cb.qb[cmin];
+  const int32_t n_cells = cb.pb[c1] - q0, n_pairs = cb.qb[c1] - x0;
+  // the part's rows, whole: cells [row0, row0 + n_row) of the band, some of them outside the part's columns
+  const int32_t row0 = static_cast<int32_t>(b.rowoff[rmin]), n_row = static_cast<int32_t>(b.rowoff[c1]) - row0;
   const int tid = threadIdx.x;
   const float INF = __builtin_inff();
-  int2* kin = reinterpret_cast<int2*>(pool);           // (rowoff - s_lo, qoff - q_lo) of node k
-  int2* prg = kin + n;                                 // predecessors [p_lo, p_hi) of node r
-  float2* VA = reinterpret_cast<float2*>(prg + n);     // (V_{i-1}, A(r, c)) of every cell: one read per term
-  float* C = reinterpret_cast<float*>(VA + Q);         // C(k, c) of every two-step pair
-  int16_t* crow = reinterpret_cast<int16_t*>(C + QC);  // row of every cell
-  for (int32_t k = tid; k < n; k += kFusedThreads) {
-    const int32_t r0 = static_cast<int32_t>(b.rowoff[k]), r1 = static_cast<int32_t>(b.rowoff[k + 1]);
-    kin[k] = make_int2(r0 - b.s_lo[k], static_cast<int32_t>(b.qoff[k]) - b.q_lo[k]);
-    prg[k] = make_int2(b.p_lo[k], b.p_hi[k]);
-    for (int32_t q = r0; q < r1; ++q) crow[q] = static_cast<int16_t>(k);
-  }
-  for (int32_t q = tid; q < Q; q += kFusedThreads) VA[q].y = b.A[q];
-  for (int32_t q = tid; q < QC; q += kFusedThreads) C[q] = b.C[q];
-  __syncthreads();
+  float2* VA = reinterpret_cast<float2*>(pool);           // (V_{i-1}, A) of the part's cells, by column
+  float* C = reinterpret_cast<float*>(VA + n_cells);      // C of its two-step pairs, by column
+  // of every step: the model angles, frame gap and first live column
+  struct Step {
+    float2 th;
+    int32_t dtm, live;
+  };
+  Step* steps = reinterpret_cast<Step*>(pool + kFusedLds) - M;
+  for (int32_t i = tid; i < M; i += kFusedThreads)
+    steps[i] = i < 2 ? Step{make_float2(0.f, 0.f), 0, 0}
+                     : Step{md.theta[i], md.m.t[i] - md.m.t[i - 1], lim[M - 1 - i]};
+  for (int32_t q = tid; q < n_cells; q += kFusedThreads) VA[q].y = cb.At[q0 + q];
+  for (int32_t q = tid; q < n_pairs; q += kFusedThreads) C[q] = cb.Ct[x0 + q];
 
-  // the thread's cells and step 1: V_1(r, c) = l1 (U_0(r) + U_1(c)) + l2 |dt|
-  int32_t cr[kFusedSlots], cc[kFusedSlots], lo[kFusedSlots], hi[kFusedSlots], dt[kFusedSlots];
-  float arc[kFusedSlots];
-  bool same[kFusedSlots];
+  // the thread's cells and step 1: V_1(r, c) = l1 (U_0(r) + U_1(c)) + l2 |dt|.
+  // Packed in 16 bits each (at most 8192 cells, 40.8k pairs and 32,767 nodes): the
+  // places of the first predecessor's cell (k, r) in VA and pair (k, c) in C, the
+  // cell's own place in VA, the number of predecessors.  Cells outside the part's
+  // columns have column -1.
+  uint32_t at[kFusedSlots], me[kFusedSlots];
+  int32_t cc[kFusedSlots], dt[kFusedSlots];
+  float arc[kFusedSlots], nv[kFusedSlots];
+  uint32_t same = 0;  // bit j: the points of cell j coincide
   const int32_t dtm1 = md.m.t[1] - md.m.t[0];
 #pragma unroll
   for (int j = 0; j < kFusedSlots; ++j) {
-    const int32_t q = tid + kFusedThreads * j;
-    const bool valid = q < Q;
-    const int32_t r = valid ? crow[q] : 0;
-    const int32_t c = valid ? q - kin[r].x : 0;  // s_lo[r] + (q - rowoff[r])
-    const int2 p = prg[r];
-    cr[j] = r;
-    cc[j] = c;
-    lo[j] = valid ? p.x : 0;
-    hi[j] = valid ? p.y : 0;
-    dt[j] = a.t[c] - a.t[r];
-    arc[j] = valid ? VA[q].y : 0.f;
-    if (DEGEN) {
-      const float2 xr = a.xy[r], xc = a.xy[c];
-      same[j] = xr.x == xc.x && xr.y == xc.y;
-    } else {
-      same[j] = false;
-    }
-    if (valid) {
-      const float v = first_value(a, md.U[r], md.U[n + c], dtm1, dt[j]);
-      VA[q].x = v;
-      md.V[q] = v;
+    const int32_t x = tid + kFusedThreads * j;
+    at[j] = me[j] = 0;
+    cc[j] = -1;
+    dt[j] = 0;
+    arc[j] = nv[j] = 0.f;
+    if (x < n_row) {
+      const int32_t r = cb.row[row0 + x], c = b.s_lo[r] + (row0 + x - static_cast<int32_t>(b.rowoff[r]));
+      if (c >= cmin && c < c1) {
+        // (a row before cmin has its predecessors outside the part: its cells are needed at step 1 only)
+        const int32_t k = b.p_lo[r], n_pred = r >= cmin ? b.p_hi[r] - k : 0;
+        if (n_pred > 0)
+          at[j] = static_cast<uint32_t>(cb.pb[r] - q0) | static_cast<uint32_t>(cb.qb[c] - x0 + (k - cb.qp_lo[c])) << 16;
+        me[j] = static_cast<uint32_t>(cb.pb[c] - q0 + (r - b.p_lo[c])) | static_cast<uint32_t>(n_pred) << 16;
+        cc[j] = c;
+        dt[j] = a.t[c] - a.t[r];
+        arc[j] = b.A[row0 + x];
+        if (DEGEN) {
+          const float2 xr = a.xy[r], xc = a.xy[c];
+          if (xr.x == xc.x && xr.y == xc.y) same |= 1u << j;
+        }
+        const float v = first_value(a, md.U[r], md.U[a.n + c], dtm1, dt[j]);
+        VA[me[j] & 0xffffu].x = v;
+        if (c >= own.x) md.V[row0 + x] = v;
+      }
     }
   }
-  __syncthreads();
+  float u[kFusedSlots];  // U of the cells' columns, read a step ahead
+  const auto read_u = [&](int32_t i) {
+    const float* Ui = md.U + (long long)i * a.n;
+#pragma unroll
+    for (int j = 0; j < kFusedSlots; ++j)
+      if (cc[j] >= 0) u[j] = Ui[cc[j]];
+  };
+  if (M > 2) read_u(2);
+  lds_barrier();
 
   for (int32_t i = 2; i < M; ++i) {
-    const float2 th = md.theta[i];
-    const int32_t dtm = md.m.t[i] - md.m.t[i - 1];
+    const Step st = steps[i];
+    const float2 th = st.th;
+    const int32_t dtm = st.dtm, live = st.live;  // columns from `live` on are needed
     const float qw = a.lambda2 * (i <= M - 2 ? 2.f : 1.f);
-    const float* Ui = md.U + (long long)i * n;
-    float* Vi = md.V + (long long)(i - 1) * a.Q;
-    float nv[kFusedSlots];
+    float* Vi = md.V + (long long)(i - 1) * a.Q + row0;
 #pragma unroll
     for (int j = 0; j < kFusedSlots; ++j) {
-      nv[j] = INF;
-      if (tid + kFusedThreads * j < Q) {
+      if (cc[j] >= live) {
+        const float cu = __fmul_rn(a.lambda1, u[j]);
         float bm, be;
         cell_brackets(th, -arc[j], bm, be);
-        const int32_t r = cr[j], c = cc[j];
+        const float2* va = VA + (at[j] & 0xffffu);
+        const float* cx = C + (at[j] >> 16);
+        const bool sm = same >> j & 1u;
         float best = INF;
-        // unrolled by two (the whole video at T = 10, one model: 0.49 ms per run,
-        // against 0.53 not unrolled and 0.52 by four)
-#pragma unroll 2
-        for (int32_t k = lo[j]; k < hi[j]; ++k) {
-          const int2 kk = kin[k];
-          const int32_t off = kk.x + r;  // cell (k, r)
-          const float2 va = VA[off];
-          best = fminf(best, relax<DEGEN>(va.x, va.y, C[kk.y + c], bm, be, th, same[j], a.w));
+        const int32_t n_pred = me[j] >> 16;
+        int32_t k = 0;
+        for (; k + 1 < n_pred; k += 2) {
+          const float2 v0 = va[k], v1 = va[k + 1];
+          const float t0 = relax<DEGEN>(v0.x, v0.y, cx[k], bm, be, th, sm, a.w);
+          const float t1 = relax<DEGEN>(v1.x, v1.y, cx[k + 1], bm, be, th, sm, a.w);
+          best = fminf(fminf(best, t0), t1);
         }
-        nv[j] = step_value(__fmul_rn(a.lambda1, Ui[c]), qw, dtm, dt[j], best);
+        if (k < n_pred) {
+          const float2 v0 = va[k];
+          best = fminf(best, relax<DEGEN>(v0.x, v0.y, cx[k], bm, be, th, sm, a.w));
+        }
+        nv[j] = step_value(cu, qw, dtm, dt[j], best);
       }
     }
-    __syncthreads();  // every read of V_{i-1} done
+    if (i + 1 < M) read_u(i + 1);
+    lds_barrier();  // every read of V_{i-1} done
 #pragma unroll
-    for (int j = 0; j < kFusedSlots; ++j) {
-      const int32_t q = tid + kFusedThreads * j;
-      if (q < Q) {
-        VA[q].x = nv[j];
-        Vi[q] = nv[j];
+    for (int j = 0; j < kFusedSlots; ++j)
+      if (cc[j] >= live) {
+        VA[me[j] & 0xffffu].x = nv[j];
+        if (cc[j] >= own.x) Vi[tid + kFusedThreads * j] = nv[j];
       }
-    }
-    __syncthreads();
+    lds_barrier();
+  }
+}
+
+// The direction tables by column: cell (k, c) and pair (k, c) of column c =
+// blockIdx.x, k ascending.
+__global__ __launch_bounds__(64) void k_trellis_columns(TrellisBand b, TrellisColumns cb) {
+  const int32_t c = blockIdx.x;
+  for (int32_t q = cb.pb[c] + threadIdx.x; q < cb.pb[c + 1]; q += 64) {
+    const int32_t k = b.p_lo[c] + (q - cb.pb[c]);
+    cb.At[q] = b.A[b.base[2LL * k] + c];
+  }
+  for (int32_t q = cb.qb[c] + threadIdx.x; q < cb.qb[c + 1]; q += 64) {
+    const int32_t k = cb.qp_lo[c] + (q - cb.qb[c]);
+    cb.Ct[q] = b.C[b.base[2LL * k + 1] + c];
   }
 }
 
@@ -634,6 +686,21 @@ __global__ __launch_bounds__(kFusedThreads) void k_trellis_fused(TrellisRun a) {
 // video without a closeness limit: 378 -> 75 us; 50 models at T = 10: 53 -> 27).
 constexpr int kFinalThreads = 1024;
 constexpr int kFinalNodes = 4096;
+
+// The minimum over a wave's 64 lanes (no lane holds NaN), in every lane.
+__device__ __forceinline__ float wave_min(float x) {
+  const auto step = [&](auto ctrl) {
+    const int o = __builtin_amdgcn_update_dpp(0x7f800000, __float_as_int(x), decltype(ctrl)::value, 0xf, 0xf, false);
+    x = fminf(x, __int_as_float(o));
+  };
+  step(std::integral_constant<int, 0x111>{});  // row_shr 1, 2, 4, 8: lane 15 of each row of 16
+  step(std::integral_constant<int, 0x112>{});
+  step(std::integral_constant<int, 0x114>{});
+  step(std::integral_constant<int, 0x118>{});
+  step(std::integral_constant<int, 0x142>{});  // lane 15 of a row to the next row, then lane 31 to rows 2, 3
+  step(std::integral_constant<int, 0x143>{});
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63));
+}
 
 template <bool DEGEN>
 __global__ __launch_bounds__(kFinalThreads) void k_trellis_final(TrellisRun a) {
@@ -735,8 +802,13 @@ __global__ __launch_bounds__(kFinalThreads) void k_trellis_final(TrellisRun a) {
     const auto meet = [&](float ov, int32_t ok, float oa) {
       if (ov < tot || (ov == tot && ok < bk)) { tot = ov; bk = ok; ta = oa; }
     };
-    for (int off = 32; off > 0; off >>= 1) meet(__shfl_xor(tot, off), __shfl_xor(bk, off), __shfl_xor(ta, off));
-    if (wide) {
+    if (!wide) {  // one predecessor a lane, k ascending: the first lane of the minimum
+      const float m = wave_min(tot);
+      const int first = __ffsll(static_cast<long long>(__ballot(tot == m))) - 1;
+      bk = __builtin_amdgcn_readlane(bk, first);
+      ta = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(ta), first));
+    } else {
+      for (int off = 32; off > 0; off >>= 1) meet(__shfl_xor(tot, off), __shfl_xor(bk, off), __shfl_xor(ta, off));
       const int s = i & 1;  // the buffers alternate: one barrier a step
       if (lane == 0) {
         red_v[s][wv] = tot;
@@ -781,8 +853,14 @@ hipError_t launch_trellis_dirs(const TrellisBand& b, int32_t n, const float2* xy
   return hipGetLastError();
 }
 
-bool trellis_fits_fused(long long Q, long long QC, int32_t n) {
-  return Q > 0 && Q <= (long long)kFusedThreads * kFusedSlots && n <= 32767 && fused_bytes(Q, QC, n) <= kFusedLds;
+bool trellis_fits_fused(long long Q, long long QC, int32_t m_max) {
+  return Q > 0 && Q <= (long long)kFusedThreads * kFusedSlots && fused_bytes(Q, QC, m_max) <= kFusedLds;
+}
+
+hipError_t launch_trellis_columns(const TrellisBand& b, const TrellisColumns& c, int32_t n, hipStream_t st) {
+  if (n <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_trellis_columns, dim3(n), dim3(64), 0, st, b, c);
+  return hipGetLastError();
 }
 
 namespace {
@@ -812,11 +890,12 @@ hipError_t launch_trellis_run(const TrellisRun& a, int32_t n_tiles, TrellisTilin
   if (a.n_models <= 0) return hipSuccess;
   hipError_t e;
   if (fused) {
-    if (!trellis_fits_fused(a.Q, a.QC, a.n)) return hipErrorInvalidValue;
+    if (a.cols.parts < 1) return hipErrorInvalidValue;
+    const dim3 grid(a.cols.parts, a.n_models);
     if (degen)
-      hipLaunchKernelGGL(k_trellis_fused<true>, dim3(a.n_models), dim3(kFusedThreads), 0, st, a);
+      hipLaunchKernelGGL(k_trellis_fused<true>, grid, dim3(kFusedThreads), 0, st, a);
     else
-      hipLaunchKernelGGL(k_trellis_fused<false>, dim3(a.n_models), dim3(kFusedThreads), 0, st, a);
+      hipLaunchKernelGGL(k_trellis_fused<false>, grid, dim3(kFusedThreads), 0, st, a);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   } else if (a.Q > 0) {
     hipLaunchKernelGGL(k_trellis_first, dim3(a.n, a.n_models), dim3(64), 0, st, a);
@@ -827,10 +906,11 @@ hipError_t launch_trellis_run(const TrellisRun& a, int32_t n_tiles, TrellisTilin
       if ((e = hipGetLastError()) != hipSuccess) return e;
     }
   }
+  const dim3 one(a.n_models), threads(kFinalThreads);
   if (degen)
-    hipLaunchKernelGGL(k_trellis_final<true>, dim3(a.n_models), dim3(kFinalThreads), 0, st, a);
+    hipLaunchKernelGGL(k_trellis_final<true>, one, threads, 0, st, a);
   else
-    hipLaunchKernelGGL(k_trellis_final<false>, dim3(a.n_models), dim3(kFinalThreads), 0, st, a);
+    hipLaunchKernelGGL(k_trellis_final<false>, one, threads, 0, st, a);
   return hipGetLastError();
 }
 

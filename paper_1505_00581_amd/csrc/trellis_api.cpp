@@ -28,6 +28,7 @@ struct stm_trellis {
   float* U = nullptr;           // [m_total][n]
   float* V = nullptr;
   stm::TrellisBand band{};
+  stm::TrellisColumns cols{};   // fused runs only
   long long Q = 0, QC = 0;
   stm::TrellisTile* tiles = nullptr;
   int32_t n_tiles = 0;
@@ -96,6 +97,7 @@ int tr_enqueue(stm_trellis* p, float* e32, double* e64, double* eu, int32_t* as,
   a.models = p->models_dev;
   a.n_models = p->n_models;
   a.band = p->band;
+  a.cols = p->cols;
   a.tiles = p->tiles;
   a.t = block.t;
   a.xy = block.xy;
@@ -184,6 +186,44 @@ std::vector<stm::TrellisTile> make_wide_tiles(const std::vector<int32_t>& slo, c
     return x.k1 - x.k0 > y.k1 - y.k0;
   });
   return out;
+}
+
+// Column parts of a run in one launch: at most n_parts of them, cut so that the
+// largest number of cells a part computes over the steps of an m_max-point model
+// (own columns, and before them those that its later steps need) is smallest.
+// pb: cells before each column; plo: first predecessor of each node.
+void cut_parts(const std::vector<int32_t>& pb, const std::vector<int32_t>& plo, int m_max, int n_parts,
+               std::vector<int2>& own, std::vector<int32_t>& lim) {
+  const int32_t n = static_cast<int32_t>(plo.size());
+  const int depth = std::max(1, m_max - 1);  // steps 1..M-1
+  const auto limits = [&](int32_t c0) {
+    std::vector<int32_t> l(depth);
+    for (int d = 0; d < depth; ++d) l[d] = d == 0 ? c0 : plo[l[d - 1]];
+    return l;
+  };
+  // cuts with at most `budget` cells a part; false when that takes too many parts
+  const auto cut = [&](long long budget) {
+    own.clear();
+    lim.clear();
+    for (int32_t c0 = 0; c0 < n;) {
+      if ((int)own.size() == n_parts) return false;
+      const std::vector<int32_t> l = limits(c0);
+      long long before = 0;
+      for (int32_t x : l) before += pb[x];
+      int32_t c1 = c0 + 1;
+      while (c1 < n && (long long)depth * pb[c1 + 1] - before <= budget) ++c1;
+      own.push_back(make_int2(c0, c1));
+      lim.insert(lim.end(), l.begin(), l.end());
+      c0 = c1;
+    }
+    return true;
+  };
+  long long lo = 0, hi = (long long)depth * pb[n];  // hi: one part holds everything
+  while (lo < hi) {
+    const long long mid = (lo + hi) / 2;
+    if (cut(mid)) hi = mid; else lo = mid + 1;
+  }
+  (void)cut(hi);
 }
 
 int check_trellis_params(const stm_params* p) {
@@ -327,7 +367,8 @@ int stm_trellis_create(stm_ctx* ctx, const stm_points* models, int32_t n_models,
   TR_HIP(hipStreamSynchronize(st));
   p->Q = ends[0];
   p->QC = ends[1];
-  p->fused = !(params->flags & STM_TRELLIS_STEPWISE) && stm::trellis_fits_fused(p->Q, p->QC, n);
+  p->fused = !(params->flags & STM_TRELLIS_STEPWISE) && n <= 32767 &&
+             stm::trellis_fits_fused(p->Q, p->QC, p->m_max);
   // Tiling of the step launches (us per run of M = 30 models on the 754-node
   // video or its first 200 nodes, staged cells / 8 rows / 4 rows by 64 columns):
   //  * launches of few workgroups wait for the staging, whatever the width: 4 x
@@ -402,6 +443,57 @@ int stm_trellis_create(stm_ctx* ctx, const stm_points* models, int32_t n_models,
   TR_HIP(hipMemcpyAsync(&flag, val, sizeof(int32_t), hipMemcpyDeviceToHost, st));
   TR_HIP(hipStreamSynchronize(st));
   p->degen = flag != 0;
+
+  if (p->fused) {
+    // the band by column and its parts: one workgroup per part and model, as many
+    // as the chip has CUs (more parts than kMaxParts recompute more than they gain)
+    constexpr int kMaxParts = 16;
+    const long long T = stm::pair_limit(p->sp);
+    std::vector<int32_t> pb(n + 1, 0), qb(n + 1, 0), qpl(n);
+    for (int32_t c = 0; c < n; ++c) {
+      pb[c + 1] = pb[c] + std::max(0, phi[c] - plo[c]);
+      const auto at = [&](long long t) {  // first node with frame >= t
+        return static_cast<int32_t>(std::lower_bound(th.begin(), th.end(), t) - th.begin());
+      };
+      qpl[c] = T > 0 ? at(th[c] - 2 * T + 2) : 0;
+      qb[c + 1] = qb[c] + std::max(0, at((long long)th[c] - 1) - qpl[c]);
+    }
+    if (pb[n] != p->Q || qb[n] != p->QC) return bail(fail(STM_EHIP, "band by row and by column differ"));
+    int n_cu = 0;
+    TR_HIP(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, ctx->device));
+    std::vector<int2> own;
+    std::vector<int32_t> lim;
+    cut_parts(pb, plo, p->m_max, std::max(1, std::min(kMaxParts, n_cu / n_models)), own, lim);
+    std::vector<int32_t> row;
+    row.reserve(p->Q);
+    for (int32_t r = 0; r < n; ++r) row.insert(row.end(), std::max(0, shi[r] - slo[r]), r);
+    int32_t *d_pb, *d_qb, *d_qpl, *d_lim, *d_row;
+    int2* d_own;
+    TR_ALLOC(d_pb, int32_t, (size_t)n + 1);
+    TR_ALLOC(d_qb, int32_t, (size_t)n + 1);
+    TR_ALLOC(d_qpl, int32_t, n);
+    TR_ALLOC(d_row, int32_t, row.size());
+    TR_ALLOC(d_own, int2, own.size());
+    TR_ALLOC(d_lim, int32_t, lim.size());
+    TR_ALLOC(p->cols.At, float, std::max(1LL, p->Q));
+    TR_ALLOC(p->cols.Ct, float, std::max(1LL, p->QC));
+    TR_HIP(hipMemcpyAsync(d_pb, pb.data(), sizeof(int32_t) * pb.size(), hipMemcpyHostToDevice, st));
+    TR_HIP(hipMemcpyAsync(d_qb, qb.data(), sizeof(int32_t) * qb.size(), hipMemcpyHostToDevice, st));
+    TR_HIP(hipMemcpyAsync(d_qpl, qpl.data(), sizeof(int32_t) * qpl.size(), hipMemcpyHostToDevice, st));
+    TR_HIP(hipMemcpyAsync(d_own, own.data(), sizeof(int2) * own.size(), hipMemcpyHostToDevice, st));
+    TR_HIP(hipMemcpyAsync(d_lim, lim.data(), sizeof(int32_t) * lim.size(), hipMemcpyHostToDevice, st));
+    TR_HIP(hipMemcpyAsync(d_row, row.data(), sizeof(int32_t) * row.size(), hipMemcpyHostToDevice, st));
+    p->cols.row = d_row;
+    p->cols.pb = d_pb;
+    p->cols.qb = d_qb;
+    p->cols.qp_lo = d_qpl;
+    p->cols.own = d_own;
+    p->cols.lim = d_lim;
+    p->cols.parts = static_cast<int32_t>(own.size());
+    p->cols.lim_stride = static_cast<int32_t>(lim.size() / own.size());
+    TR_HIP(stm::launch_trellis_columns(b, p->cols, n, st));
+    TR_HIP(hipStreamSynchronize(st));  // the host arrays above go out of scope
+  }
 
   // unary tables, value tables, the model table and the re-score's pair table
   TR_ALLOC(p->U, float, (size_t)p->m_total * n);
