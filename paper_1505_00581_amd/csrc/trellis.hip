@@ -529,9 +529,9 @@ __global__ __launch_bounds__(NW * 64) void k_trellis_wide(TrellisRun a, int32_t 
 // adjacent: a term is two LDS reads at running addresses and its arithmetic.  The
 // threads take the cells by row, as the value tables hold them: the lanes of one
 // row read the same V and A (by column, the reads met in a quarter of the banks:
-// 198 us).  Bound by the VALU of a part's CU (the whole video
-// at T = 10, 50 models in 5 parts: FUSED_US us against 336 with one part, cells by row
-// and an offset table read per term).
+// 198 us).  Bound by the LDS latency of the short predecessor loops (the whole
+// video at T = 10, 50 models in 5 parts: 172 us for 28 steps of at most 2.9k cells
+// a part, against 336 with one part a model and an offset table read per term).
 constexpr int kFusedThreads = 1024;
 constexpr int kFusedSlots = 8;                                   // cells per thread
 constexpr int kFusedLds = 160 * 1024 - 512;                      // bytes of the LDS pool

@@ -3,7 +3,9 @@ registers, at the edges of their tiles: blocks of a few nodes, around one and
 two column windows and row groups that are not full, several points per frame
 (predecessors of some rows only), both readings of closeness and coincident
 points, against the FP64 oracle; many models (8 x 64) equal to lone ones
-(4 x 64) bit for bit; backtracking on more nodes than it holds in LDS."""
+(4 x 64) bit for bit; backtracking on more nodes than it holds in LDS; and
+every step in one launch, with a model's columns cut into 16, 8 or 1 parts and
+models of different sizes, equal to one launch per step bit for bit."""
 import dataclasses
 
 import numpy as np
@@ -87,6 +89,22 @@ def test_backtracking_on_many_nodes(ctx, n):
     a, b = stm.Trellis(ctx, [m], s, p), stm.Trellis(ctx, [m], s, p, 0, 4000)
     ra, rb = a.run(), b.run()
     assert np.isfinite(ra["energy32"]).all()
+    for k in ("energy32", "energy64", "energy_u64", "assign"):
+        np.testing.assert_array_equal(ra[k], rb[k])
+    a.close()
+    b.close()
+
+
+@pytest.mark.parametrize("n,per_frame,T,span,grid,models", [
+    (5, 1, 3, False, 0, 1), (17, 1, 3, False, 0, 2), (200, 1, 10, False, 0, 1), (200, 1, 10, True, 0, 30),
+    (201, 3, 4, False, 10, 3), (150, 1, 0, False, 0, 1), (127, 1, 0, False, 0, 2), (400, 2, 5, False, 0, 257)])
+def test_column_parts_equal_step_launches(ctx, n, per_frame, T, span, grid, models):
+    s = _block(9700 + n, n, per_frame, grid=grid)[1]
+    ms = [_block(9700 + n + q, n, per_frame, m=3 + q % 7)[0] for q in range(models)]
+    p = synth.Params(T=T, closeness_span=span)
+    a, b = stm.Trellis(ctx, ms, s, p), stm.Trellis(ctx, ms, s, p, stepwise=True)
+    ra, rb = a.run(), b.run()
+    assert a.info()["fused"] == (a.info()["cells_per_step"] <= 8192) and not b.info()["fused"]
     for k in ("energy32", "energy64", "energy_u64", "assign"):
         np.testing.assert_array_equal(ra[k], rb[k])
     a.close()
