@@ -16,7 +16,7 @@
 // on the scene block only and are built once.
 //
 // One launch per step i computes V_i from V_{i-1} for every model.  Wide bands
-// and launches of few workgroups run k_trellis_wide (operands in registers).
+// and launches of few workgroups run k_trellis_wide.
 // Otherwise a workgroup takes one tile, a rectangle of rows [r0, r1) by columns [c0, c1)
 // holding at most 1024 cells (narrow bands: up to 64 consecutive rows whose
 // successors span at most 128 nodes; wide bands: 32 rows by a 32-column
@@ -381,19 +381,23 @@ void k_trellis_step(TrellisRun a, int32_t i) {
   }
 }
 
-// ---- wide bands: every operand of a term in registers ------------------------------
+// ---- wide bands ---------------------------------------------------------------------
 // Where a step has many cells per row (no closeness limit, or many points per
-// frame), a workgroup takes R rows by 64 columns, lane = column, and its NW waves
-// split the predecessors.  For a predecessor k the values V_{i-1}(k, r) and A(k,
-// r) of the R rows are wave-uniform and adjacent in the band, so they are scalar
-// loads, and a lane reads one C(k, c) for its R cells: nothing is staged, and a
-// relaxation is its arithmetic.  The waves' minima meet in LDS.  Predecessors of
-// some of the rows only (at the ends of the range) take a second loop that tests
-// each row.  Scalar loads of R values stay inside the band: a predecessor of all R
-// rows has all R cells.
+// frame), and in launches of few workgroups, a workgroup takes R rows by 64
+// columns, lane = column, and its NW waves split the predecessors.  V_{i-1}(k, r)
+// and A(k, r) of a predecessor k are wave-uniform: a wave reads those of 64
+// predecessors at once and holds them in LDS rows of its own, read back as
+// broadcasts; a lane reads one C(k, c) for its R cells.  No barrier but the one
+// before the waves' minima meet.  8 rows by 4 waves is bound by the VALU (50 models on
+// the whole video without a closeness limit 34.3 ms, 78% of its issue rate; 36.2
+// staged), 4 rows by 8 waves by latency (one model there 1.27 ms; 4.06 staged).
+// As scalar loads instead, V and A gave 33.9 and 1.17 ms, but the predecessors of
+// only some rows then need a loop of their own, whose chain of scalar loads took
+// up to 2.3 ms.  Eight C values ahead instead of four: 35.4 and 1.31 ms.
 template <bool DEGEN, int R, int NW>
 __global__ __launch_bounds__(NW * 64) void k_trellis_wide(TrellisRun a, int32_t i) {
-  __shared__ float part[NW][R][64];
+  // per wave: V and A of 64 predecessors of the R rows; at the end its minima
+  __shared__ __align__(16) float stage[NW][64][2 * R];
   const TrellisModel md = a.models[blockIdx.y];
   const int32_t M = md.m.M;
   if (i >= M) return;
@@ -417,87 +421,92 @@ __global__ __launch_bounds__(NW * 64) void k_trellis_wide(TrellisRun a, int32_t 
     same[j] = xr.x == xc.x && xr.y == xc.y;
     best[j] = __builtin_inff();
   }
-  // this wave's predecessors [kb, ke), of which [mb, me) precede all R rows
+  // this wave's predecessors [kb, ke): 64 at a time, lane l reads V and A of
+  // predecessor l for the R rows (a chunk ahead of their use; +inf where l is no
+  // predecessor of the row, which changes no minimum) and the wave stages them in
+  // its own LDS rows; C is read four predecessors ahead
   const int32_t seg = (tl.k1 - tl.k0 + NW - 1) / NW;
   const int32_t kb = min(tl.k0 + wv * seg, tl.k1), ke = min(kb + seg, tl.k1);
-  const int32_t cb = ro(b.p_lo + (tl.r1 - 1)), ce = ro(b.p_hi + tl.r0);
-  const bool all = tl.r1 - tl.r0 == R && cb < ce;
-  const int32_t mb = all ? min(max(kb, cb), ke) : ke;
-  const int32_t me = all ? mb + (max(min(ke, ce) - mb, 0) & ~1) : ke;  // an even count: two per trip
-  // The operands of the next predecessor are read while the current one is
-  // relaxed.  Scalar loads return in any order, so a wave can only wait for all
-  // of them: the current operands are waited for (`arrived`) before the next
-  // ones are asked for.
-  struct Operands {
-    float v[R], ar[R], c;
-  };
-  struct Bases {
-    long long v, c;
-  };
-  const auto bases = [&](int32_t k) {
-    const long long* p = b.base + 2LL * min(k, me - 1);
-    return Bases{ro(p), ro(p + 1)};
-  };
-  const auto load = [&](const Bases& y) {
-    Operands t;
-    t.c = (b.C + y.c)[c];
-    const float* pv = Vp + (y.v + tl.r0);
-    const float* pa = b.A + (y.v + tl.r0);
+  constexpr int kAhead = 4;
+  int32_t rj[R], plo[R], phi[R];
 #pragma unroll
-    for (int j = 0; j < R; ++j) t.v[j] = ro(pv + j);
-#pragma unroll
-    for (int j = 0; j < R; ++j) t.ar[j] = ro(pa + j);
-    return t;
-  };
-  const auto arrived = [&](const Operands& t, const Bases& y) {
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int j = 0; j < R; ++j) asm volatile("" ::"s"(t.v[j]), "s"(t.ar[j]));
-    asm volatile("" ::"s"(y.v), "s"(y.c));
-    __builtin_amdgcn_sched_barrier(0);
-  };
-  float wl = w;  // in a vector register: a term's fma takes V from a scalar one
-  asm volatile("" : "+v"(wl));
-  if (mb < me) {
-    Bases y = bases(mb);
-    Operands t0 = load(y), t1;
-    y = bases(mb + 1);
-    for (int32_t k = mb; k < me; k += 2) {
-      float s0[R];
-      arrived(t0, y);
-      t1 = load(y);
-      y = bases(k + 2);
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int j = 0; j < R; ++j) s0[j] = relax<DEGEN>(t0.v[j], t0.ar[j], t0.c, bm[j], be[j], th, same[j], wl);
-      arrived(t1, y);
-      t0 = load(y);
-      y = bases(k + 3);
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int j = 0; j < R; ++j)
-        best[j] = fminf(fminf(best[j], s0[j]), relax<DEGEN>(t1.v[j], t1.ar[j], t1.c, bm[j], be[j], th, same[j], wl));
-    }
+  for (int j = 0; j < R; ++j) {
+    rj[j] = min(tl.r0 + j, tl.r1 - 1);
+    plo[j] = ro(b.p_lo + rj[j]);
+    phi[j] = min(ro(b.p_hi + rj[j]), ke);
   }
-  const auto some_rows = [&](int32_t from, int32_t to) {
-    for (int32_t k = from; k < to; ++k) {
-      const int32_t ql = ro(b.q_lo + k), qh = ro(b.q_hi + k);
-      if (ql >= qh) continue;  // no two-step pair: no admissible triple
-      const float ck = b.C[ro(b.base + (2LL * k + 1)) + min(max(c, ql), qh - 1)];
+  float rv[R], ra[R];
+  longlong2 bases, bases_next;  // this lane's predecessor's bases in the value and C tables
+  const auto fetch_bases = [&](int32_t k0) {
+    const int32_t k = min(k0 + lane, ke - 1);
+    bases_next.x = b.base[2LL * k];
+    bases_next.y = b.base[2LL * k + 1];
+  };
+  const auto fetch = [&](int32_t k0) {
+    bases = bases_next;
+    const int32_t k = k0 + lane;
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+      const bool in = k >= plo[j] && k < phi[j];
+      const long long q = in ? bases.x + rj[j] : 0;
+      const float v = Vp[q];
+      ra[j] = b.A[q];
+      rv[j] = in ? v : __builtin_inff();
+    }
+    fetch_bases(k0 + 64);
+  };
+  if (kb < ke) {
+    fetch_bases(kb);
+    fetch(kb);
+    for (int32_t k0 = kb; k0 < ke; k0 += 64) {
+      const int32_t n = min(64, ke - k0);
+      float* row = stage[wv][lane];
 #pragma unroll
       for (int j = 0; j < R; ++j) {
-        const int32_t r = tl.r0 + j;
-        if (r < tl.r1 && k >= ro(b.p_lo + r) && k < ro(b.p_hi + r)) {
-          const long long vo = ro(b.base + 2LL * k) + r;
-          best[j] = fminf(best[j], relax<DEGEN>(ro(Vp + vo), ro(b.A + vo), ck, bm[j], be[j], th, same[j], w));
+        row[j] = rv[j];
+        row[R + j] = ra[j];
+      }
+      // C of predecessor k0 + kk: a wave-uniform base, kept as an offset from the
+      // first.  Pairs outside the band (of cells or predecessors that do not count)
+      // read its neighbours, or the margin of n floats on either side of the table.
+      const long long c_first = __shfl(bases.y, 0);
+      const int32_t c_rel = static_cast<int32_t>(bases.y - c_first);
+      const float* cp = b.C + c_first + c;
+      const auto c_at = [&](int32_t kk) { return cp[__builtin_amdgcn_readlane(c_rel, min(kk, n - 1))]; };
+      float cn[kAhead];
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) cn[u] = c_at(u);
+      if (k0 + 64 < ke) fetch(k0 + 64);
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      for (int32_t g = 0; g < n; g += kAhead) {
+        float cc[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) cc[u] = cn[u];
+        if (g + kAhead < n)
+#pragma unroll
+          for (int u = 0; u < kAhead; ++u) cn[u] = c_at(g + kAhead + u);
+#pragma unroll
+        for (int u = 0; u < kAhead; u += 2) {
+          const float* s0 = stage[wv][g + u];
+          const float* s1 = stage[wv][g + u + 1];
+#pragma unroll
+          for (int j = 0; j < R; ++j)
+            best[j] = fminf(fminf(best[j], relax<DEGEN>(s0[j], s0[R + j], cc[u], bm[j], be[j], th, same[j], w)),
+                            relax<DEGEN>(s1[j], s1[R + j], cc[u + 1], bm[j], be[j], th, same[j], w));
         }
       }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
-  };
-  some_rows(kb, mb);
-  some_rows(me, ke);
+  }
+  float* part = &stage[0][0][0];  // [NW][R][64]: each wave's own rows hold its minima
+  static_assert(sizeof(stage) >= sizeof(float) * NW * R * 64, "minima in the staging rows");
+  __syncthreads();
 #pragma unroll
-  for (int j = 0; j < R; ++j) part[wv][j][lane] = best[j];
+  for (int j = 0; j < R; ++j) part[(wv * R + j) * 64 + lane] = best[j];
   __syncthreads();
   float* Vi = md.V + (long long)(i - 1) * a.Q;
   const int32_t dtm = md.m.t[i] - md.m.t[i - 1];
@@ -505,9 +514,9 @@ __global__ __launch_bounds__(NW * 64) void k_trellis_wide(TrellisRun a, int32_t 
   const float cu = __fmul_rn(a.lambda1, md.U[(long long)i * a.n + c]);
   for (int j = wv; j < tl.r1 - tl.r0; j += NW) {
     const int32_t r = tl.r0 + j, lo = b.s_lo[r], hi = b.s_hi[r];
-    float m = part[0][j][lane];
+    float m = part[j * 64 + lane];
 #pragma unroll
-    for (int q = 1; q < NW; ++q) m = fminf(m, part[q][j][lane]);
+    for (int q = 1; q < NW; ++q) m = fminf(m, part[(q * R + j) * 64 + lane]);
     if (tl.c0 + lane < tl.c1 && c >= lo && c < hi)
       Vi[b.rowoff[r] + (c - lo)] = step_value(cu, qw, dtm, a.t[c] - a.t[r], m);
   }

@@ -373,12 +373,12 @@ int stm_trellis_create(stm_ctx* ctx, const stm_points* models, int32_t n_models,
   // video or its first 200 nodes, staged cells / 8 rows / 4 rows by 64 columns):
   //  * launches of few workgroups wait for the staging, whatever the width: 4 x
   //    64 tiles split the predecessors over 8 waves (1 model, no limit 3710 /
-  //    3842 / 2281; T = 10 426 / 472 / 297; 8 models, 200 nodes, T = 40 721 / 868
+  //    3842 / 1270; T = 20 456 / 629 / 259; 8 models, 200 nodes, T = 40 721 / 868
   //    / 503);
-  //  * rows of 128 and more successors fill the 64 columns: 36225 / 33880 / 39067
-  //    (50 models, no limit), 9766 / 8191 / 7377 (8 models, which still want the
+  //  * rows of 128 and more successors fill the 64 columns: 36225 / 34310 / 39067
+  //    (50 models, no limit), 9766 / 8191 / 6592 (8 models, which still want the
   //    shorter tiles); rows of 64 only while the chip is not full (200 nodes, 50
-  //    models, T = 100: 2073 / 1650 / 1929; 754 nodes: 5038 / 6054 / 7815);
+  //    models, T = 100: 2073 / 1566 / 1929; 754 nodes: 5038 / 6054 / 7815);
   //  * narrower rows leave lanes without a cell: staged cells (T = 20, 50 models
   //    1020 / 1734 / 2095), in tiles of 1024, or of 256 when a step launch would
   //    have fewer than kFewTiles workgroups: one workgroup per CU leaves its
@@ -436,7 +436,11 @@ int stm_trellis_create(stm_ctx* ctx, const stm_points* models, int32_t n_models,
 
   // direction tables, and whether coincident points take part
   TR_ALLOC(b.A, float, std::max(1LL, p->Q));
-  TR_ALLOC(b.C, float, std::max(1LL, p->QC));
+  // (with a margin of n on either side: wide step launches read C at columns
+  // outside a predecessor's pairs, for cells that do not count)
+  TR_ALLOC(b.C, float, p->QC + 2LL * n);
+  TR_HIP(hipMemsetAsync(b.C, 0, sizeof(float) * (size_t)(p->QC + 2LL * n), st));
+  b.C += n;
   TR_HIP(hipMemsetAsync(val, 0, sizeof(int32_t), st));
   TR_HIP(stm::launch_trellis_dirs(b, n, bxy, bt, stm::span_limit(p->sp), val, st));
   int32_t flag = 0;
