@@ -232,8 +232,7 @@ stm::BatchLaunch plan_launch(stm_plan* p, const stm::PairDev* pairs, const int2*
 int plan_enqueue_tables(stm_plan* p, hipStream_t st) {
   for (int j = 0; j < p->n_scenes; ++j)
     STM_HIP(stm::launch_fstart(p->sv[j].t, p->sv[j].S, p->sv[j].F, p->fstart[j], st));
-  for (int i = 0; i < p->n_models; ++i)
-    STM_HIP(stm::launch_model_angles(p->mv[i], p->theta_all + p->mrow[i], st));
+  STM_HIP(stm::launch_models_angles(p->mv.data(), p->mrow.data(), p->n_models, p->theta_all, st));
   stm::ModelView all{nullptr, nullptr, p->mdesc_all, static_cast<int32_t>(p->m_total)};
   if (p->bf16)
     STM_HIP(stm::launch_to_bf16(p->mdesc_all, static_cast<int32_t>(p->m_total), p->dim,
@@ -1005,19 +1004,20 @@ int stm_plan_run_lists(stm_plan* p, const int32_t* const* cand, const int32_t* c
   const hipStream_t st = p->stream;
   // the lists: counts in [0, kc], ascending nodes of the pair's scene
   std::vector<stm::PairDev> ph = p->pairs_host;
-  STM_HIP(stm::launch_fill_i32(p->ls_bad, 1, 0, st));
+  long long rows_max = 0;
   for (size_t q = 0; q < ph.size(); ++q) {
     if (ph[q].n_tau > 0 && (!cand[q] || !count[q])) return fail(STM_EINVAL, "null list of a pair with offsets");
-    STM_HIP(stm::launch_check_lists(cand[q], count[q], (long long)ph[q].n_tau * ph[q].m.M, kc, ph[q].s.S, p->ls_bad,
-                                    st));
+    rows_max = std::max(rows_max, (long long)ph[q].n_tau * ph[q].m.M);
     ph[q].cand = cand[q];
     ph[q].ccount = count[q];
     ph[q].cstride = kc;
   }
   int32_t bad = 0;
-  STM_HIP(hipMemcpyAsync(&bad, p->ls_bad, sizeof(bad), hipMemcpyDeviceToHost, st));
+  STM_HIP(stm::launch_fill_i32(p->ls_bad, 1, 0, st));
   if (!ph.empty())
     STM_HIP(hipMemcpyAsync(p->ls_pairs_dev, ph.data(), ph.size() * sizeof(stm::PairDev), hipMemcpyHostToDevice, st));
+  STM_HIP(stm::launch_check_pair_lists(p->ls_pairs_dev, static_cast<int>(ph.size()), rows_max, kc, p->ls_bad, st));
+  STM_HIP(hipMemcpyAsync(&bad, p->ls_bad, sizeof(bad), hipMemcpyDeviceToHost, st));
   STM_HIP(hipStreamSynchronize(st));
   if (bad) return fail(STM_EINVAL, "candidate lists: count outside [0, kc], node outside the scene or not ascending");
 

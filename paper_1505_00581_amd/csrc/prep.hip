@@ -155,14 +155,30 @@ __global__ __launch_bounds__(kBlock) void k_unary_f32(ModelView m, SceneView s, 
 // ---- model angles of the triangle ending at point i (FP64, then rounded) ------
 // theta[i] = (angle at i-1 of (i, i-1, i-2), angle at i of (i-1, i, i-2)),
 // oriented, 0 for a zero-length side (Eq. 6).
-__global__ void k_model_angles(ModelView m, float2* __restrict__ theta) {
-  const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= m.M) return;
+__device__ __forceinline__ void model_angle(const float2* __restrict__ xy, int32_t i, float2* __restrict__ theta) {
   if (i < 2) { theta[i] = make_float2(0.f, 0.f); return; }
-  const float2 pi = m.xy[i], pj = m.xy[i - 1], pk = m.xy[i - 2];
+  const float2 pi = xy[i], pj = xy[i - 1], pk = xy[i - 2];
   const double mid = ang64(pi.x, pi.y, pj.x, pj.y, pk.x, pk.y);
   const double end = ang64(pj.x, pj.y, pi.x, pi.y, pk.x, pk.y);
   theta[i] = make_float2(static_cast<float>(mid), static_cast<float>(end));
+}
+
+__global__ void k_model_angles(ModelView m, float2* __restrict__ theta) {
+  const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < m.M) model_angle(m.xy, i, theta);
+}
+
+// Several models in one launch (model blockIdx.y): each is a few microseconds
+// of latency, so fifty launches took 97 us and one takes 3.
+constexpr int kAngleModels = 64;  // models per launch, passed as kernel arguments
+struct AngleModels {
+  const float2* xy[kAngleModels];
+  long long row[kAngleModels];
+  int32_t M[kAngleModels];
+};
+__global__ void k_models_angles(AngleModels m, float2* __restrict__ theta) {
+  const int32_t i = blockIdx.x * blockDim.x + threadIdx.x, q = blockIdx.y;
+  if (i < m.M[q]) model_angle(m.xy[q], i, theta + m.row[q]);
 }
 
 // ---- work counts (one 64-lane block per offset) --------------------------------
@@ -282,6 +298,22 @@ hipError_t launch_unary_f32(const ModelView& m, const SceneView& s, float* U, hi
 
 hipError_t launch_model_angles(const ModelView& m, float2* theta, hipStream_t st) {
   hipLaunchKernelGGL(k_model_angles, dim3((m.M + 63) / 64), dim3(64), 0, st, m, theta);
+  return hipGetLastError();
+}
+
+hipError_t launch_models_angles(const ModelView* m, const long long* row, int n, float2* theta, hipStream_t st) {
+  for (int q0 = 0; q0 < n; q0 += kAngleModels) {
+    AngleModels a{};
+    const int k = n - q0 < kAngleModels ? n - q0 : kAngleModels;
+    int32_t m_max = 1;
+    for (int q = 0; q < k; ++q) {
+      a.xy[q] = m[q0 + q].xy;
+      a.row[q] = row[q0 + q];
+      a.M[q] = m[q0 + q].M;
+      m_max = a.M[q] > m_max ? a.M[q] : m_max;
+    }
+    hipLaunchKernelGGL(k_models_angles, dim3((m_max + 63) / 64, k), dim3(64), 0, st, a, theta);
+  }
   return hipGetLastError();
 }
 

@@ -197,6 +197,8 @@ hipError_t launch_unary_f32(const ModelView& m, const SceneView& s, float* U, hi
 hipError_t launch_count(const ModelView& m, const SceneView& s, const SearchParams& sp,
                         int32_t tau0, int32_t n_tau, unsigned long long* counts, hipStream_t st);
 hipError_t launch_model_angles(const ModelView& m, float2* theta, hipStream_t st);
+// The same for n models, model q's angles from theta + row[q].
+hipError_t launch_models_angles(const ModelView* m, const long long* row, int n, float2* theta, hipStream_t st);
 
 // BF16 split-precision unary table.  launch_to_bf16 writes x [n_valid][dim]
 // rounded to BF16 into out [np][bf16_padded_dim(dim)] (zero padding) and the
@@ -464,6 +466,9 @@ hipError_t launch_pruner_infer(const PrunerInfer& q, hipStream_t st);
 // Checks caller-given lists [rows][kc] with counts [rows]; ORs error bits into *bad.
 hipError_t launch_check_lists(const int32_t* cand, const int32_t* count, long long rows, int kc, int S, int32_t* bad,
                               hipStream_t st);
+// The lists of every pair (at most rows_max each, cand and ccount set).
+hipError_t launch_check_pair_lists(const PairDev* pairs, int n_pairs, long long rows_max, int kc, int32_t* bad,
+                                   hipStream_t st);
 // Exact re-solves of n offsets taus[] (rows r) back into outputs indexed by tau - tau0.
 hipError_t launch_scatter_fallback(const int32_t* taus, int n, int tau0, int M, const float* e32, const double* e64,
                                   const double* eu, const int32_t* as, float* o32, double* o64, double* ou,
