@@ -39,10 +39,11 @@
 // one point per frame, lists spanning many frames) a group has only a few
 // cells, so the packed variant numbers all cells of a step across the chunks
 // and gives lane l of packed chunk p cell 64 p + l, each lane with its own
-// predecessor range; the minima, and so every result, are the same.  Per step the LDS holds the previous V cells
-// with their directions and the (a_{i-2}, a_i) direction table; the new cells
-// stay in registers until every wave has finished reading, then replace the
-// old ones.  Only admissible cells are ever read back.
+// predecessor range; the minima, and so every result, are the same.  Per step
+// the LDS holds the previous V cells with their directions and the (a_{i-2},
+// a_i) direction table; the new cells stay in registers until every wave has
+// finished reading, then replace the old ones (packed: go to a second buffer).
+// Only admissible cells are ever read back.
 //
 // Degenerate triangles.  A zero-length side gives a scene angle of 0 in the
 // definition, which the direction form does not reproduce.  The fast variant
@@ -270,18 +271,26 @@ struct DummyShared<KL, true> {
   float dg[2];
 };
 
-// Packed schedules: first cell number of every chunk, and the step's cell count.
+// The cells of the previous step, [a_{i-2}][a_{i-1}]: (V_{i-1}, -phi(z_{i-2} ->
+// z_{i-1})).  Packed schedules keep two buffers of values, so that a step that
+// keeps the directions of the one before needs no barrier between reading and
+// publishing, beside the first cell number of every chunk and the step's cell
+// count.
 template <int KL, bool PACKED>
-struct PackedShared {};
+struct CellShared {
+  float2 va[KL * KL];
+};
 template <int KL>
-struct PackedShared<KL, true> {
+struct CellShared<KL, true> {
+  float v[2][KL * KL];
+  float dir[KL * KL];
   int16_t pstart[2][KL + 1];
   int32_t ptot[2];
+  int32_t same[8];  // list j (at j & 7) holds the nodes of list j - 1
 };
 
 template <int NW, int KL, bool DUMMY = false, bool PACKED = false>
-struct DPShared : DummyShared<KL, DUMMY>, PackedShared<KL, PACKED> {
-  float2 va[KL * KL];   // [a_{i-2}][a_{i-1}]: (V_{i-1}, -phi(z_{i-2} -> z_{i-1}))
+struct DPShared : DummyShared<KL, DUMMY>, CellShared<KL, PACKED> {
   float ct[KL * KL];    // [a_{i-2}][a_i]: -phi(z_{i-2} -> z_i)
   float2 cxy[4][KL];    // candidate ring: coordinates,
   int32_t ctt[4][KL];   //   frames,
@@ -325,9 +334,10 @@ struct Cands {
   __device__ __forceinline__ int node(int a) const { return list ? ro(list + a) : cand_node(r, a); }
 };
 
+template <bool LISTS = false>
 __device__ __forceinline__ Cands cands_of(const MatchView& a, int j) {
   Cands c;
-  if (a.cand) {
+  if (LISTS || a.cand) {
     c.list = a.cand + (long long)j * a.cstride;
     c.n = ro(a.ccount + j);
     c.r = CandRange{0, 0, 0, 0};
@@ -340,10 +350,11 @@ __device__ __forceinline__ Cands cands_of(const MatchView& a, int j) {
 }
 
 // Value table of step i (cells V_i(a_{i-1}, a_i), i = 1..M-2) inside the
-// matching's scratch vt [M-2][vs][vs], stored by column: V_i(r, c) at c * vs +
-// r, so that backtracking reads the values of one column (every predecessor of
-// the chosen cell) contiguously (with dummies, index K holds the epsilon state
-// on either side).
+// matching's scratch vt [M-2][vs][vs], V_i(r, c) at r * vs + c: the lanes of a
+// chunk run along rows, so a store touches a few lines; by column every lane
+// of it would touch its own (k_dp at 1387 offsets, 75 points, K = 64: 5.51 ms
+// against 5.72).  With dummies, index K holds the epsilon state on
+// either side.
 __device__ __forceinline__ float* vtable(float* vt, const MatchView& a, int i) {
   return vt + (long long)(i - 1) * a.vs * a.vs;
 }
@@ -360,11 +371,13 @@ struct DPResult {
 
 // Forward pass of one matching by the whole workgroup (NW waves): writes the
 // value tables of steps 1..M-2 to vtm and returns the optimum to every thread.
-template <int NW, bool DEGEN, int KL, bool DUMMY = false, bool PACKED = false, bool UNS = false>
-__device__ DPResult dp_forward(DPShared<NW, KL, DUMMY, PACKED>& sh, const MatchView& a, float* vtm) {
+template <int NW, bool DEGEN, int KL, bool DUMMY = false, bool PACKED = false, bool UNS = false, bool LISTS = false>
+__device__ __forceinline__ DPResult dp_forward(DPShared<NW, KL, DUMMY, PACKED>& sh, const MatchView& a, float* vtm) {
   static_assert(KL == 16 || KL == 32 || KL == 64, "list capacity");
   static_assert(!DUMMY || KL == kMaxList, "dummies use the 64-slot layout");
   static_assert(!PACKED || (KL == kMaxList && !DUMMY), "packed schedules: 64-slot layout, no dummies");
+  static_assert(!LISTS || PACKED, "list variant: packed schedules");
+  constexpr bool RUNS = LISTS && !DEGEN;  // steps whose lists do not change keep their tables
   constexpr int RPW = KL / NW;  // chunk slots per wave (a step has <= KL chunks)
   const int tau = a.tau;
   const int lane = threadIdx.x & 63;
@@ -403,6 +416,15 @@ __device__ DPResult dp_forward(DPShared<NW, KL, DUMMY, PACKED>& sh, const MatchV
       return valid;
     }
   };
+  // lists i, i - 1, i - 2 each hold the nodes of the list before them
+  auto same_lists = [&](int i) {
+    if constexpr (RUNS) {
+      const int32_t s = sh.same[i & 7] & sh.same[(i - 1) & 7] & sh.same[(i - 2) & 7];
+      return __builtin_amdgcn_readfirstlane(s) != 0;
+    } else {
+      return false;
+    }
+  };
   // sr, sc, sp: ring slots of the rows', columns' and predecessors' lists
   auto schedule = [&](int sr, int sc, int spv, int b) {
     const int32_t* trow = sh.ctt[sr];
@@ -418,37 +440,70 @@ __device__ DPResult dp_forward(DPShared<NW, KL, DUMMY, PACKED>& sh, const MatchV
                      ring, sr, sc, spv);
   };
 
-  // The candidates of list j, read by wave 0 in two halves: fetch_slot issues
-  // the reads into registers (its frame boundaries, then its nodes' position,
-  // frame and unary cost) a step before commit_slot stores them into ring slot
-  // j & 3, so that their latency overlaps the recursion of the step between.
+  // The candidates of list j, read by wave 0 in three parts, each a step before
+  // the next, so that their latencies overlap the recursions between: fetch_list
+  // issues the reads of the list (its frame boundaries, or its nodes),
+  // fetch_values those of its nodes' position, frame and unary cost, and
+  // commit_slot stores them into ring slot j & 3.
+  struct ListRegs {
+    Cands c;
+    int32_t node;  // explicit lists: this lane's entry
+  };
   struct SlotRegs {
     Cands c;
     float2 xy;
     int32_t t;
     float u;
+    int32_t node = -1;  // packed: this lane's node, -1 past the list
+    bool same = false;  // packed: the list holds the nodes of the list before
   };
-  auto fetch_slot = [&](int j) {
-    SlotRegs f;
+  int32_t count_l = 0;  // list variant: the lengths of 64 lists, one per lane
+  auto fetch_list = [&](int j) {
+    ListRegs l;
     if (wv == 0) {
-      f.c = cands_of(a, j);
-      if (lane < f.c.count()) {
-        const int n = f.c.node(lane);
-        f.xy = ro(a.s.xy + n);
-        f.t = ro(a.s.t + n);
+      if (LISTS) {
+        if ((j & 63) == 0) count_l = a.ccount[min(j + lane, M - 1)];
+        l.c.list = a.cand + (long long)j * a.cstride;
+        l.c.n = __builtin_amdgcn_readlane(count_l, j & 63);
+        l.c.r = CandRange{0, 0, 0, 0};
+      } else {
+        l.c = cands_of(a, j);
+      }
+      if (l.c.list) l.node = ro(l.c.list + (lane < a.cstride ? lane : 0));
+    }
+    return l;
+  };
+  // f: the previous list's values, kept where the lists hold the same nodes
+  auto fetch_values = [&](int j, const ListRegs& l, SlotRegs& f) {
+    if (wv == 0) {
+      f.c = l.c;
+      const int n = f.c.list ? l.node : cand_node(f.c.r, lane);
+      const bool in = lane < f.c.count();
+      if constexpr (RUNS) {
+        const int nd = in ? n : -1;
+        f.same = j > 0 && __all(nd == f.node);
+        f.node = nd;
+        if (lane == 0) sh.same[j & 7] = f.same;
+      }
+      if (in) {
+        if (!f.same) {
+          f.xy = ro(a.s.xy + n);
+          f.t = ro(a.s.t + n);
+        }
         f.u = ro(a.U + (long long)j * a.us + n);
       }
     }
-    return f;
   };
-  auto commit_slot = [&](int j, const SlotRegs& f) {
+  // unary: the slot holds the list's other data already
+  auto commit_slot = [&](int j, const SlotRegs& f, bool unary = false) {
     if (wv == 0) {
       const int k = f.c.count();
       const int sl = j & 3;
+      if (lane < k) sh.cu[sl][lane] = a.lambda1 * f.u;
+      if (unary) return;
       if (lane < k) {
         sh.cxy[sl][lane] = f.xy;
         sh.ctt[sl][lane] = f.t;
-        sh.cu[sl][lane] = a.lambda1 * f.u;
       }
       if (lane == 0) {
         sh.ck[sl] = k;
@@ -456,20 +511,39 @@ __device__ DPResult dp_forward(DPShared<NW, KL, DUMMY, PACKED>& sh, const MatchV
       }
     }
   };
-  auto load_slot = [&](int j) { commit_slot(j, fetch_slot(j)); };
 
+  ListRegs list_next;  // list i + 2 in flight during step i - 1's recursion and step i's phase 1
+  SlotRegs next;       // list i + 1's values, likewise
   if (threadIdx.x == 0) sh.flag = 0;
-  load_slot(0);
-  load_slot(1);
-  load_slot(2);
+  {
+    const ListRegs l0 = fetch_list(0), l1 = fetch_list(1), l2 = fetch_list(2);
+    SlotRegs f0, f1, f2;
+    fetch_values(0, l0, f0);
+    f1 = f0;
+    fetch_values(1, l1, f1);
+    f2 = f1;
+    fetch_values(2, l2, f2);
+    next = f2;
+    commit_slot(0, f0);
+    commit_slot(1, f1);
+    commit_slot(2, f2);
+  }
   __syncthreads();
   if (wv == kBuilder) schedule(0, 1, -1, 1);
   __syncthreads();
-  SlotRegs next;  // list i + 1 in flight during step i - 1's recursion and step i's phase 1
-  if (3 < M) next = fetch_slot(3);
+  if (3 < M) fetch_values(3, fetch_list(3), next);
+  if (4 < M) list_next = fetch_list(4);
 
   float vr[RPW], ar[RPW];
-  int pi[RPW];  // LDS index (row * KL + column) of each slot's cell, -1: none
+  // LDS index (row * KL + column) of each slot's cell, negative: none; packed:
+  // in the low 12 bits, then the first predecessor and the count (7 bits each)
+  int pi[RPW];
+  constexpr int kCell = PACKED ? 0xfff : -1;
+  // packed: largest count of the slot's lanes, and kFew if a lane has fewer than
+  // four predecessors
+  constexpr int kFew = 1 << 8;
+  int longest[PACKED ? RPW : 1];
+  int b_prev = 1;             // schedule buffer of the previous step
 #pragma unroll
   for (int s = 0; s < RPW; ++s) { vr[s] = INF; ar[s] = 0.f; pi[s] = -1; }
 
@@ -491,8 +565,11 @@ __device__ DPResult dp_forward(DPShared<NW, KL, DUMMY, PACKED>& sh, const MatchV
         const float q = a.lambda2 * fabsf(static_cast<float>(dtm - (tp - tr)));
         vr[s] = (sh.cu[0][r] + sh.cu[1][col]) + q;
         ar[s] = neg_dir<DEGEN>(xr, xa);
-        if (valid) vt[col * VS + r] = vr[s];
+        if (valid) vt[r * VS + col] = vr[s];
         pi[s] = valid ? r * KL + col : -1;
+        if constexpr (PACKED) {
+          if (valid) sh.v[1][pi[s]] = vr[s];
+        }
       }
     }
     if constexpr (DUMMY) {
@@ -501,12 +578,12 @@ __device__ DPResult dp_forward(DPShared<NW, KL, DUMMY, PACKED>& sh, const MatchV
         if (lane < sh.ck[1]) {
           const float e = cw + sh.cu[1][lane];
           sh.de[1][lane] = e;
-          vt[lane * VS + Kc] = e;
+          vt[Kc * VS + lane] = e;
         }
         if (lane < sh.ck[0]) {
           const float f = sh.cu[0][lane] + cw;
           sh.df[1][lane] = f;
-          vt[Kc * VS + lane] = f;
+          vt[lane * VS + Kc] = f;
         }
         if (lane == 0) {
           sh.dg[1] = cw + cw;
@@ -516,24 +593,166 @@ __device__ DPResult dp_forward(DPShared<NW, KL, DUMMY, PACKED>& sh, const MatchV
     }
   }
 
+  // Angles and frames of the model points, one point per lane and 64 points at
+  // a time, read by readlane (kLanes: where a step is short a scalar read of its
+  // point is waited for, 0.9 of 4.6 ms over blocks of 60 nodes without their
+  // terms; where the terms fill the step it is hidden).
+  constexpr bool kLanes = PACKED || KL < kMaxList;
+  float2 th_l = make_float2(0.f, 0.f);
+  int32_t tm_l = 0, tm_prev = 0;
+  auto load_points = [&](int i0) {
+    const int j = min(i0 + lane, M - 1);
+    th_l = a.theta[j];
+    tm_l = a.m.t[j];
+  };
+  if constexpr (kLanes) {
+    load_points(0);
+    tm_prev = __builtin_amdgcn_readlane(tm_l, 1);
+  }
+  // the angles of point i and its frames since point i - 1
+  auto point = [&](int i, float2& th, int& dtm) {
+    if constexpr (kLanes) {
+      if ((i & 63) == 0) load_points(i);
+      th.x = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(th_l.x), i & 63));
+      th.y = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(th_l.y), i & 63));
+      const int tm = __builtin_amdgcn_readlane(tm_l, i & 63);
+      dtm = tm - tm_prev;
+      tm_prev = tm;
+    } else {
+      th = ro(a.theta + i);
+      dtm = ro(a.m.t + i) - ro(a.m.t + (i - 1));
+    }
+  };
+
+  // Packed cells: the minimum over a lane's predecessors [lo, lo + len) of its
+  // cell (row r, column col).  The wave runs to its longest range: four
+  // predecessors per trip, the last trip moved back onto the end of the lane's
+  // range (a repeated predecessor changes no minimum), one or two left over one
+  // at a time; lanes with fewer than four take theirs one by one instead.
+  auto packed_min = [&](int vb, int r, int col, int lo, int len, int longest, float bm, float be, float2 th,
+                        bool same) {
+    float best = INF;
+    if constexpr (PACKED) {
+      const float* vcol = sh.v[vb] + r;
+      const float* dcol = sh.dir + r;
+      const float* ccol = sh.ct + col;
+      const float w = a.w;
+      const int n = longest & (kFew - 1);
+      const int end = max(lo + len - 1, 0);  // the lane's last predecessor
+      const int k1 = max(end - 3, 0), k0 = min(lo, k1);
+      int j = 0;
+      for (; j + 2 < n; j += 4) {
+        const int o = min(k0 + j, k1) * KL;
+        const float* vk = vcol + o;
+        const float* dk = dcol + o;
+        const float* ck = ccol + o;
+        const float t0 = relax<DEGEN, UNS>(vk[0], dk[0], ck[0], bm, be, th, same, w);
+        const float t1 = relax<DEGEN, UNS>(vk[KL], dk[KL], ck[KL], bm, be, th, same, w);
+        const float t2 = relax<DEGEN, UNS>(vk[2 * KL], dk[2 * KL], ck[2 * KL], bm, be, th, same, w);
+        const float t3 = relax<DEGEN, UNS>(vk[3 * KL], dk[3 * KL], ck[3 * KL], bm, be, th, same, w);
+        best = fminf(fminf(best, fminf(fminf(t0, t1), t2)), t3);
+      }
+      for (; j < n; ++j) {
+        const int o = min(lo + j, end) * KL;
+        best = fminf(best, relax<DEGEN, UNS>(vcol[o], dcol[o], ccol[o], bm, be, th, same, w));
+      }
+      if (longest & kFew) {
+        float few = INF;
+        for (j = 0; j < min(n, 3); ++j) {
+          const int o = min(lo + j, end) * KL;
+          few = fminf(few, relax<DEGEN, UNS>(vcol[o], dcol[o], ccol[o], bm, be, th, same, w));
+        }
+        best = len < 4 ? (len > 0 ? few : INF) : best;
+      }
+    }
+    return best;
+  };
+
+  // A run of steps whose lists all hold the same nodes (a block searched whole):
+  // schedule, cells, ranges and directions stay those of step i - 1, the lists
+  // change their unary costs only, and one barrier a step is enough.  NS: chunk
+  // slots per wave (steps of more than 2 NW chunks are bound by their terms and
+  // take the loop below).  Returns the first step past the run.  Bound by
+  // instruction issue and the barrier (nine chunks on eight waves at T = 10).
+  // 50 models x 678 blocks of 60 nodes, 30 points: 6.0 ms with the tables kept,
+  // 13.9 with every step built anew; spreading the ninth chunk over all waves
+  // cost as much as it evened out.
+  auto same_steps = [&](int i, int nch, auto ns) {
+    constexpr int NS = decltype(ns)::value;
+    if constexpr (RUNS) {
+      int dt[NS];
+#pragma unroll
+      for (int s = 0; s < NS; ++s)
+        dt[s] = sh.ctt[i & 3][pi[s] & (KL - 1)] - sh.ctt[(i - 1) & 3][(pi[s] >> 6) & (KL - 1)];
+      for (;;) {
+        if (i + 1 < M) commit_slot(i + 1, next, next.same);
+        if (i + 2 < M) fetch_values(i + 2, list_next, next);
+        if (i + 3 < M) list_next = fetch_list(i + 3);
+        const bool again = i + 1 < M && __builtin_amdgcn_readfirstlane(sh.same[(i + 1) & 7]) != 0;
+        float2 th;
+        int dtm;
+        point(i, th, dtm);
+        const float qw = a.lambda2 * (i <= M - 2 ? 2.f : 1.f);
+        float* vt = i <= M - 2 ? vtable(vtm, a, i) : nullptr;
+        const int vb = (i & 1) ^ 1;
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+          if (wv + NW * s < nch) {
+            const int r = (pi[s] >> 6) & (KL - 1), col = pi[s] & (KL - 1);
+            float bm, be;
+            cell_consts<UNS>(th, ar[s], bm, be);
+            const float best = packed_min(vb, r, col, (pi[s] >> 12) & 127, (pi[s] >> 19) & 127, longest[s], bm, be,
+                                          th, false);
+            const float v = (sh.cu[i & 3][col] + qw * fabsf(static_cast<float>(dtm - dt[s]))) + best;
+            if (pi[s] >= 0) {
+              sh.v[vb ^ 1][pi[s] & kCell] = v;
+              if (vt) vt[r * VS + col] = v;
+            }
+          }
+        }
+        __syncthreads();
+        ++i;
+        if (!again) break;
+      }
+    }
+    return i;
+  };
+
   // ---- points 2 .. M-1 -----------------------------------------------------------
   for (int i = 2; i < M; ++i) {
+    if constexpr (RUNS) {
+      if (i >= 3 && same_lists(i)) {
+        const int n = n_slots(b_prev);
+        if (n <= 2 * NW) {
+          i = n <= NW ? same_steps(i, n, std::integral_constant<int, 1>{})
+                      : same_steps(i, n, std::integral_constant<int, 2>{});
+          if (i >= M) break;
+        }
+      }
+    }
     const int s2 = (i - 2) & 3, s1 = (i - 1) & 3, s0 = i & 3;
     const int Kq = sh.ck[s2], Kp = sh.ck[s1], Kn = sh.ck[s0];
-    const int cur = i & 1, prv = cur ^ 1;
+    // Consecutive points with one and the same list (a block searched whole):
+    // schedule, cells and directions are those of the previous step.
+    const bool reuse = RUNS && i >= 3 && same_lists(i);
+    const int prv = PACKED ? b_prev : (i & 1) ^ 1, cur = reuse ? prv : prv ^ 1;
+    b_prev = cur;
 
     // Phase 1: publish the previous step's cells, build this step's schedule and
     // (a_{i-2}, a_i) direction table, prefetch the next candidate list.
-    {
+    if (!reuse) {
       const int nprev = n_slots(prv);
 #pragma unroll
       for (int s = 0; s < RPW; ++s) {
         const int ch = wv + NW * s;
-        if (ch < nprev && pi[s] >= 0) sh.va[pi[s]] = make_float2(vr[s], ar[s]);
+        if (ch < nprev && pi[s] >= 0) {
+          if constexpr (PACKED) sh.dir[pi[s] & kCell] = ar[s];
+          else sh.va[pi[s]] = make_float2(vr[s], ar[s]);
+        }
       }
     }
-    if (wv == kBuilder) schedule(s1, s0, s2, cur);
-    {
+    if (wv == kBuilder && !reuse) schedule(s1, s0, s2, cur);
+    if (!reuse) {
       // the (a_{i-2}, a_i) direction of row k, column c; a pair is used only
       // if some z_{i-1} fits strictly between its frames and within T of
       // both: 2 <= t_i - t_{i-2} <= 2T - 2 (node order: between its nodes,
@@ -586,16 +805,19 @@ __device__ DPResult dp_forward(DPShared<NW, KL, DUMMY, PACKED>& sh, const MatchV
       }
     }
     if (i + 1 < M) commit_slot(i + 1, next);
-    __syncthreads();
-    if (i + 2 < M) next = fetch_slot(i + 2);
+    if (!reuse) __syncthreads();
+    if (i + 2 < M) fetch_values(i + 2, list_next, next);
+    if (i + 3 < M) list_next = fetch_list(i + 3);
 
     // Phase 2: the minima over a_{i-2} of every admissible cell, chunk by chunk.
-    const float2 th = ro(a.theta + i);
-    const int dtm = ro(a.m.t + i) - ro(a.m.t + (i - 1));
+    float2 th;
+    int dtm;
+    point(i, th, dtm);
     const float qw = a.lambda2 * (i <= M - 2 ? 2.f : 1.f);
     float* vt = i <= M - 2 ? vtable(vtm, a, i) : nullptr;
     const float w = a.w;
     const int nch = n_slots(cur);
+    const int vb = (i & 1) ^ 1;  // packed: buffer of V_{i-1}
 #pragma unroll
     for (int s = 0; s < RPW; ++s) {
       const int ch = wv + NW * s;
@@ -603,37 +825,36 @@ __device__ DPResult dp_forward(DPShared<NW, KL, DUMMY, PACKED>& sh, const MatchV
       if constexpr (PACKED) {
         if (ch < nch) {
           // lane-own cell and predecessor range; the wave runs to the longest
-          // range, a lane past its own repeats its last predecessor, masked
-          int r, col, lo, hi;
-          const bool valid = packed_cell(sh.sched[cur], sh.pstart[cur], sh.nch[cur], sh.ptot[cur], ch * 64 + lane, r,
-                                         col, lo, hi);
+          // range, a lane past its own repeats its last predecessor (which
+          // changes no minimum)
+          bool same = false;
+          if (!reuse) {
+            int r, col, lo, hi;
+            const bool valid = packed_cell(sh.sched[cur], sh.pstart[cur], sh.nch[cur], sh.ptot[cur], ch * 64 + lane,
+                                           r, col, lo, hi);
+            const float2 xr = sh.cxy[s1][r], xa = sh.cxy[s0][col];
+            same = xa.x == xr.x && xa.y == xr.y;
+            if (!DEGEN && same && valid) sh.flag = 1;
+            ar[s] = neg_dir<DEGEN>(xr, xa);
+            const int n = hi - lo;
+            pi[s] = (r * KL + col) | lo << 12 | n << 19 | (valid ? 0 : 1 << 31);
+            int n_max = n;
+            for (int off = 32; off > 0; off >>= 1) n_max = max(n_max, __shfl_xor(n_max, off));
+            longest[s] = __builtin_amdgcn_readfirstlane(n_max) | (__any(n < 4) ? kFew : 0);
+          }
+          const int r = (pi[s] >> 6) & (KL - 1), col = pi[s] & (KL - 1);
+          const int lo = (pi[s] >> 12) & 127, len = (pi[s] >> 19) & 127;
           const int tr = sh.ctt[s1][r], tp = sh.ctt[s0][col];
-          const float2 xr = sh.cxy[s1][r], xa = sh.cxy[s0][col];
-          const bool same = xa.x == xr.x && xa.y == xr.y;
-          if (!DEGEN && same && valid) sh.flag = 1;
-          anew = neg_dir<DEGEN>(xr, xa);
+          anew = ar[s];
           float bm, be;
           cell_consts<UNS>(th, anew, bm, be);
-          const float2* vcol = sh.va + r;
-          const float* ccol = sh.ct + col;
-          const int len = hi - lo;
-          int longest = len;
-          for (int off = 32; off > 0; off >>= 1) longest = max(longest, __shfl_xor(longest, off));
-          longest = __builtin_amdgcn_readfirstlane(longest);
-          const int last = max(len - 1, 0);
-          float best = INF;
-          for (int j = 0; j < longest; ++j) {
-            const int kk = min(lo + min(j, last), KL - 1);
-            const float2 v0 = vcol[kk * KL];
-            const float t0 = relax<DEGEN, UNS>(v0.x, v0.y, ccol[kk * KL], bm, be, th, same, w);
-            best = fminf(best, j < len ? t0 : INF);
-          }
+          const float best = packed_min(vb, r, col, lo, len, longest[s], bm, be, th, same);
           const float q = qw * fabsf(static_cast<float>(dtm - (tp - tr)));
           vnew = (sh.cu[s0][col] + q) + best;
-          if (valid && vt) vt[col * VS + r] = vnew;
-          pi[s] = valid ? r * KL + col : -1;
-          vr[s] = vnew;
-          ar[s] = anew;
+          if (pi[s] >= 0) {
+            sh.v[vb ^ 1][pi[s] & kCell] = vnew;
+            if (vt) vt[r * VS + col] = vnew;
+          }
         }
       } else {
         if (ch < nch) {
@@ -689,7 +910,7 @@ __device__ DPResult dp_forward(DPShared<NW, KL, DUMMY, PACKED>& sh, const MatchV
           }
           const float q = qw * fabsf(static_cast<float>(dtm - (tp - tr)));
           vnew = (sh.cu[s0][col] + q) + best;
-          if (valid && vt) vt[col * VS + r] = vnew;
+          if (valid && vt) vt[r * VS + col] = vnew;
           pi[s] = valid ? r * KL + col : -1;
           vr[s] = vnew;
           ar[s] = anew;
@@ -718,7 +939,7 @@ __device__ DPResult dp_forward(DPShared<NW, KL, DUMMY, PACKED>& sh, const MatchV
         if (r < Kp && sub == 0) {
           const float v = cw + fminf(sh.de[prv][r], m);
           sh.df[cur][r] = v;
-          if (vt) vt[Kc * VS + r] = v;
+          if (vt) vt[r * VS + Kc] = v;
         }
       }
       if (wv == kBuilder) {
@@ -728,7 +949,7 @@ __device__ DPResult dp_forward(DPShared<NW, KL, DUMMY, PACKED>& sh, const MatchV
         if (lane < Kn) {
           const float v = sh.cu[s0][lane] + m;
           sh.de[cur][lane] = v;
-          if (vt) vt[lane * VS + Kc] = v;
+          if (vt) vt[Kc * VS + lane] = v;
         }
         if (lane == 0) {
           sh.dg[cur] = cw + m;
@@ -742,14 +963,20 @@ __device__ DPResult dp_forward(DPShared<NW, KL, DUMMY, PACKED>& sh, const MatchV
   // ---- optimum: first row-major minimum of V_{M-1}(a_{M-2}, a_{M-1}) ------------
   {
     constexpr int RS = KL + (DUMMY ? 1 : 0);  // row stride of the result index
-    const int last = (M - 1) & 1;
+    const int last = PACKED ? b_prev : (M - 1) & 1;
     const int nch = n_slots(last);
     float bv = INF;
     int bi = 0x7fffffff;
 #pragma unroll
     for (int s = 0; s < RPW; ++s) {
       const int ch = wv + NW * s;
-      if (ch < nch) {
+      if constexpr (PACKED) {
+        if (ch < nch && pi[s] >= 0) {
+          const int idx = pi[s] & kCell;
+          const float v = sh.v[(M - 1) & 1][idx];
+          if (v < bv || (v == bv && idx < bi)) { bv = v; bi = idx; }
+        }
+      } else if (ch < nch) {
         int r, col;
         if (slot_cell(last, ch, r, col)) {
           const int idx = r * RS + col;
@@ -801,39 +1028,60 @@ __device__ DPResult dp_forward(DPShared<NW, KL, DUMMY, PACKED>& sh, const MatchV
 //
 // The candidates of a list do not depend on the path, so each lane holds one
 // candidate (node, frame, coordinates) of the three lists of the current
-// step, and the next list is fetched while the current step runs; the chosen
-// nodes' data come from their lanes by shuffles.  The one read that waits for
-// the previous step's choice is the value-table column of the chosen cell.
+// step; a list is read two steps and its nodes' data one step before their
+// use.  The chosen cell is wave-uniform, so its data come from their lanes by
+// readlane and the minimum by DPP: of the step's chain only the read of the
+// chosen cell's values waits for memory.  1387 matchings of 75 points: 157 us,
+// 228 with the lists' reads in the chain and shuffles.
 struct LaneCand {
   int node;   // scene node of this lane's candidate, -1 past the list
   int t;      // its frame
   float2 xy;  // its coordinates
   int n;      // list length
 };
+struct LaneList {
+  Cands c;
+  int node;  // explicit lists: this lane's entry
+};
 
-__device__ __forceinline__ LaneCand lane_cand(const MatchView& a, int j, int lane) {
-  const Cands q = cands_of(a, j);
+template <bool LISTS>
+__device__ __forceinline__ LaneList lane_list(const MatchView& a, int j, int lane) {
+  LaneList l;
+  l.c = cands_of<LISTS>(a, j);
+  l.node = l.c.list ? ro(l.c.list + (lane < a.cstride ? lane : 0)) : 0;
+  return l;
+}
+
+__device__ __forceinline__ LaneCand lane_cand(const MatchView& a, const LaneList& l, int lane) {
   LaneCand L;
-  L.n = q.count();
-  L.node = lane < L.n ? q.node(lane) : -1;
+  L.n = l.c.count();
+  L.node = lane < L.n ? (l.c.list ? l.node : cand_node(l.c.r, lane)) : -1;
   L.t = L.node >= 0 ? ro(a.s.t + L.node) : 0;
   L.xy = L.node >= 0 ? ro(a.s.xy + L.node) : make_float2(0.f, 0.f);
   return L;
 }
 
-template <bool DEGEN, bool DUMMY = false, bool UNS = false>
-__device__ void backtrack_wave(const MatchView& a, const float* vtm, int r, int c, int lane,
+__device__ __forceinline__ float lane_value(float x, int l) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), l));
+}
+
+template <bool DEGEN, bool DUMMY = false, bool UNS = false, bool LISTS = false>
+__device__ __forceinline__ void backtrack_wave(const MatchView& a, const float* vtm, int r_end, int c_end, int lane,
                                int32_t* out) {
   const int M = a.m.M, Kc = a.sp.K, VS = a.vs;
   const int T = pair_limit(a.sp), TS = span_limit(a.sp);
   const float INF = __builtin_inff();
   // candidate index idx of a list held in lanes -> its node (dummy: kDummyNode)
   auto node_at = [&](const LaneCand& L, int idx) {
-    return DUMMY && idx == kEps ? kDummyNode : __shfl(L.node, idx);
+    return DUMMY && idx == kEps ? kDummyNode : __builtin_amdgcn_readlane(L.node, idx);
   };
-  LaneCand Lc = lane_cand(a, M - 1, lane);
-  LaneCand Lr = lane_cand(a, M - 2, lane);
-  LaneCand Lk = lane_cand(a, M - 3, lane);
+  int r = __builtin_amdgcn_readfirstlane(r_end), c = __builtin_amdgcn_readfirstlane(c_end);
+  const LaneList l1 = lane_list<LISTS>(a, M - 1, lane), l2 = lane_list<LISTS>(a, M - 2, lane), l3 = lane_list<LISTS>(a, M - 3, lane);
+  LaneList ln;
+  if (M >= 4) ln = lane_list<LISTS>(a, M - 4, lane);
+  LaneCand Lc = lane_cand(a, l1, lane);
+  LaneCand Lr = lane_cand(a, l2, lane);
+  LaneCand Lk = lane_cand(a, l3, lane);
   {
     const int nc0 = node_at(Lc, c), nr0 = node_at(Lr, r);
     if (lane == 0) {
@@ -844,43 +1092,38 @@ __device__ void backtrack_wave(const MatchView& a, const float* vtm, int r, int 
   for (int i = M - 1; i >= 2; --i) {
     const int nk = Lk.n;
     const float* vp = vtable(vtm, a, i - 1);
-    // the column of the chosen cell: V_{i-1}(k, r) for every candidate k
-    float vcol = INF;
-    if (lane < nk && !(DUMMY && r == kEps)) vcol = vp[r * VS + lane];
-    // the next list, fetched while this step runs
-    LaneCand Ln;
-    if (i >= 3) Ln = lane_cand(a, i - 3, lane);
     float tot = INF, teps = INF;
-    if (DUMMY && r == kEps) {
-      // V_i(eps, .) = ... + min(V_{i-1}(eps, eps), min_k V_{i-1}(k, eps))
-      if (lane < nk) tot = vp[Kc * VS + lane];
-      teps = vp[Kc * VS + Kc];
-    } else {
-      const float2 xr = make_float2(__shfl(Lr.xy.x, r), __shfl(Lr.xy.y, r));
-      const int tr = __shfl(Lr.t, r);
-      const int nr = __shfl(Lr.node, r);
-      if (DUMMY) teps = vp[r * VS + Kc];
-      if (DUMMY && c == kEps) {
-        // V_i(r, eps) = l1 W^d + min(V_{i-1}(eps, r), min_k V_{i-1}(k, r))
-        if (lane < nk && admissible(Lk.t, tr, T)) tot = vcol;
-      } else {
-        const float2 xa = make_float2(__shfl(Lc.xy.x, c), __shfl(Lc.xy.y, c));
-        const int tc = __shfl(Lc.t, c);
-        const float2 th = ro(a.theta + i);
-        const bool same = xa.x == xr.x && xa.y == xr.y;
-        float bm, be;
-        cell_consts<UNS>(th, neg_dir<DEGEN>(xr, xa), bm, be);
-        if (lane < nk && consecutive_ok(a.sp, T, Lk.node, Lk.t, nr, tr) && span_ok(Lk.t, tc, TS))
-          tot = relax<DEGEN, UNS>(vcol, neg_dir<DEGEN>(Lk.xy, xr), neg_dir<DEGEN>(Lk.xy, xa), bm, be, th, same, a.w);
-      }
+    const bool r_eps = DUMMY && r == kEps, c_eps = DUMMY && c == kEps;
+    const int nr = __builtin_amdgcn_readlane(Lr.node, r), tr = __builtin_amdgcn_readlane(Lr.t, r);
+    const int tc = __builtin_amdgcn_readlane(Lc.t, c);
+    // the lanes with an admissible predecessor of the chosen cell, and their
+    // values V_{i-1}(k, r)
+    bool adm = lane < nk;
+    if (!r_eps) adm = adm && (c_eps ? admissible(Lk.t, tr, T)
+                                    : consecutive_ok(a.sp, T, Lk.node, Lk.t, nr, tr) && span_ok(Lk.t, tc, TS));
+    float v = INF;
+    if (adm) v = vp[lane * VS + (r_eps ? Kc : r)];
+    if (DUMMY) teps = vp[Kc * VS + (r_eps ? Kc : r)];
+    // the next lists, fetched while this step runs
+    LaneCand Ln;
+    if (i >= 3) Ln = lane_cand(a, ln, lane);
+    if (i >= 4) ln = lane_list<LISTS>(a, i - 4, lane);
+    if (r_eps || c_eps) {
+      // V_i(eps, .) = ... + min(V_{i-1}(eps, eps), min_k V_{i-1}(k, eps)),
+      // V_i(r, eps) = l1 W^d + min(V_{i-1}(eps, r), min_k V_{i-1}(k, r))
+      tot = v;
+    } else if (adm) {
+      const float2 xr = make_float2(lane_value(Lr.xy.x, r), lane_value(Lr.xy.y, r));
+      const float2 xa = make_float2(lane_value(Lc.xy.x, c), lane_value(Lc.xy.y, c));
+      const float2 th = ro(a.theta + i);
+      const bool same = xa.x == xr.x && xa.y == xr.y;
+      float bm, be;
+      cell_consts<UNS>(th, neg_dir<DEGEN>(xr, xa), bm, be);
+      tot = relax<DEGEN, UNS>(v, neg_dir<DEGEN>(Lk.xy, xr), neg_dir<DEGEN>(Lk.xy, xa), bm, be, th, same, a.w);
     }
-    int bk = lane;
-    for (int off = 32; off > 0; off >>= 1) {
-      const float ot = __shfl_xor(tot, off);
-      const int ok = __shfl_xor(bk, off);
-      if (ot < tot || (ot == tot && ok < bk)) { tot = ot; bk = ok; }
-    }
-    if (DUMMY && teps < tot) bk = kEps;
+    const float best = wave_min(tot);
+    int bk = __ffsll(static_cast<long long>(__ballot(tot == best))) - 1;
+    if (DUMMY && teps < best) bk = kEps;
     const int nbk = node_at(Lk, bk);
     if (lane == 0) out[i - 2] = nbk;
     c = r;
@@ -917,14 +1160,14 @@ __device__ __forceinline__ float* scratch_of(const DPLaunch& a, int tl) {
   return a.vt + (long long)tl * (a.m.M - 2) * vs * vs;
 }
 
-template <int NW, bool DEGEN, int KL, bool DUMMY = false, bool PACKED = false, bool UNS = false>
+template <int NW, bool DEGEN, int KL, bool DUMMY = false, bool PACKED = false, bool UNS = false, bool LISTS = false>
 __global__ __launch_bounds__(NW * 64)
-__attribute__((amdgpu_waves_per_eu(KL == kMaxList && NW == 8 ? 4 : 1)))
+__attribute__((amdgpu_waves_per_eu(KL < kMaxList || NW == 8 ? 4 : 1)))
 void k_dp(DPLaunch a) {
   __shared__ DPShared<NW, KL, DUMMY, PACKED> sh;
   const int tl = blockIdx.x;
   if (DEGEN && a.degen[tl] == 0) return;
-  const DPResult r = dp_forward<NW, DEGEN, KL, DUMMY, PACKED, UNS>(sh, view_of(a, tl), scratch_of(a, tl));
+  const DPResult r = dp_forward<NW, DEGEN, KL, DUMMY, PACKED, UNS, LISTS>(sh, view_of(a, tl), scratch_of(a, tl));
   if (threadIdx.x == 0) {
     constexpr int RS = KL + (DUMMY ? 1 : 0);
     a.e32[tl] = r.v;
@@ -993,7 +1236,8 @@ __device__ __forceinline__ MatchView view_of(const BatchLaunch& b, const PairDev
 // the LDS of one matching would allow three, but at 80 registers the kernel
 // spills and runs slower (1.3% on the realistic workload, 3.9% on the batched
 // one).
-template <int NW, bool DEGEN, int KL = kMaxList, bool DUMMY = false, bool PACKED = false, bool UNS = false>
+template <int NW, bool DEGEN, int KL = kMaxList, bool DUMMY = false, bool PACKED = false, bool UNS = false,
+          bool LISTS = false>
 __global__ __launch_bounds__(NW * 64)
 __attribute__((amdgpu_waves_per_eu(DUMMY || PACKED ? 4 : (NW >= 8 ? 4 : 3))))
 void k_dp_persistent(BatchLaunch b) {
@@ -1017,7 +1261,7 @@ void k_dp_persistent(BatchLaunch b) {
       const int2 it = b.items[item];
       const PairDev pd = b.pairs[it.x];
       const MatchView mv = view_of(b, pd, it.y);
-      const DPResult r = dp_forward<NW, DEGEN, KL, DUMMY, PACKED, UNS>(sh, mv, vwg + slot * b.vt_stride);
+      const DPResult r = dp_forward<NW, DEGEN, KL, DUMMY, PACKED, UNS, LISTS>(sh, mv, vwg + slot * b.vt_stride);
       if (threadIdx.x == 0) {
         if (!DEGEN && r.flag) {
           b.degen_items[atomicAdd(b.degen_count, 1)] = item;
@@ -1038,7 +1282,7 @@ void k_dp_persistent(BatchLaunch b) {
         int32_t* out = b.assign + pd.assign0 + (long long)it.y * pd.m.M;
         const int idx = bt_idx[wv];
         if (idx >= 0) {
-          backtrack_wave<DEGEN, DUMMY, UNS>(view_of(b, pd, it.y), vwg + wv * b.vt_stride, idx / RS, idx % RS, lane,
+          backtrack_wave<DEGEN, DUMMY, UNS, LISTS>(view_of(b, pd, it.y), vwg + wv * b.vt_stride, idx / RS, idx % RS, lane,
                                        out);
         } else {
           for (int i = lane; i < pd.m.M; i += 64) out[i] = -1;
@@ -1221,7 +1465,10 @@ hipError_t launch_dp_waves(const DPLaunch& a, hipStream_t st) {
     return hipGetLastError();
   }
   if (a.packed && a.sp.K > 32) {  // sparse scenes, long lists: packed schedules
-    hipLaunchKernelGGL((k_dp<8, DEGEN, 64, false, true>), dim3(a.n_tau), dim3(8 * 64), 0, st, a);
+    if (a.cand)
+      hipLaunchKernelGGL((k_dp<8, DEGEN, 64, false, true, false, true>), dim3(a.n_tau), dim3(8 * 64), 0, st, a);
+    else
+      hipLaunchKernelGGL((k_dp<8, DEGEN, 64, false, true>), dim3(a.n_tau), dim3(8 * 64), 0, st, a);
     return hipGetLastError();
   }
   if (a.sp.K <= 16) {
@@ -1263,7 +1510,11 @@ hipError_t launch_persistent_variant(const BatchLaunch& b, int n_wg, hipStream_t
     return hipGetLastError();
   }
   if (b.packed) {  // sparse scenes: packed schedules, 8 waves
-    hipLaunchKernelGGL((k_dp_persistent<8, DEGEN, kMaxList, false, true>), dim3(n_wg), dim3(8 * 64), 0, st, b);
+    if (b.lists)
+      hipLaunchKernelGGL((k_dp_persistent<8, DEGEN, kMaxList, false, true, false, true>), dim3(n_wg), dim3(8 * 64), 0,
+                         st, b);
+    else
+      hipLaunchKernelGGL((k_dp_persistent<8, DEGEN, kMaxList, false, true>), dim3(n_wg), dim3(8 * 64), 0, st, b);
     return hipGetLastError();
   }
   switch (b.waves) {

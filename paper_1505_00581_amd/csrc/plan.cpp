@@ -1029,6 +1029,7 @@ int stm_plan_run_lists(stm_plan* p, const int32_t* const* cand, const int32_t* c
   STM_HIP(stm::launch_fill_i32(p->counters, 3, 0, st));
   stm::BatchLaunch b = plan_launch(p, p->ls_pairs_dev, p->items_dev, p->n_items, e32, asg);
   b.sp.K = kc;
+  b.lists = 1;
   const bool timed = p->ctx->prof;
   if (timed) STM_HIP(hipEventRecord(p->ev_k0, st));
   STM_HIP(stm::launch_dp_persistent(b, p->n_cu * p->wgs_per_cu, st));

@@ -288,6 +288,7 @@ struct BatchLaunch {
   int32_t dummy = 0;    // dummy assignments (Eq. 2) enabled
   float cw = 0.f;       // lambda1 * W^d in FP32
   int32_t packed = 0;   // packed schedules (sparse scenes; no dummies)
+  int32_t lists = 0;    // every pair has explicit candidate lists
   float* e32;           // [rows]
   int32_t* assign;      // [sum over pairs of n_tau * M]
   int32_t waves;        // 4, 8 or 16 waves per workgroup

@@ -696,21 +696,6 @@ __global__ __launch_bounds__(64) void k_trellis_columns(TrellisBand b, TrellisCo
 constexpr int kFinalThreads = 1024;
 constexpr int kFinalNodes = 4096;
 
-// The minimum over a wave's 64 lanes (no lane holds NaN), in every lane.
-__device__ __forceinline__ float wave_min(float x) {
-  const auto step = [&](auto ctrl) {
-    const int o = __builtin_amdgcn_update_dpp(0x7f800000, __float_as_int(x), decltype(ctrl)::value, 0xf, 0xf, false);
-    x = fminf(x, __int_as_float(o));
-  };
-  step(std::integral_constant<int, 0x111>{});  // row_shr 1, 2, 4, 8: lane 15 of each row of 16
-  step(std::integral_constant<int, 0x112>{});
-  step(std::integral_constant<int, 0x114>{});
-  step(std::integral_constant<int, 0x118>{});
-  step(std::integral_constant<int, 0x142>{});  // lane 15 of a row to the next row, then lane 31 to rows 2, 3
-  step(std::integral_constant<int, 0x143>{});
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63));
-}
-
 template <bool DEGEN>
 __global__ __launch_bounds__(kFinalThreads) void k_trellis_final(TrellisRun a) {
   constexpr int kWaves = kFinalThreads / 64;
