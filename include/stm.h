@@ -611,7 +611,8 @@ STM_API int stm_plan_run_pruned(stm_plan* plan, stm_pruner* pruner, int32_t topk
 /* ---- tuning ----------------------------------------------------------------- */
 
 /* Waves per workgroup of the recursion kernel (one workgroup per matching):
- * 4, 8 or 16; 0 restores the default (8).  Results do not depend on it. */
+ * 4, 8 or 16; 0 restores the default (8, or 16 where a call has at most one
+ * matching per CU).  Results do not depend on it. */
 STM_API int stm_set_dp_waves(stm_ctx* ctx, int waves);
 
 /* ---- kernel timing for benchmarks -------------------------------------------- */

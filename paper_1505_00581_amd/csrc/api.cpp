@@ -460,8 +460,7 @@ int stm_count_work(stm_ctx* ctx, const stm_points* model, const stm_points* scen
 int stm_set_dp_waves(stm_ctx* ctx, int waves) {
   err().clear();
   if (!ctx) return fail(STM_EINVAL, "null context");
-  if (waves == 0) waves = 8;
-  if (waves != 4 && waves != 8 && waves != 16) return fail(STM_EINVAL, "waves must be 4, 8 or 16");
+  if (waves != 0 && waves != 4 && waves != 8 && waves != 16) return fail(STM_EINVAL, "waves must be 4, 8 or 16");
   ctx->dp_waves = waves;
   return STM_OK;
 }

@@ -1343,21 +1343,28 @@ __device__ __forceinline__ double wrap64(double x) {
   return x - two_pi * rint(x / two_pi);
 }
 
-// One wave re-scores the assignment z of one matching into e64[row], eu64[row].
+// A workgroup re-scores the assignment z of one matching into e64[tl], eu64[tl].
 // A dummy (kDummyNode) costs wd; a Delta term needs both of its points
 // matched, D^g all three, and only matched consecutive points are checked.
 // The descriptor distances are taken four points at a time, 16 lanes per
 // point striding its descriptor (coalesced reads; partial sums joined by a
-// 16-lane tree); the triangle terms one point per lane.
-__device__ void rescore_wave(const ModelView& m, const SceneView& s, const SearchParams& sp, double l1, double l2,
-                             double l3, double wd, const int32_t* __restrict__ z, long long tl,
-                             double* __restrict__ e64, double* __restrict__ eu64) {
-  const int lane = threadIdx.x & 63;
+// 16-lane tree); the triangle terms one point per lane.  A chain of dependent
+// reads bounds it, so W = 4 waves share a matching's points where few matchings
+// leave the chip idle (1387 of 75 points: 57 us, 96 with one wave) and one takes
+// each where there are many (34,000 of 30 points: 169 us, 220 with four).
+constexpr int kRescoreMany = 4096;
+template <int W>
+__device__ __forceinline__ void rescore(const ModelView& m, const SceneView& s, const SearchParams& sp, double l1, double l2,
+                                        double l3, double wd, const int32_t* __restrict__ z, long long tl,
+                                        double* __restrict__ e64, double* __restrict__ eu64) {
+  __shared__ double part_u[W], part_d[W];
+  __shared__ int part_bad[W];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int32_t T = pair_limit(sp), TS = span_limit(sp);
   const int M = m.M, dim = s.dim;
   const double inf = __builtin_inf();
   if (ro(z) == -1) {
-    if (lane == 0) {
+    if (threadIdx.x == 0) {
       if (e64) e64[tl] = inf;
       if (eu64) eu64[tl] = inf;
     }
@@ -1366,7 +1373,7 @@ __device__ void rescore_wave(const ModelView& m, const SceneView& s, const Searc
   double su = 0.0, sd = 0.0;
   int bad = 0;
   const int grp = lane >> 4, gl = lane & 15;
-  for (int i0 = 0; i0 < M; i0 += 4) {
+  for (int i0 = wv * 4; i0 < M; i0 += W * 4) {
     const int i = i0 + grp;
     const int n = i < M ? ro(z + i) : kDummyNode;
     double acc = 0.0;
@@ -1381,7 +1388,7 @@ __device__ void rescore_wave(const ModelView& m, const SceneView& s, const Searc
     for (int off = 8; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
     if (gl == 0 && i < M) su += n == kDummyNode ? wd : sqrt(acc);
   }
-  for (int i = lane; i < M; i += 64) {
+  for (int i = threadIdx.x; i < M; i += W * 64) {
     const int n = ro(z + i);
     const int nj = i >= 1 ? ro(z + (i - 1)) : kDummyNode;
     const int nk = i >= 2 ? ro(z + (i - 2)) : kDummyNode;
@@ -1424,19 +1431,32 @@ __device__ void rescore_wave(const ModelView& m, const SceneView& s, const Searc
     bad |= __shfl_xor(bad, off);
   }
   if (lane == 0) {
+    part_u[wv] = su;
+    part_d[wv] = sd;
+    part_bad[wv] = bad;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int q = 1; q < W; ++q) {
+      su += part_u[q];
+      sd += part_d[q];
+      bad |= part_bad[q];
+    }
     if (e64) e64[tl] = bad ? inf : l1 * su + l2 * sd;
     if (eu64) eu64[tl] = bad ? inf : l1 * su;
   }
 }
 
-__global__ __launch_bounds__(64) void k_rescore(ModelView m, SceneView s, SearchParams sp, double l1, double l2,
+template <int W>
+__global__ __launch_bounds__(W * 64) void k_rescore(ModelView m, SceneView s, SearchParams sp, double l1, double l2,
                                                double l3, double wd, const int32_t* __restrict__ assign,
                                                double* __restrict__ e64, double* __restrict__ eu64) {
   const int tl = blockIdx.x;
-  rescore_wave(m, s, sp, l1, l2, l3, wd, assign + (long long)tl * m.M, tl, e64, eu64);
+  rescore<W>(m, s, sp, l1, l2, l3, wd, assign + (long long)tl * m.M, tl, e64, eu64);
 }
 
-__global__ __launch_bounds__(64) void k_rescore_batch(const PairDev* __restrict__ pairs,
+template <int W>
+__global__ __launch_bounds__(W * 64) void k_rescore_batch(const PairDev* __restrict__ pairs,
                                                      const int2* __restrict__ items, int n_items,
                                                      SearchParams sp, double l1, double l2, double l3, double wd,
                                                      const int32_t* __restrict__ assign,
@@ -1445,14 +1465,22 @@ __global__ __launch_bounds__(64) void k_rescore_batch(const PairDev* __restrict_
   if (item >= n_items) return;
   const int2 it = items[item];
   const PairDev pd = pairs[it.x];
-  rescore_wave(pd.m, pd.s, sp, l1, l2, l3, wd, assign + pd.assign0 + (long long)it.y * pd.m.M,
-               pd.row0 + it.y, e64, eu64);
+  rescore<W>(pd.m, pd.s, sp, l1, l2, l3, wd, assign + pd.assign0 + (long long)it.y * pd.m.M,
+          pd.row0 + it.y, e64, eu64);
 }
 
 // Lists of at most 16 or 32 candidates take a smaller LDS layout and fewer
 // waves per matching (more matchings resident per CU); longer lists take the
-// 64-slot layout with the requested number of waves.  The arithmetic of every
-// cell is the same, so the results do not depend on the variant.
+// 64-slot layout with the requested number of waves.  Where the matchings of a
+// launch leave CUs idle, the steps of one bound the call, so more waves share
+// them.  Whole calls of 30 points, lists of 12 to 18, one, two and four waves:
+// 370, 290, 253 us up to 512 matchings; 398, 319, 283 at 1024; 461, 370, 414 at
+// 2048; 537, 570, 591 at 4096.  Lists of 20 to 32, two, four and eight waves:
+// 595, 408, 342 us at 512; 732, 526, 582 at 1024; 848, 844, 975 at 2048.  Lists
+// of 60, eight and sixteen waves: 681, 563 us at 256; 902, 918 at 512.  The
+// arithmetic of every cell is the same, so the results do not depend on the
+// variant.
+constexpr int kCUs = 256;
 template <bool DEGEN>
 hipError_t launch_dp_waves(const DPLaunch& a, hipStream_t st) {
   if (a.n_tau <= 0) return hipSuccess;
@@ -1472,14 +1500,24 @@ hipError_t launch_dp_waves(const DPLaunch& a, hipStream_t st) {
     return hipGetLastError();
   }
   if (a.sp.K <= 16) {
-    hipLaunchKernelGGL((k_dp<1, DEGEN, 16>), dim3(a.n_tau), dim3(64), 0, st, a);
+    if (a.n_tau <= 4 * kCUs)
+      hipLaunchKernelGGL((k_dp<4, DEGEN, 16>), dim3(a.n_tau), dim3(4 * 64), 0, st, a);
+    else if (a.n_tau <= 8 * kCUs)
+      hipLaunchKernelGGL((k_dp<2, DEGEN, 16>), dim3(a.n_tau), dim3(2 * 64), 0, st, a);
+    else
+      hipLaunchKernelGGL((k_dp<1, DEGEN, 16>), dim3(a.n_tau), dim3(64), 0, st, a);
     return hipGetLastError();
   }
   if (a.sp.K <= 32) {
-    hipLaunchKernelGGL((k_dp<2, DEGEN, 32>), dim3(a.n_tau), dim3(2 * 64), 0, st, a);
+    if (a.n_tau <= 2 * kCUs)
+      hipLaunchKernelGGL((k_dp<8, DEGEN, 32>), dim3(a.n_tau), dim3(8 * 64), 0, st, a);
+    else if (a.n_tau <= 4 * kCUs)
+      hipLaunchKernelGGL((k_dp<4, DEGEN, 32>), dim3(a.n_tau), dim3(4 * 64), 0, st, a);
+    else
+      hipLaunchKernelGGL((k_dp<2, DEGEN, 32>), dim3(a.n_tau), dim3(2 * 64), 0, st, a);
     return hipGetLastError();
   }
-  switch (a.waves) {
+  switch (a.waves ? a.waves : a.n_tau <= kCUs ? 16 : 8) {
     case 4:
       hipLaunchKernelGGL((k_dp<4, DEGEN, 64>), dim3(a.n_tau), dim3(4 * 64), 0, st, a);
       break;
@@ -1561,7 +1599,8 @@ hipError_t launch_rescore_batch(const PairDev* pairs, const int2* items, int n_i
                                 double lambda1, double lambda2, double lambda3, double w_dummy,
                                 const int32_t* assign, double* e64, double* eu64, hipStream_t st) {
   if (n_items <= 0 || (!e64 && !eu64)) return hipSuccess;
-  hipLaunchKernelGGL(k_rescore_batch, dim3(n_items), dim3(64), 0, st, pairs, items, n_items, sp,
+  const bool many = n_items > kRescoreMany;
+  hipLaunchKernelGGL((many ? k_rescore_batch<1> : k_rescore_batch<4>), dim3(n_items), dim3(many ? 64 : 256), 0, st, pairs, items, n_items, sp,
                      lambda1, lambda2, lambda3, w_dummy, assign, e64, eu64);
   return hipGetLastError();
 }
@@ -1576,7 +1615,8 @@ hipError_t launch_rescore(const ModelView& m, const SceneView& s, const SearchPa
                           double lambda2, double lambda3, double w_dummy, const int32_t* assign,
                           int32_t n_tau, double* e64, double* eu64, hipStream_t st) {
   if (n_tau <= 0 || (!e64 && !eu64)) return hipSuccess;
-  hipLaunchKernelGGL(k_rescore, dim3(n_tau), dim3(64), 0, st, m, s, sp, lambda1, lambda2, lambda3,
+  const bool many = n_tau > kRescoreMany;
+  hipLaunchKernelGGL((many ? k_rescore<1> : k_rescore<4>), dim3(n_tau), dim3(many ? 64 : 256), 0, st, m, s, sp, lambda1, lambda2, lambda3,
                      w_dummy, assign, e64, eu64);
   return hipGetLastError();
 }

@@ -56,7 +56,7 @@ struct stm_ctx {
   int64_t prof_matchings = 0;
   double prof_plan_ms = 0.0;      // recursion launches of plan runs (events inside the graph)
   int64_t prof_plan_launches = 0;
-  int dp_waves = 8;
+  int dp_waves = 0;  // 0: the launch's rule
 };
 
 // The learned candidate pruner: FP32 parameters packed as

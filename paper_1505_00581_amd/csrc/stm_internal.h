@@ -222,7 +222,7 @@ struct DPLaunch {
   float* e32;           // [n_tau]
   int2* last2;          // [n_tau]
   int32_t* degen;       // [n_tau], written by the fast variant
-  int32_t waves;        // waves per workgroup of the recursion: 4, 8 or 16
+  int32_t waves;        // waves per workgroup of the recursion: 4, 8, 16 or 0 (by the number of matchings)
   // explicit candidate lists (null: the windowed rule): offset tl, point j has
   // the nodes cand[(tl * M + j) * cstride + a], a < ccount[tl * M + j], ascending
   const int32_t* cand = nullptr;
