@@ -19,6 +19,7 @@
 // w3, b3], NI = 2 D + 8.
 #include <math.h>
 
+#include "dp_math.h"
 #include "stm_internal.h"
 
 namespace stm {
@@ -30,18 +31,10 @@ constexpr int H = kPrunerHidden;
 
 __device__ __forceinline__ int wave_argmin_node(const CandRange& c, const float* __restrict__ Urow, int lane) {
   const int k = c.k1 + c.k2;
-  float v = __builtin_inff();
-  int idx = 0x7fffffff;
-  if (lane < k) {
-    v = Urow[cand_node(c, lane)];
-    idx = lane;
-  }
-  for (int off = 32; off > 0; off >>= 1) {
-    const float ov = __shfl_xor(v, off);
-    const int oi = __shfl_xor(idx, off);
-    if (ov < v || (ov == v && oi < idx)) { v = ov; idx = oi; }
-  }
-  return k > 0 ? cand_node(c, idx) : -1;
+  if (k <= 0) return -1;
+  const float v = lane < k ? Urow[cand_node(c, lane)] : __builtin_inff();
+  const float best = wave_min(v);
+  return cand_node(c, __ffsll(static_cast<long long>(__ballot(v == best))) - 1);
 }
 
 // Candidate node and features of lane `lane` of group (tau, i); node -1 past
@@ -170,7 +163,9 @@ __global__ __launch_bounds__(256) void k_project_bf16(const uint16_t* __restrict
     }
 }
 
-// Inference: one wave per group, no block barriers after the set-up.
+// Inference: one wave per group, no block barriers after the set-up.  Bound by
+// instruction issue beside the matrix cores (173 us of them at 104,000 groups of
+// 64); two candidate tiles at a time share the reads of W2: 507 us, 562 with one.
 //
 // Layer 1 runs transposed, Z1^T [hidden k][candidate c], per 16 x 16 tile
 // (kt, ct): the accumulator starts at A'_i[k] + B_n[k] (A' = W1a (D f) + b1,
@@ -261,44 +256,53 @@ __global__ __launch_bounds__(kInferWaves * 64) __attribute__((amdgpu_waves_per_e
     for (int kt = 0; kt < 8; ++kt) arow[kt] = *reinterpret_cast<const float4*>(A + (long long)gi.y * H + 16 * kt + 4 * lq);
     float sc = -__builtin_inff();
 #pragma unroll 1
-    for (int ct = 0; ct < 4; ++ct) {
-      const int c = 16 * ct + lr;  // this lane's candidate in the tile
-      const int nc = node[c];
-      const float p0 = phi[c][lq], p1 = phi[c][lq + 4];
-      const float* brow = B + (long long)(nc < 0 ? 0 : nc) * H + 4 * lq;
-      bf16x8_t hb[4];
+    for (int c0 = 0; c0 < 4; c0 += 2) {  // two candidate tiles at a time share the reads of W2
+      bf16x8_t hb[2][4];
 #pragma unroll
-      for (int kt = 0; kt < 8; ++kt) {
-        const float4 bv = *reinterpret_cast<const float4*>(brow + 16 * kt);
-        f32x4_t z = {arow[kt].x + bv.x, arow[kt].y + bv.y, arow[kt].z + bv.z, arow[kt].w + bv.w};
-        z = __builtin_amdgcn_mfma_f32_16x16x4f32(w1c[kt][0], p0, z, 0, 0, 0);
-        z = __builtin_amdgcn_mfma_f32_16x16x4f32(w1c[kt][1], p1, z, 0, 0, 0);
+      for (int t = 0; t < 2; ++t) {
+        const int c = 16 * (c0 + t) + lr;  // this lane's candidate in the tile
+        const int nc = node[c];
+        const float p0 = phi[c][lq], p1 = phi[c][lq + 4];
+        const float* brow = B + (long long)(nc < 0 ? 0 : nc) * H + 4 * lq;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const float hv = nc < 0 ? 0.f : fmaxf(z[j], 0.f);
-          hb[kt >> 1][(kt & 1) * 4 + j] = static_cast<__bf16>(hv);  // v_cvt_pk_bf16_f32, nearest even
+        for (int kt = 0; kt < 8; ++kt) {
+          const float4 bv = *reinterpret_cast<const float4*>(brow + 16 * kt);
+          f32x4_t z = {arow[kt].x + bv.x, arow[kt].y + bv.y, arow[kt].z + bv.z, arow[kt].w + bv.w};
+          z = __builtin_amdgcn_mfma_f32_16x16x4f32(w1c[kt][0], p0, z, 0, 0, 0);
+          z = __builtin_amdgcn_mfma_f32_16x16x4f32(w1c[kt][1], p1, z, 0, 0, 0);
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            // v_cvt_pk_bf16_f32, nearest even; an empty slot's column is dropped below
+            hb[t][kt >> 1][(kt & 1) * 4 + j] = static_cast<__bf16>(fmaxf(z[j], 0.f));
+          }
         }
       }
-      float part = 0.f;
+      float part[2] = {0.f, 0.f};
 #pragma unroll 2
       for (int ot = 0; ot < 8; ++ot) {
-        f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+        f32x4_t acc[2] = {f32x4_t{0.f, 0.f, 0.f, 0.f}, f32x4_t{0.f, 0.f, 0.f, 0.f}};
         const uint16_t* wrow = sh.w2p + (16 * ot + lr) * kW2Row + lq * 8;
 #pragma unroll
         for (int pb = 0; pb < 4; ++pb) {
           const bf16x8_t wa = *reinterpret_cast<const bf16x8_t*>(wrow + pb * 32);
-          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa, hb[pb], acc, 0, 0, 0);
+#pragma unroll
+          for (int t = 0; t < 2; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa, hb[t][pb], acc[t], 0, 0, 0);
         }
         // rows of acc: output units o = 16 ot + 4 lq + j, column: candidate c
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
           const int o = 16 * ot + 4 * lq + j;
-          part = fmaf(fmaxf(acc[j] + sh.b2[o], 0.f), sh.w3[o], part);
+          const float b2o = sh.b2[o], w3o = sh.w3[o];
+#pragma unroll
+          for (int t = 0; t < 2; ++t) part[t] = fmaf(fmaxf(acc[t][j] + b2o, 0.f), w3o, part[t]);
         }
       }
-      part += __shfl_xor(part, 16);
-      part += __shfl_xor(part, 32);
-      if (ct == lq) sc = part + b3;  // lane l = 16 ct + l % 16 owns candidate l
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        part[t] += __shfl_xor(part[t], 16);
+        part[t] += __shfl_xor(part[t], 32);
+        if (c0 + t == lq) sc = part[t] + b3;  // lane l = 16 ct + l % 16 owns candidate l
+      }
     }
     if (n < 0) sc = -__builtin_inff();
     if (scores) scores[g * 64 + lane] = sc;
