@@ -209,34 +209,41 @@ int check_range(const Prepared& pr, int32_t tau_begin, int32_t tau_end) {
   return STM_OK;
 }
 
-int match_kernels(stm_ctx* ctx, const Prepared& pr, const stm_params* params, int32_t tau_begin, int n_tau,
-                  float* d_e32, double* d_e64, double* d_eu, int32_t* d_as, const MatchScratch& sc, bool timed) {
-  const int M = pr.m.M;
-  const hipStream_t st = pr.st;
+int match_kernels(stm_ctx* ctx, const MatchPart* parts, int n_parts, const stm_params* params, int n_tau,
+                  const MatchScratch& sc, bool timed) {
+  const hipStream_t st = parts[0].pr.st;
   int rc;
-  STM_HIP(stm::launch_model_angles(pr.m, sc.theta, st));
-  if ((rc = unary_table(ctx, pr, sc.U, &sc.bf))) return rc;
+  for (int q = 0; q < n_parts; ++q) {
+    STM_HIP(stm::launch_model_angles(parts[q].pr.m, parts[q].theta, st));
+    if ((rc = unary_table(ctx, parts[q].pr, parts[q].U, &sc.bf))) return rc;
+  }
   for (int c0 = 0; c0 < n_tau; c0 += sc.chunk) {
     const int nc = std::min(sc.chunk, n_tau - c0);
-    stm::DPLaunch a;
-    a.m = pr.m;
-    a.s = pr.s;
-    a.sp = pr.sp;
-    a.U = sc.U;
-    a.theta = sc.theta;
-    a.lambda1 = static_cast<float>(params->lambda1);
-    a.lambda2 = static_cast<float>(params->lambda2);
-    a.w = static_cast<float>(params->lambda2 * params->lambda3);
-    a.dummy = dummy_on(params) ? 1 : 0;
-    a.cw = dummy_cost32(params);
-    a.packed = !a.dummy && sparse_scene(pr.s.S, pr.s.F) ? 1 : 0;
-    a.tau0 = tau_begin + c0;
-    a.n_tau = nc;
-    a.vt = sc.vt;
-    a.e32 = d_e32 + c0;
-    a.last2 = sc.last2;
-    a.degen = sc.degen;
-    a.waves = ctx->dp_waves;
+    stm::DPLaunch a[stm::kDPParts];
+    float* vt = sc.vt;
+    for (int q = 0; q < n_parts; ++q) {
+      const Prepared& pr = parts[q].pr;
+      a[q].m = pr.m;
+      a[q].s = pr.s;
+      a[q].sp = pr.sp;
+      a[q].U = parts[q].U;
+      a[q].theta = parts[q].theta;
+      a[q].lambda1 = static_cast<float>(params->lambda1);
+      a[q].lambda2 = static_cast<float>(params->lambda2);
+      a[q].w = static_cast<float>(params->lambda2 * params->lambda3);
+      a[q].dummy = dummy_on(params) ? 1 : 0;
+      a[q].cw = dummy_cost32(params);
+      a[q].packed = !a[q].dummy && sparse_scene(pr.s.S, pr.s.F) ? 1 : 0;
+      a[q].tau0 = parts[q].tau_begin + c0;
+      a[q].n_tau = nc;
+      a[q].vt = vt;
+      vt += vt_bytes_per_offset(pr.m.M, params) / sizeof(float) * sc.chunk;
+      a[q].e32 = parts[q].e32 + c0;
+      a[q].last2 = sc.last2 + (size_t)q * sc.chunk;
+      a[q].degen = sc.degen + (size_t)q * sc.chunk;
+      a[q].assign = parts[q].assign + (size_t)c0 * pr.m.M;
+      a[q].waves = ctx->dp_waves;
+    }
     if (timed && ctx->prof) {
       if (ctx->prof_used + 2 > ctx->prof_ev.size()) {
         for (int q = 0; q < 2; ++q) {
@@ -246,18 +253,22 @@ int match_kernels(stm_ctx* ctx, const Prepared& pr, const stm_params* params, in
         }
       }
       STM_HIP(hipEventRecord(ctx->prof_ev[ctx->prof_used], st));
-      STM_HIP(stm::launch_dp_fast(a, st));
+      STM_HIP(stm::launch_dp_fast(a, n_parts, st));
       STM_HIP(hipEventRecord(ctx->prof_ev[ctx->prof_used + 1], st));
       ctx->prof_used += 2;
-      ctx->prof_matchings += nc;
+      ctx->prof_matchings += (int64_t)nc * n_parts;
     } else {
-      STM_HIP(stm::launch_dp_fast(a, st));
+      STM_HIP(stm::launch_dp_fast(a, n_parts, st));
     }
-    STM_HIP(stm::launch_dp_degenerate(a, st));
-    STM_HIP(stm::launch_backtrack(a, d_as + (size_t)c0 * M, st));
-    STM_HIP(stm::launch_rescore(pr.m, pr.s, pr.sp, params->lambda1, params->lambda2,
-                                params->lambda3, w_dummy_of(params), d_as + (size_t)c0 * M, nc,
-                                d_e64 ? d_e64 + c0 : nullptr, d_eu ? d_eu + c0 : nullptr, st));
+    STM_HIP(stm::launch_dp_degenerate(a, n_parts, st));
+    STM_HIP(stm::launch_backtrack(a, n_parts, st));
+    for (int q = 0; q < n_parts; ++q) {
+      const Prepared& pr = parts[q].pr;
+      STM_HIP(stm::launch_rescore(pr.m, pr.s, pr.sp, params->lambda1, params->lambda2, params->lambda3,
+                                  w_dummy_of(params), a[q].assign, nc,
+                                  parts[q].e64 ? parts[q].e64 + c0 : nullptr,
+                                  parts[q].eu ? parts[q].eu + c0 : nullptr, st));
+    }
   }
   return STM_OK;
 }
@@ -368,12 +379,19 @@ int stm_match(stm_ctx* ctx, const stm_points* model, const stm_points* scene,
   if ((rc = grow(ctx, ctx->vt, per_tau * sc.chunk, st))) return rc;
   if ((rc = grow(ctx, ctx->last2, (size_t)sc.chunk * sizeof(int2), st))) return rc;
   if ((rc = grow(ctx, ctx->degen, (size_t)sc.chunk * sizeof(int32_t), st))) return rc;
-  sc.theta = static_cast<float2*>(ctx->theta.p);
-  sc.U = static_cast<float*>(ctx->U.p);
+  MatchPart part;
+  part.theta = static_cast<float2*>(ctx->theta.p);
+  part.U = static_cast<float*>(ctx->U.p);
   sc.vt = static_cast<float*>(ctx->vt.p);
   sc.last2 = static_cast<int2*>(ctx->last2.p);
   sc.degen = static_cast<int32_t*>(ctx->degen.p);
-  if ((rc = match_kernels(ctx, pr, params, tau_begin, n_tau, d_e32, d_e64, d_eu, d_as, sc, true))) return rc;
+  part.pr = pr;
+  part.tau_begin = tau_begin;
+  part.e32 = d_e32;
+  part.e64 = d_e64;
+  part.eu = d_eu;
+  part.assign = d_as;
+  if ((rc = match_kernels(ctx, &part, 1, params, n_tau, sc, true))) return rc;
 
   if (!pr.device) {
     STM_HIP(hipMemcpyAsync(energy32, d_e32, (size_t)n_tau * sizeof(float), hipMemcpyDeviceToHost, st));

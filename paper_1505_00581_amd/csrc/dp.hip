@@ -1134,7 +1134,14 @@ __device__ __forceinline__ void backtrack_wave(const MatchView& a, const float* 
   }
 }
 
-// ---- per-offset kernels: one workgroup per offset of one (model, scene) pair ------
+// ---- per-offset kernels: one workgroup per offset of a (model, scene) pair ------
+__device__ __forceinline__ int part_of(const DPParts& b, int wg) {
+  int q = 0;
+#pragma unroll
+  for (int x = 1; x < kDPParts; ++x) q += x < b.n && wg >= b.first[x];
+  return q;
+}
+
 __device__ __forceinline__ MatchView view_of(const DPLaunch& a, int tl) {
   MatchView v;
   v.m = a.m;
@@ -1163,9 +1170,10 @@ __device__ __forceinline__ float* scratch_of(const DPLaunch& a, int tl) {
 template <int NW, bool DEGEN, int KL, bool DUMMY = false, bool PACKED = false, bool UNS = false, bool LISTS = false>
 __global__ __launch_bounds__(NW * 64)
 __attribute__((amdgpu_waves_per_eu(KL < kMaxList || NW == 8 ? 4 : 1)))
-void k_dp(DPLaunch a) {
+void k_dp(DPParts parts) {
   __shared__ DPShared<NW, KL, DUMMY, PACKED> sh;
-  const int tl = blockIdx.x;
+  const int part = part_of(parts, blockIdx.x), tl = blockIdx.x - parts.first[part];
+  const DPLaunch& a = parts.p[part];
   if (DEGEN && a.degen[tl] == 0) return;
   const DPResult r = dp_forward<NW, DEGEN, KL, DUMMY, PACKED, UNS, LISTS>(sh, view_of(a, tl), scratch_of(a, tl));
   if (threadIdx.x == 0) {
@@ -1176,10 +1184,11 @@ void k_dp(DPLaunch a) {
   }
 }
 
-__global__ __launch_bounds__(64) void k_backtrack(DPLaunch a, int32_t* __restrict__ assign) {
-  const int tl = blockIdx.x, lane = threadIdx.x;
+__global__ __launch_bounds__(64) void k_backtrack(DPParts parts) {
+  const int part = part_of(parts, blockIdx.x), tl = blockIdx.x - parts.first[part], lane = threadIdx.x;
+  const DPLaunch& a = parts.p[part];
   const int M = a.m.M;
-  int32_t* out = assign + (long long)tl * M;
+  int32_t* out = a.assign + (long long)tl * M;
   if (!(a.e32[tl] < __builtin_inff())) {
     for (int i = lane; i < M; i += 64) out[i] = -1;
     return;
@@ -1481,60 +1490,76 @@ __global__ __launch_bounds__(W * 64) void k_rescore_batch(const PairDev* __restr
 // arithmetic of every cell is the same, so the results do not depend on the
 // variant.
 constexpr int kCUs = 256;
+
+DPParts dp_parts(const DPLaunch* a, int n_parts, int& n) {
+  DPParts b;
+  b.n = n_parts;
+  n = 0;
+  for (int q = 0; q < kDPParts; ++q) {
+    b.p[q] = a[q < n_parts ? q : 0];
+    b.first[q] = n;
+    if (q < n_parts) n += a[q].n_tau;
+  }
+  return b;
+}
+
 template <bool DEGEN>
-hipError_t launch_dp_waves(const DPLaunch& a, hipStream_t st) {
-  if (a.n_tau <= 0) return hipSuccess;
+hipError_t launch_dp_waves(const DPLaunch* parts, int n_parts, hipStream_t st) {
+  int n = 0;
+  const DPParts b = dp_parts(parts, n_parts, n);
+  if (n <= 0) return hipSuccess;
+  const DPLaunch& a = parts[0];
   if (a.dummy) {  // dummies: one variant, 8 waves and the 64-slot layout
-    hipLaunchKernelGGL((k_dp<8, DEGEN, 64, true>), dim3(a.n_tau), dim3(8 * 64), 0, st, a);
+    hipLaunchKernelGGL((k_dp<8, DEGEN, 64, true>), dim3(n), dim3(8 * 64), 0, st, b);
     return hipGetLastError();
   }
   if (a.sp.uns) {  // unsigned angles: one variant, 8 waves, the 64-slot layout and dense schedules
-    hipLaunchKernelGGL((k_dp<8, DEGEN, 64, false, false, true>), dim3(a.n_tau), dim3(8 * 64), 0, st, a);
+    hipLaunchKernelGGL((k_dp<8, DEGEN, 64, false, false, true>), dim3(n), dim3(8 * 64), 0, st, b);
     return hipGetLastError();
   }
   if (a.packed && a.sp.K > 32) {  // sparse scenes, long lists: packed schedules
     if (a.cand)
-      hipLaunchKernelGGL((k_dp<8, DEGEN, 64, false, true, false, true>), dim3(a.n_tau), dim3(8 * 64), 0, st, a);
+      hipLaunchKernelGGL((k_dp<8, DEGEN, 64, false, true, false, true>), dim3(n), dim3(8 * 64), 0, st, b);
     else
-      hipLaunchKernelGGL((k_dp<8, DEGEN, 64, false, true>), dim3(a.n_tau), dim3(8 * 64), 0, st, a);
+      hipLaunchKernelGGL((k_dp<8, DEGEN, 64, false, true>), dim3(n), dim3(8 * 64), 0, st, b);
     return hipGetLastError();
   }
   if (a.sp.K <= 16) {
-    if (a.n_tau <= 4 * kCUs)
-      hipLaunchKernelGGL((k_dp<4, DEGEN, 16>), dim3(a.n_tau), dim3(4 * 64), 0, st, a);
-    else if (a.n_tau <= 8 * kCUs)
-      hipLaunchKernelGGL((k_dp<2, DEGEN, 16>), dim3(a.n_tau), dim3(2 * 64), 0, st, a);
+    if (n <= 4 * kCUs)
+      hipLaunchKernelGGL((k_dp<4, DEGEN, 16>), dim3(n), dim3(4 * 64), 0, st, b);
+    else if (n <= 8 * kCUs)
+      hipLaunchKernelGGL((k_dp<2, DEGEN, 16>), dim3(n), dim3(2 * 64), 0, st, b);
     else
-      hipLaunchKernelGGL((k_dp<1, DEGEN, 16>), dim3(a.n_tau), dim3(64), 0, st, a);
+      hipLaunchKernelGGL((k_dp<1, DEGEN, 16>), dim3(n), dim3(64), 0, st, b);
     return hipGetLastError();
   }
   if (a.sp.K <= 32) {
-    if (a.n_tau <= 2 * kCUs)
-      hipLaunchKernelGGL((k_dp<8, DEGEN, 32>), dim3(a.n_tau), dim3(8 * 64), 0, st, a);
-    else if (a.n_tau <= 4 * kCUs)
-      hipLaunchKernelGGL((k_dp<4, DEGEN, 32>), dim3(a.n_tau), dim3(4 * 64), 0, st, a);
+    if (n <= 2 * kCUs)
+      hipLaunchKernelGGL((k_dp<8, DEGEN, 32>), dim3(n), dim3(8 * 64), 0, st, b);
+    else if (n <= 4 * kCUs)
+      hipLaunchKernelGGL((k_dp<4, DEGEN, 32>), dim3(n), dim3(4 * 64), 0, st, b);
     else
-      hipLaunchKernelGGL((k_dp<2, DEGEN, 32>), dim3(a.n_tau), dim3(2 * 64), 0, st, a);
+      hipLaunchKernelGGL((k_dp<2, DEGEN, 32>), dim3(n), dim3(2 * 64), 0, st, b);
     return hipGetLastError();
   }
-  switch (a.waves ? a.waves : a.n_tau <= kCUs ? 16 : 8) {
+  switch (a.waves ? a.waves : n <= kCUs ? 16 : 8) {
     case 4:
-      hipLaunchKernelGGL((k_dp<4, DEGEN, 64>), dim3(a.n_tau), dim3(4 * 64), 0, st, a);
+      hipLaunchKernelGGL((k_dp<4, DEGEN, 64>), dim3(n), dim3(4 * 64), 0, st, b);
       break;
     case 16:
-      hipLaunchKernelGGL((k_dp<16, DEGEN, 64>), dim3(a.n_tau), dim3(16 * 64), 0, st, a);
+      hipLaunchKernelGGL((k_dp<16, DEGEN, 64>), dim3(n), dim3(16 * 64), 0, st, b);
       break;
     default:
-      hipLaunchKernelGGL((k_dp<8, DEGEN, 64>), dim3(a.n_tau), dim3(8 * 64), 0, st, a);
+      hipLaunchKernelGGL((k_dp<8, DEGEN, 64>), dim3(n), dim3(8 * 64), 0, st, b);
   }
   return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_dp_fast(const DPLaunch& a, hipStream_t st) { return launch_dp_waves<false>(a, st); }
+hipError_t launch_dp_fast(const DPLaunch* a, int n, hipStream_t st) { return launch_dp_waves<false>(a, n, st); }
 
-hipError_t launch_dp_degenerate(const DPLaunch& a, hipStream_t st) { return launch_dp_waves<true>(a, st); }
+hipError_t launch_dp_degenerate(const DPLaunch* a, int n, hipStream_t st) { return launch_dp_waves<true>(a, n, st); }
 
 template <bool DEGEN>
 hipError_t launch_persistent_variant(const BatchLaunch& b, int n_wg, hipStream_t st) {
@@ -1605,9 +1630,11 @@ hipError_t launch_rescore_batch(const PairDev* pairs, const int2* items, int n_i
   return hipGetLastError();
 }
 
-hipError_t launch_backtrack(const DPLaunch& a, int32_t* assign, hipStream_t st) {
-  if (a.n_tau <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_backtrack, dim3(a.n_tau), dim3(64), 0, st, a, assign);
+hipError_t launch_backtrack(const DPLaunch* a, int n_parts, hipStream_t st) {
+  int n = 0;
+  const DPParts b = dp_parts(a, n_parts, n);
+  if (n <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_backtrack, dim3(n), dim3(64), 0, st, b);
   return hipGetLastError();
 }
 

@@ -127,13 +127,22 @@ inline int bf16_rows_scene(int S) { return (S + 255) / 256 * 256; }
 int unary_table(stm_ctx* ctx, const Prepared& pr, float* U, const Bf16Bufs* fixed = nullptr);
 int check_range(const Prepared& pr, int32_t tau_begin, int32_t tau_end);
 
-// Device scratch of one exact matching call: the model angles [M], the unary
-// table [M][S], the BF16 buffers (split precision), and for `chunk` offsets
-// at a time the value tables (per offset (M - 2) x side^2 floats), the last
-// state pairs and the degenerate flags.
-struct MatchScratch {
+// One model of an exact matching call: its prepared inputs, first offset, the
+// scratch of its angles [M] and unary table [M][S], and its device outputs.
+struct MatchPart {
+  Prepared pr;
+  int32_t tau_begin = 0;
   float2* theta = nullptr;
   float* U = nullptr;
+  float* e32 = nullptr;
+  double *e64 = nullptr, *eu = nullptr;
+  int32_t* assign = nullptr;
+};
+
+// Device scratch of the call: the BF16 buffers (split precision) and, for
+// `chunk` offsets of every model at a time, the value tables (per offset and
+// model (M - 2) x side^2 floats), the last state pairs and the degenerate flags.
+struct MatchScratch {
   Bf16Bufs bf;
   float* vt = nullptr;
   int2* last2 = nullptr;
@@ -141,13 +150,13 @@ struct MatchScratch {
   int chunk = 0;
 };
 
-// The kernels of stm_match over offsets [tau_begin, tau_begin + n_tau) on
-// prepared inputs and device outputs: model angles, unary table, then per
-// chunk of offsets the recursion (fast and degenerate variants),
-// backtracking and the FP64 re-score.  `timed`: HIP events around the fast
-// recursion launches when the context's profiling is on.
-int match_kernels(stm_ctx* ctx, const Prepared& pr, const stm_params* p, int32_t tau_begin, int n_tau,
-                  float* e32, double* e64, double* eu, int32_t* assign, const MatchScratch& sc, bool timed);
+// The kernels of stm_match over n_tau offsets of every model (at most
+// stm::kDPParts, one scene) on prepared inputs and device outputs: model angles,
+// unary tables, then per chunk of offsets the recursion (fast and degenerate
+// variants), backtracking and the FP64 re-score.  `timed`: HIP events around
+// the fast recursion launches when the context's profiling is on.
+int match_kernels(stm_ctx* ctx, const MatchPart* parts, int n_parts, const stm_params* p, int n_tau,
+                  const MatchScratch& sc, bool timed);
 
 
 // Looks up the device address of stm_match_noalloc's fixed array on the

@@ -104,8 +104,9 @@ extern "C" int stm_match_noalloc(stm_ctx* ctx, const stm_points* model, const st
   fp.val = cv.take<int32_t>(2);
   fp.fstart = cv.take<int32_t>((size_t)F + 1);
   MatchScratch sc;
-  sc.theta = cv.take<float2>(M);
-  sc.U = cv.take<float>((size_t)M * S);
+  MatchPart part;
+  part.theta = cv.take<float2>(M);
+  part.U = cv.take<float>((size_t)M * S);
   if (bf16) {
     const int Mp = bf16_rows_model(M), Sp = bf16_rows_scene(S), dp = stm::bf16_padded_dim(dim);
     sc.bf.fb = cv.take<uint16_t>((size_t)Mp * dp);
@@ -135,5 +136,11 @@ extern "C" int stm_match_noalloc(stm_ctx* ctx, const stm_points* model, const st
   sc.degen = cv.take<int32_t>(sc.chunk);
   sc.vt = cv.take<float>(vt_bytes_per_offset(M, params) / sizeof(float) * sc.chunk);
   if (cv.used > limit) return fail(STM_EINVAL, "scratch layout exceeds the fixed array");
-  return match_kernels(ctx, pr, params, tau_begin, n_tau, energy32, energy64, energy_u64, assign, sc, false);
+  part.pr = pr;
+  part.tau_begin = tau_begin;
+  part.e32 = energy32;
+  part.e64 = energy64;
+  part.eu = energy_u64;
+  part.assign = assign;
+  return match_kernels(ctx, &part, 1, params, n_tau, sc, false);
 }

@@ -297,9 +297,10 @@ int dp_scratch(stm_ctx* ctx, const Prepared& pr, const stm_params* params, int c
 int dp_rows(const Prepared& pr, const stm_params* params, stm::DPLaunch b, float* e32, double* e64, double* eu,
             int32_t* as) {
   b.e32 = e32;
-  STM_HIP(stm::launch_dp_fast(b, pr.st));
-  STM_HIP(stm::launch_dp_degenerate(b, pr.st));
-  STM_HIP(stm::launch_backtrack(b, as, pr.st));
+  b.assign = as;
+  STM_HIP(stm::launch_dp_fast(&b, 1, pr.st));
+  STM_HIP(stm::launch_dp_degenerate(&b, 1, pr.st));
+  STM_HIP(stm::launch_backtrack(&b, 1, pr.st));
   STM_HIP(stm::launch_rescore(pr.m, pr.s, pr.sp, params->lambda1, params->lambda2, params->lambda3,
                               w_dummy_of(params), as, b.n_tau,
                               e64, eu, pr.st));

@@ -222,6 +222,7 @@ struct DPLaunch {
   float* e32;           // [n_tau]
   int2* last2;          // [n_tau]
   int32_t* degen;       // [n_tau], written by the fast variant
+  int32_t* assign = nullptr;  // [n_tau][M], written by backtracking
   int32_t waves;        // waves per workgroup of the recursion: 4, 8, 16 or 0 (by the number of matchings)
   // explicit candidate lists (null: the windowed rule): offset tl, point j has
   // the nodes cand[(tl * M + j) * cstride + a], a < ccount[tl * M + j], ascending
@@ -237,12 +238,22 @@ struct DPLaunch {
   // step on its own lane, chunk after chunk
   int32_t packed = 0;
 };
-// The fast variant over every matching of the launch, then the variant for
-// degenerate triangles, which only recomputes the matchings flagged by the first.
-hipError_t launch_dp_fast(const DPLaunch& a, hipStream_t st);
-hipError_t launch_dp_degenerate(const DPLaunch& a, hipStream_t st);
+// Several models' matchings in one launch, part after part (same scene,
+// parameters and variant): the last workgroups of one part leave no CU idle
+// while another part has matchings left.
+constexpr int kDPParts = 4;
+struct DPParts {
+  DPLaunch p[kDPParts];
+  int32_t first[kDPParts];  // first workgroup of every part
+  int32_t n;                // parts
+};
+// n <= kDPParts parts.  The fast variant over every matching of the launch, then
+// the variant for degenerate triangles, which only recomputes the matchings
+// flagged by the first; then the backtracking into every part's assign.
+hipError_t launch_dp_fast(const DPLaunch* a, int n, hipStream_t st);
+hipError_t launch_dp_degenerate(const DPLaunch* a, int n, hipStream_t st);
+hipError_t launch_backtrack(const DPLaunch* a, int n, hipStream_t st);
 
-hipError_t launch_backtrack(const DPLaunch& a, int32_t* assign, hipStream_t st);
 
 // FP64 energy of each assignment row; w_dummy is W^d, the unary cost of a
 // dummy (node id -2 in assign; never present when dummies are off).
