@@ -131,6 +131,10 @@ __device__ __forceinline__ int count_lt(const int32_t* a, int n, int x) {
   return pos;
 }
 
+__device__ __forceinline__ float lane_value(float x, int l) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), l));
+}
+
 // Cell of lane `lane` in chunk c: row r and column a; false past the last cell.
 __device__ __forceinline__ bool chunk_cell(const Chunk& c, int lane, int& r, int& a) {
   const int e = c.e0 + lane;
@@ -373,7 +377,7 @@ struct DPResult {
 // value tables of steps 1..M-2 to vtm and returns the optimum to every thread.
 template <int NW, bool DEGEN, int KL, bool DUMMY = false, bool PACKED = false, bool UNS = false, bool LISTS = false>
 __device__ __forceinline__ DPResult dp_forward(DPShared<NW, KL, DUMMY, PACKED>& sh, const MatchView& a, float* vtm) {
-  static_assert(KL == 16 || KL == 32 || KL == 64, "list capacity");
+  static_assert(KL == 16 || KL == 64, "list capacity");
   static_assert(!DUMMY || KL == kMaxList, "dummies use the 64-slot layout");
   static_assert(!PACKED || (KL == kMaxList && !DUMMY), "packed schedules: 64-slot layout, no dummies");
   static_assert(!LISTS || PACKED, "list variant: packed schedules");
@@ -1019,6 +1023,228 @@ __device__ __forceinline__ DPResult dp_forward(DPShared<NW, KL, DUMMY, PACKED>& 
   return res;
 }
 
+// ---- forward pass of short lists ---------------------------------------------------
+// The same recursion for short lists (KL = 16 or 32, plain reading), where the
+// chain of steps of one matching bounds the launch: one barrier a step instead
+// of two.  NW waves work on step i, writing its cells to
+// a second buffer, then build the (a_{i-1}, a_{i+1}) directions of step i + 1;
+// one more wave builds the schedule of step i + 1 and brings in list i + 2
+// meanwhile (at step i the ring of four holds lists i - 1 .. i + 1 in use).  Every
+// term, minimum and sum is the one dp_forward takes.  The second buffers cost 64-slot
+// lists a workgroup per CU, so those stay with dp_forward.  20 points, lists of
+// 16, 40 matchings: 53 us, 79 with four waves and two barriers, 146 with one
+// wave.
+template <int NW, int KL>
+struct FewShared {
+  float2 va[2][KL * KL];  // V_i and directions of step i's cells, by parity of i
+  float ct[2][KL * KL];
+  float2 cxy[4][KL];
+  int32_t ctt[4][KL];
+  float cu[4][KL];
+  uint2 sched[2][KL];
+  int32_t nch[2];
+  int32_t ck[4];
+  CandRange crange[4];
+  int32_t flag;
+  float red_v[NW];
+  int32_t red_i[NW];
+};
+
+template <int NW, bool DEGEN, int KL>
+__device__ __forceinline__ DPResult dp_forward_few(FewShared<NW, KL>& sh, const MatchView& a, float* vtm) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const bool producer = wv == NW;
+  const int M = a.m.M, VS = a.vs;
+  const int T = pair_limit(a.sp), TS = span_limit(a.sp);
+  const float INF = __builtin_inff();
+  const CandRange* ring = a.sp.node ? sh.crange : nullptr;
+
+  struct List {
+    Cands c;
+    int32_t node;
+  };
+  struct Values {
+    Cands c;
+    float2 xy;
+    int32_t t;
+    float u;
+  };
+  auto fetch_list = [&](int j) {
+    List l;
+    l.c = cands_of(a, j);
+    l.node = l.c.list ? ro(l.c.list + (lane < a.cstride ? lane : 0)) : 0;
+    return l;
+  };
+  auto fetch_values = [&](int j, const List& l) {
+    Values f;
+    f.c = l.c;
+    if (lane < l.c.count()) {
+      const int n = l.c.list ? l.node : cand_node(l.c.r, lane);
+      f.xy = ro(a.s.xy + n);
+      f.t = ro(a.s.t + n);
+      f.u = ro(a.U + (long long)j * a.us + n);
+    }
+    return f;
+  };
+  auto commit = [&](int j, const Values& f) {
+    const int k = f.c.count(), sl = j & 3;
+    if (lane < k) {
+      sh.cxy[sl][lane] = f.xy;
+      sh.ctt[sl][lane] = f.t;
+      sh.cu[sl][lane] = a.lambda1 * f.u;
+    }
+    if (lane == 0) {
+      sh.ck[sl] = k;
+      sh.crange[sl] = f.c.r;
+    }
+  };
+  // the schedule of step i: rows list i - 1, columns list i, predecessors i - 2
+  auto schedule = [&](int i) {
+    const int sr = (i - 1) & 3, sc = i & 3, sp = i >= 2 ? (i - 2) & 3 : -1;
+    build_schedule(sh.ctt[sr], sh.ck[sr], sh.ctt[sc], sh.ck[sc], sp >= 0 ? sh.ctt[sp] : nullptr,
+                   sp >= 0 ? sh.ck[sp] : 0, T, sh.sched[i & 1], &sh.nch[i & 1], lane, nullptr, nullptr, ring, sr, sc,
+                   sp);
+  };
+  // the (a_{i-2}, a_i) directions of step i, by the working waves
+  auto directions = [&](int i) {
+    const int s2 = (i - 2) & 3, s0 = i & 3, Kq = sh.ck[s2], Kn = sh.ck[s0];
+    const int gap_min = a.sp.node ? 0 : 2;
+    const int c = threadIdx.x & (KL - 1);
+    if (c >= Kn) return;
+    const int tc = sh.ctt[s0][c];
+    const float2 pc = sh.cxy[s0][c];
+    for (int k = threadIdx.x / KL; k < Kq; k += NW * 64 / KL) {
+      const int gap = tc - sh.ctt[s2][k];
+      if (gap >= gap_min && (T <= 0 || gap <= 2 * T - 2)) {
+        if (TS > 0 && gap >= TS) {
+          sh.ct[i & 1][k * KL + c] = INF;
+          continue;
+        }
+        const float2 pk = sh.cxy[s2][k];
+        if (!DEGEN && pk.x == pc.x && pk.y == pc.y) sh.flag = 1;
+        sh.ct[i & 1][k * KL + c] = neg_dir<DEGEN>(pk, pc);
+      }
+    }
+  };
+  // angles and frames of 64 model points at a time, one per lane
+  float2 th_l = make_float2(0.f, 0.f);
+  int32_t tm_l = 0, tm_prev = 0;
+  auto load_points = [&](int i0) {
+    const int j = min(i0 + lane, M - 1);
+    th_l = a.theta[j];
+    tm_l = a.m.t[j];
+  };
+
+  List next_list;
+  Values next;
+  if (producer) {
+    const List l0 = fetch_list(0), l1 = fetch_list(1), l2 = fetch_list(2);
+    if (3 < M) next_list = fetch_list(3);
+    const Values f0 = fetch_values(0, l0), f1 = fetch_values(1, l1), f2 = fetch_values(2, l2);
+    if (3 < M) next = fetch_values(3, next_list);
+    if (4 < M) next_list = fetch_list(4);
+    if (lane == 0) sh.flag = 0;
+    commit(0, f0);
+    commit(1, f1);
+    commit(2, f2);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    schedule(1);
+  } else {
+    load_points(0);
+    tm_prev = __builtin_amdgcn_readlane(tm_l, 0);
+  }
+  __syncthreads();
+
+  float bv = INF;  // first row-major minimum of the last step's cells
+  int bi = 0x7fffffff;
+  for (int i = 1; i < M; ++i) {
+    if (producer) {
+      if (i + 2 < M) commit(i + 2, next);
+      if (i + 3 < M) next = fetch_values(i + 3, next_list);
+      if (i + 4 < M) next_list = fetch_list(i + 4);
+      if (i + 1 < M) schedule(i + 1);
+    } else {
+      const int s1 = (i - 1) & 3, s0 = i & 3, b = i & 1;
+      if ((i & 63) == 0) load_points(i);
+      const float2 th = make_float2(lane_value(th_l.x, i & 63), lane_value(th_l.y, i & 63));
+      const int tm = __builtin_amdgcn_readlane(tm_l, i & 63);
+      const int dtm = tm - tm_prev;
+      tm_prev = tm;
+      const float qw = a.lambda2 * (i >= 2 && i <= M - 2 ? 2.f : 1.f);
+      float* vt = i <= M - 2 ? vtable(vtm, a, i) : nullptr;
+      const int nch = sh.nch[b];
+      for (int ch = wv; ch < nch; ch += NW) {
+        const Chunk c = unpack_chunk(sh.sched[b][ch]);
+        int r, col;
+        const bool valid = chunk_cell(c, lane, r, col);
+        if (!valid) { r = c.r0; col = c.clo; }  // in-range reads; results unused
+        const int tr = sh.ctt[s1][r], tp = sh.ctt[s0][col];
+        const float2 xr = sh.cxy[s1][r], xa = sh.cxy[s0][col];
+        const bool same = xa.x == xr.x && xa.y == xr.y;
+        if (!DEGEN && same && valid) sh.flag = 1;
+        const float anew = neg_dir<DEGEN>(xr, xa);
+        const float q = qw * fabsf(static_cast<float>(dtm - (tp - tr)));
+        float v;
+        if (i == 1) {
+          v = (sh.cu[s1][r] + sh.cu[s0][col]) + q;
+        } else {
+          float bm, be;
+          cell_consts<false>(th, anew, bm, be);
+          const float2* vcol = sh.va[b ^ 1] + r;
+          const float* ccol = sh.ct[b] + col;
+          const float w = a.w;
+          float best = INF;
+          int k = c.lo;
+          for (; k + 3 < c.hi; k += 4) {
+            const float2 v0 = vcol[k * KL], v1 = vcol[(k + 1) * KL];
+            const float2 v2 = vcol[(k + 2) * KL], v3 = vcol[(k + 3) * KL];
+            const float t0 = relax<DEGEN>(v0.x, v0.y, ccol[k * KL], bm, be, th, same, w);
+            const float t1 = relax<DEGEN>(v1.x, v1.y, ccol[(k + 1) * KL], bm, be, th, same, w);
+            const float t2 = relax<DEGEN>(v2.x, v2.y, ccol[(k + 2) * KL], bm, be, th, same, w);
+            const float t3 = relax<DEGEN>(v3.x, v3.y, ccol[(k + 3) * KL], bm, be, th, same, w);
+            best = fminf(fminf(best, fminf(fminf(t0, t1), t2)), t3);
+          }
+          for (; k < c.hi; ++k) {
+            const float2 v0 = vcol[k * KL];
+            best = fminf(best, relax<DEGEN>(v0.x, v0.y, ccol[k * KL], bm, be, th, same, w));
+          }
+          v = (sh.cu[s0][col] + q) + best;
+        }
+        if (valid) {
+          sh.va[b][r * KL + col] = make_float2(v, anew);
+          if (vt) vt[r * VS + col] = v;
+          const int idx = r * KL + col;
+          if (i == M - 1 && (v < bv || (v == bv && idx < bi))) { bv = v; bi = idx; }
+        }
+      }
+      if (i + 1 < M) directions(i + 1);
+    }
+    __syncthreads();
+  }
+
+  for (int off = 32; off > 0; off >>= 1) {
+    const float ov = __shfl_xor(bv, off);
+    const int oi = __shfl_xor(bi, off);
+    if (ov < bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
+  }
+  if (!producer && lane == 0) { sh.red_v[wv] = bv; sh.red_i[wv] = bi; }
+  __syncthreads();
+  bv = INF;
+  bi = 0x7fffffff;
+  for (int q = 0; q < NW; ++q) {
+    const float ov = sh.red_v[q];
+    const int oi = sh.red_i[q];
+    if (ov < bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
+  }
+  DPResult res;
+  res.v = bv;
+  res.idx = bi == 0x7fffffff ? 0 : bi;
+  res.flag = DEGEN ? 0 : sh.flag;
+  return res;
+}
+
 // ---- backtracking (Eq. 12), one wave per matching ---------------------------------
 // From the optimal final pair (r, c) = (a_{M-2}, a_{M-1}), each step recomputes
 // the terms of the optimal cell over its admissible predecessors (lanes) with
@@ -1059,10 +1285,6 @@ __device__ __forceinline__ LaneCand lane_cand(const MatchView& a, const LaneList
   L.t = L.node >= 0 ? ro(a.s.t + L.node) : 0;
   L.xy = L.node >= 0 ? ro(a.s.xy + L.node) : make_float2(0.f, 0.f);
   return L;
-}
-
-__device__ __forceinline__ float lane_value(float x, int l) {
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), l));
 }
 
 template <bool DEGEN, bool DUMMY = false, bool UNS = false, bool LISTS = false>
@@ -1180,6 +1402,20 @@ void k_dp(DPParts parts) {
     constexpr int RS = KL + (DUMMY ? 1 : 0);
     a.e32[tl] = r.v;
     a.last2[tl] = make_int2(r.idx / RS, r.idx % RS);
+    if (!DEGEN) a.degen[tl] = r.flag;
+  }
+}
+
+template <int NW, bool DEGEN, int KL>
+__global__ __launch_bounds__((NW + 1) * 64) void k_dp_few(DPParts parts) {
+  __shared__ FewShared<NW, KL> sh;
+  const int part = part_of(parts, blockIdx.x), tl = blockIdx.x - parts.first[part];
+  const DPLaunch& a = parts.p[part];
+  if (DEGEN && a.degen[tl] == 0) return;
+  const DPResult r = dp_forward_few<NW, DEGEN, KL>(sh, view_of(a, tl), scratch_of(a, tl));
+  if (threadIdx.x == 0) {
+    a.e32[tl] = r.v;
+    a.last2[tl] = make_int2(r.idx / KL, r.idx % KL);
     if (!DEGEN) a.degen[tl] = r.flag;
   }
 }
@@ -1478,16 +1714,27 @@ __global__ __launch_bounds__(W * 64) void k_rescore_batch(const PairDev* __restr
           pd.row0 + it.y, e64, eu64);
 }
 
-// Lists of at most 16 or 32 candidates take a smaller LDS layout and fewer
-// waves per matching (more matchings resident per CU); longer lists take the
-// 64-slot layout with the requested number of waves.  Where the matchings of a
-// launch leave CUs idle, the steps of one bound the call, so more waves share
-// them.  Whole calls of 30 points, lists of 12 to 18, one, two and four waves:
-// 370, 290, 253 us up to 512 matchings; 398, 319, 283 at 1024; 461, 370, 414 at
-// 2048; 537, 570, 591 at 4096.  Lists of 20 to 32, two, four and eight waves:
-// 595, 408, 342 us at 512; 732, 526, 582 at 1024; 848, 844, 975 at 2048.  Lists
-// of 60, eight and sixteen waves: 681, 563 us at 256; 902, 918 at 512.  The
-// arithmetic of every cell is the same, so the results do not depend on the
+// Lists of at most 32 candidates take dp_forward_few, with fewer working waves
+// per matching the more matchings a launch has; many matchings of at most 16
+// candidates one wave each without barriers to speak of.  Longer lists take the
+// 64-slot layout with the requested number of waves, by default 8, or 16 where
+// there is at most one matching per CU.  Whole calls of 30 points in us:
+//   lists of 12 to 18       512   1024   2048   4096 matchings
+//     dp_forward, 1 wave     370    398    461    537
+//     dp_forward, 4 waves    253    283    414    591
+//     3 working waves        233    256    358    545
+//     4 working waves        224    304    452    726
+//   lists of 20 to 32       256    512   1024   4096
+//     dp_forward, 2 waves    589    595    732   1780
+//     dp_forward, 8 waves    321    342    582   1855
+//     3 working waves        352    366    480   1350
+//     7 working waves        268    297    493   1507
+//     12 working waves       247    352    583   1948
+//   lists of 60             256    512
+//     dp_forward, 8 waves    681    902
+//     dp_forward, 16 waves   563    918
+//     15 working waves       617   1007
+// The arithmetic of every cell is the same, so the results do not depend on the
 // variant.
 constexpr int kCUs = 256;
 
@@ -1524,24 +1771,27 @@ hipError_t launch_dp_waves(const DPLaunch* parts, int n_parts, hipStream_t st) {
       hipLaunchKernelGGL((k_dp<8, DEGEN, 64, false, true>), dim3(n), dim3(8 * 64), 0, st, b);
     return hipGetLastError();
   }
+#define STM_DP_FEW(NW, KL) \
+  hipLaunchKernelGGL((k_dp_few<NW, DEGEN, KL>), dim3(n), dim3((NW + 1) * 64), 0, st, b)
   if (a.sp.K <= 16) {
-    if (n <= 4 * kCUs)
-      hipLaunchKernelGGL((k_dp<4, DEGEN, 16>), dim3(n), dim3(4 * 64), 0, st, b);
+    if (n <= 2 * kCUs)
+      STM_DP_FEW(4, 16);
     else if (n <= 8 * kCUs)
-      hipLaunchKernelGGL((k_dp<2, DEGEN, 16>), dim3(n), dim3(2 * 64), 0, st, b);
+      STM_DP_FEW(3, 16);
     else
       hipLaunchKernelGGL((k_dp<1, DEGEN, 16>), dim3(n), dim3(64), 0, st, b);
     return hipGetLastError();
   }
   if (a.sp.K <= 32) {
-    if (n <= 2 * kCUs)
-      hipLaunchKernelGGL((k_dp<8, DEGEN, 32>), dim3(n), dim3(8 * 64), 0, st, b);
-    else if (n <= 4 * kCUs)
-      hipLaunchKernelGGL((k_dp<4, DEGEN, 32>), dim3(n), dim3(4 * 64), 0, st, b);
+    if (n <= kCUs)
+      STM_DP_FEW(12, 32);
+    else if (n <= 2 * kCUs)
+      STM_DP_FEW(7, 32);
     else
-      hipLaunchKernelGGL((k_dp<2, DEGEN, 32>), dim3(n), dim3(2 * 64), 0, st, b);
+      STM_DP_FEW(3, 32);
     return hipGetLastError();
   }
+#undef STM_DP_FEW
   switch (a.waves ? a.waves : n <= kCUs ? 16 : 8) {
     case 4:
       hipLaunchKernelGGL((k_dp<4, DEGEN, 64>), dim3(n), dim3(4 * 64), 0, st, b);

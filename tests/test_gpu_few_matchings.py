@@ -1,5 +1,6 @@
-"""Launches by the number of matchings: few matchings take more waves each (short,
-medium and long lists) and four waves per re-score, many take fewer and one.  A
+"""Launches by the number of matchings: few matchings take more working waves each
+(short, medium and long lists) and four waves per re-score, many take fewer and
+one.  A
 range of offsets as one call equals its halves, quarters and single offsets bit
 for bit on either side of every line, and the FP64 energies the oracle's of the
 same assignments."""
