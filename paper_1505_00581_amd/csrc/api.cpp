@@ -112,7 +112,8 @@ int stage(stm_ctx* ctx, DevBuf& b, const T* host, size_t count, hipStream_t st) 
 }
 
 int prepare(stm_ctx* ctx, const stm_points* m, const stm_points* s, const stm_params* p,
-            void* hip_stream, Prepared& out, const FixedPrep* fixed) {
+            void* hip_stream, Prepared& out, const FixedPrep* fixed,
+            const std::function<int(const Prepared&)>& early) {
   int rc = check_shapes(m, s, p);
   if (rc) return rc;
   if (!(p->flags & STM_DEVICE_PTRS)) {
@@ -138,11 +139,8 @@ int prepare(stm_ctx* ctx, const stm_points* m, const stm_points* s, const stm_pa
       STM_HIP(hipMemsetAsync(val, 0, 2 * sizeof(int32_t), out.st));
     }
     STM_HIP(stm::launch_validate(out.m, out.s, val, out.st));
-    int32_t hv[2] = {0, 0};
-    STM_HIP(hipMemcpyAsync(hv, val, sizeof(hv), hipMemcpyDeviceToHost, out.st));
-    STM_HIP(hipStreamSynchronize(out.st));
-    if (hv[0]) return fail(STM_EINVAL, bit_message(hv[0]));
-    out.span = hv[1];
+    STM_HIP(hipMemcpyAsync(ctx->val_host, val, 2 * sizeof(int32_t), hipMemcpyDeviceToHost, out.st));
+    STM_HIP(hipEventRecord(ctx->ev_val, out.st));
   } else {
     out.span = m->t[M - 1] - m->t[0];
     if ((rc = stage(ctx, ctx->mxy, m->xy, (size_t)M * 2, out.st))) return rc;
@@ -165,6 +163,22 @@ int prepare(stm_ctx* ctx, const stm_points* m, const stm_points* s, const stm_pa
   }
   STM_HIP(stm::launch_fstart(out.s.t, S, F, fst, out.st));
   out.s.fstart = fst;
+  if (out.device) {
+    // what is queued behind the validation runs while the host waits for it; it
+    // reads the inputs within their bounds whatever they hold
+    rc = early ? early(out) : STM_OK;
+    if (rc) {
+      (void)hipStreamSynchronize(out.st);
+      return rc;
+    }
+    STM_HIP(hipEventSynchronize(ctx->ev_val));
+    const int32_t bits = ctx->val_host[0];
+    if (bits) {
+      STM_HIP(hipStreamSynchronize(out.st));
+      return fail(STM_EINVAL, bit_message(bits));
+    }
+    out.span = ctx->val_host[1];
+  }
   // a window wider than the scene adds only empty frames
   out.sp = search_params(p, std::min(p->window, F));
   return STM_OK;
@@ -209,14 +223,17 @@ int check_range(const Prepared& pr, int32_t tau_begin, int32_t tau_end) {
   return STM_OK;
 }
 
+int match_tables(stm_ctx* ctx, const Prepared& pr, float2* theta, float* U, const Bf16Bufs* bf) {
+  STM_HIP(stm::launch_model_angles(pr.m, theta, pr.st));
+  return unary_table(ctx, pr, U, bf);
+}
+
 int match_kernels(stm_ctx* ctx, const MatchPart* parts, int n_parts, const stm_params* params, int n_tau,
                   const MatchScratch& sc, bool timed) {
   const hipStream_t st = parts[0].pr.st;
   int rc;
-  for (int q = 0; q < n_parts; ++q) {
-    STM_HIP(stm::launch_model_angles(parts[q].pr.m, parts[q].theta, st));
-    if ((rc = unary_table(ctx, parts[q].pr, parts[q].U, &sc.bf))) return rc;
-  }
+  for (int q = 0; q < n_parts; ++q)
+    if (!parts[q].tables && (rc = match_tables(ctx, parts[q].pr, parts[q].theta, parts[q].U, &sc.bf))) return rc;
   for (int c0 = 0; c0 < n_tau; c0 += sc.chunk) {
     const int nc = std::min(sc.chunk, n_tau - c0);
     stm::DPLaunch a[stm::kDPParts];
@@ -290,6 +307,13 @@ int stm_create(stm_ctx** out, int hip_device) {
   stm_ctx* c = new (std::nothrow) stm_ctx();
   if (!c) return fail(STM_ENOMEM, "host allocation failed");
   c->device = hip_device;
+  if (hipHostMalloc(reinterpret_cast<void**>(&c->val_host), 2 * sizeof(int32_t), hipHostMallocDefault) != hipSuccess ||
+      hipEventCreateWithFlags(&c->ev_val, hipEventDisableTiming) != hipSuccess) {
+    (void)hipGetLastError();
+    if (c->val_host) (void)hipHostFree(c->val_host);
+    delete c;
+    return fail(STM_ENOMEM, "pinned host allocation failed");
+  }
   // the fixed scratch of stm_match_noalloc on this device; a failed lookup is
   // reported by that entry point only
   (void)noalloc_init(hip_device);
@@ -309,6 +333,8 @@ void stm_destroy(stm_ctx* ctx) {
                     &ctx->ch_eu,  &ctx->ch_as};
   for (DevBuf* b : bufs) release(*b);
   for (hipEvent_t ev : ctx->prof_ev) (void)hipEventDestroy(ev);
+  if (ctx->ev_val) (void)hipEventDestroy(ctx->ev_val);
+  if (ctx->val_host) (void)hipHostFree(ctx->val_host);
   delete ctx;
 }
 
@@ -323,8 +349,17 @@ int stm_offsets(stm_ctx* ctx, const stm_points* model, const stm_points* scene, 
   if (flags & STM_DEVICE_PTRS) {
     if (!ctx) return fail(STM_EINVAL, "device pointers need a context");
     STM_HIP(hipSetDevice(ctx->device));
-    STM_HIP(hipMemcpy(&t0, model->t, sizeof(int32_t), hipMemcpyDeviceToHost));
-    STM_HIP(hipMemcpy(&t1, model->t + model->n - 1, sizeof(int32_t), hipMemcpyDeviceToHost));
+    // one copy of all frames costs less than two of one
+    constexpr int kFew = 1024;
+    if (model->n <= kFew) {
+      int32_t t[kFew];
+      STM_HIP(hipMemcpy(t, model->t, model->n * sizeof(int32_t), hipMemcpyDeviceToHost));
+      t0 = t[0];
+      t1 = t[model->n - 1];
+    } else {
+      STM_HIP(hipMemcpy(&t0, model->t, sizeof(int32_t), hipMemcpyDeviceToHost));
+      STM_HIP(hipMemcpy(&t1, model->t + model->n - 1, sizeof(int32_t), hipMemcpyDeviceToHost));
+    }
   } else {
     t0 = model->t[0];
     t1 = model->t[model->n - 1];
@@ -340,13 +375,28 @@ int stm_match(stm_ctx* ctx, const stm_points* model, const stm_points* scene,
               double* energy64, double* energy_u64, int32_t* assign, void* hip_stream) {
   err().clear();
   Prepared pr;
-  int rc = prepare(ctx, model, scene, params, hip_stream, pr);
+  MatchPart part;
+  // model angles and the unary table (Section 3.3), queued before the host waits
+  // for the validation
+  const auto tables = [&](const Prepared& q) {
+    int rc;
+    if ((rc = grow(ctx, ctx->theta, (size_t)q.m.M * sizeof(float2), q.st))) return rc;
+    if ((rc = grow(ctx, ctx->U, (size_t)q.m.M * q.s.S * sizeof(float), q.st))) return rc;
+    part.theta = static_cast<float2*>(ctx->theta.p);
+    part.U = static_cast<float*>(ctx->U.p);
+    part.tables = true;
+    return match_tables(ctx, q, part.theta, part.U, nullptr);
+  };
+  const bool work = tau_end > tau_begin && energy32 && assign;
+  int rc = work ? prepare(ctx, model, scene, params, hip_stream, pr, nullptr, tables)
+                : prepare(ctx, model, scene, params, hip_stream, pr);
   if (rc) return rc;
   if ((rc = check_range(pr, tau_begin, tau_end))) return rc;
   const int n_tau = tau_end - tau_begin;
   if (n_tau == 0) return STM_OK;
   if (!energy32 || !assign) return fail(STM_EINVAL, "energy32 and assign are required");
-  const int M = pr.m.M, S = pr.s.S;
+  if (!part.tables && (rc = tables(pr))) return rc;
+  const int M = pr.m.M;
   const hipStream_t st = pr.st;
 
   // outputs: caller's device buffers, or staging for host pointers
@@ -369,19 +419,14 @@ int stm_match(stm_ctx* ctx, const stm_points* model, const stm_points* scene,
     }
   }
 
-  // model angles, the unary table (Section 3.3) and the recursion's scratch,
-  // the value tables in chunks of offsets bounded by vt_chunk_bytes
+  // the recursion's scratch, the value tables in chunks of offsets bounded by
+  // vt_chunk_bytes
   MatchScratch sc;
-  if ((rc = grow(ctx, ctx->theta, (size_t)M * sizeof(float2), st))) return rc;
-  if ((rc = grow(ctx, ctx->U, (size_t)M * S * sizeof(float), st))) return rc;
   const size_t per_tau = vt_bytes_per_offset(M, params);
   sc.chunk = static_cast<int>(std::min<size_t>(n_tau, std::max<size_t>(1, ctx->vt_chunk_bytes / per_tau)));
   if ((rc = grow(ctx, ctx->vt, per_tau * sc.chunk, st))) return rc;
   if ((rc = grow(ctx, ctx->last2, (size_t)sc.chunk * sizeof(int2), st))) return rc;
   if ((rc = grow(ctx, ctx->degen, (size_t)sc.chunk * sizeof(int32_t), st))) return rc;
-  MatchPart part;
-  part.theta = static_cast<float2*>(ctx->theta.p);
-  part.U = static_cast<float*>(ctx->U.p);
   sc.vt = static_cast<float*>(ctx->vt.p);
   sc.last2 = static_cast<int2*>(ctx->last2.p);
   sc.degen = static_cast<int32_t*>(ctx->degen.p);

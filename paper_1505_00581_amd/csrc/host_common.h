@@ -9,6 +9,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <functional>
 #include <string>
 #include <vector>
 
@@ -57,6 +58,9 @@ struct stm_ctx {
   double prof_plan_ms = 0.0;      // recursion launches of plan runs (events inside the graph)
   int64_t prof_plan_launches = 0;
   int dp_waves = 0;  // 0: the launch's rule
+  // the validation words on the host (pinned) and the event after their copy
+  int32_t* val_host = nullptr;
+  hipEvent_t ev_val = nullptr;
 };
 
 // The learned candidate pruner: FP32 parameters packed as
@@ -107,8 +111,12 @@ struct FixedPrep {
   int32_t* fstart = nullptr;
 };
 
+// The inputs of a call checked and on the device.  early (device pointers):
+// queues work that needs the inputs but not their validation, which the host
+// waits for meanwhile; not called for host pointers.
 int prepare(stm_ctx* ctx, const stm_points* m, const stm_points* s, const stm_params* p,
-            void* hip_stream, Prepared& out, const FixedPrep* fixed = nullptr);
+            void* hip_stream, Prepared& out, const FixedPrep* fixed = nullptr,
+            const std::function<int(const Prepared&)>& early = {});
 
 // Buffers of the split-precision unary table: BF16 descriptors (rows padded to
 // the MFMA tile) and their squared norms.  All null: the context's, grown on
@@ -137,6 +145,7 @@ struct MatchPart {
   float* e32 = nullptr;
   double *e64 = nullptr, *eu = nullptr;
   int32_t* assign = nullptr;
+  bool tables = false;  // angles and unary table are queued already
 };
 
 // Device scratch of the call: the BF16 buffers (split precision) and, for
@@ -150,11 +159,13 @@ struct MatchScratch {
   int chunk = 0;
 };
 
-// The kernels of stm_match over n_tau offsets of every model (at most
+// match_tables: a model's angles and unary table.  match_kernels: the kernels
+// of stm_match over n_tau offsets of every model (at most
 // stm::kDPParts, one scene) on prepared inputs and device outputs: model angles,
-// unary tables, then per chunk of offsets the recursion (fast and degenerate
+// unary tables where not queued, then per chunk of offsets the recursion (fast and degenerate
 // variants), backtracking and the FP64 re-score.  `timed`: HIP events around
 // the fast recursion launches when the context's profiling is on.
+int match_tables(stm_ctx* ctx, const Prepared& pr, float2* theta, float* U, const Bf16Bufs* bf);
 int match_kernels(stm_ctx* ctx, const MatchPart* parts, int n_parts, const stm_params* p, int n_tau,
                   const MatchScratch& sc, bool timed);
 

@@ -38,12 +38,16 @@ int check_pruner(stm_pruner* P) {
 // Inputs of one pair on the device with the unary table in ctx->U.
 int pair_inputs(stm_pruner* P, const stm_points* m, const stm_points* s, const stm_params* prm, void* stream,
                 Prepared& pr) {
-  int rc = prepare(P->ctx, m, s, prm, stream, pr);
+  stm_ctx* ctx = P->ctx;
+  const auto table = [&](const Prepared& q) {
+    if (m->dim != P->dim) return STM_OK;  // refused below
+    const int rc = grow(ctx, ctx->U, (size_t)q.m.M * q.s.S * sizeof(float), q.st);
+    return rc ? rc : unary_table(ctx, q, static_cast<float*>(ctx->U.p));
+  };
+  int rc = prepare(ctx, m, s, prm, stream, pr, nullptr, table);
   if (rc) return rc;
   if (m->dim != P->dim) return fail(STM_EINVAL, "descriptor dimension differs from the pruner's");
-  stm_ctx* ctx = P->ctx;
-  if ((rc = grow(ctx, ctx->U, (size_t)pr.m.M * pr.s.S * sizeof(float), pr.st))) return rc;
-  return unary_table(ctx, pr, static_cast<float*>(ctx->U.p));
+  return pr.device ? STM_OK : table(pr);
 }
 
 // Host group list (tau, i) checked against the pair and staged on the device.
