@@ -6,6 +6,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -83,6 +84,43 @@ const char* bit_message(int bits) {
   if (bits & 8) return "non-finite model coordinate or descriptor";
   if (bits & 16) return "non-finite scene coordinate or descriptor";
   return "invalid input";
+}
+
+// Pinned words of the contexts' validation results: 64 slots of one allocation
+// (0.1 ms to make) that lasts as long as the process, an allocation of its own
+// for each context beyond those.
+namespace {
+constexpr int kWordSlots = 64, kSlotWords = 16;  // a cache line each
+std::mutex words_mu;
+int32_t* words = nullptr;
+uint64_t words_used = 0;
+}  // namespace
+
+int32_t* take_words() {
+  int32_t* own = nullptr;
+  std::lock_guard<std::mutex> lock(words_mu);
+  if (!words && hipHostMalloc(reinterpret_cast<void**>(&words), kWordSlots * kSlotWords * sizeof(int32_t),
+                              hipHostMallocPortable) != hipSuccess) {
+    words = nullptr;
+    return nullptr;
+  }
+  for (int q = 0; q < kWordSlots; ++q)
+    if (!(words_used >> q & 1)) {
+      words_used |= uint64_t(1) << q;
+      return words + q * kSlotWords;
+    }
+  return hipHostMalloc(reinterpret_cast<void**>(&own), kSlotWords * sizeof(int32_t), hipHostMallocPortable) == hipSuccess
+             ? own
+             : nullptr;
+}
+
+void give_words(int32_t* p) {
+  if (!p) return;
+  std::lock_guard<std::mutex> lock(words_mu);
+  if (words && p >= words && p < words + kWordSlots * kSlotWords)
+    words_used &= ~(uint64_t(1) << ((p - words) / kSlotWords));
+  else
+    (void)hipHostFree(p);
 }
 
 int host_validate(const stm_points* m, const stm_points* s) {
@@ -307,10 +345,10 @@ int stm_create(stm_ctx** out, int hip_device) {
   stm_ctx* c = new (std::nothrow) stm_ctx();
   if (!c) return fail(STM_ENOMEM, "host allocation failed");
   c->device = hip_device;
-  if (hipHostMalloc(reinterpret_cast<void**>(&c->val_host), 2 * sizeof(int32_t), hipHostMallocDefault) != hipSuccess ||
-      hipEventCreateWithFlags(&c->ev_val, hipEventDisableTiming) != hipSuccess) {
+  c->val_host = take_words();
+  if (!c->val_host || hipEventCreateWithFlags(&c->ev_val, hipEventDisableTiming) != hipSuccess) {
     (void)hipGetLastError();
-    if (c->val_host) (void)hipHostFree(c->val_host);
+    give_words(c->val_host);
     delete c;
     return fail(STM_ENOMEM, "pinned host allocation failed");
   }
@@ -334,7 +372,7 @@ void stm_destroy(stm_ctx* ctx) {
   for (DevBuf* b : bufs) release(*b);
   for (hipEvent_t ev : ctx->prof_ev) (void)hipEventDestroy(ev);
   if (ctx->ev_val) (void)hipEventDestroy(ctx->ev_val);
-  if (ctx->val_host) (void)hipHostFree(ctx->val_host);
+  give_words(ctx->val_host);
   delete ctx;
 }
 
