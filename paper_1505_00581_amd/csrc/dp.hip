@@ -1050,8 +1050,11 @@ struct FewShared {
   int32_t red_i[NW];
 };
 
+// rec (nullable): every list's candidates are kept there, [M][K] (x, y, frame,
+// node; node -1 past the list).
 template <int NW, bool DEGEN, int KL>
-__device__ __forceinline__ DPResult dp_forward_few(FewShared<NW, KL>& sh, const MatchView& a, float* vtm) {
+__device__ __forceinline__ DPResult dp_forward_few(FewShared<NW, KL>& sh, const MatchView& a, float* vtm,
+                                                   float4* rec) {
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const bool producer = wv == NW;
   const int M = a.m.M, VS = a.vs;
@@ -1068,6 +1071,7 @@ __device__ __forceinline__ DPResult dp_forward_few(FewShared<NW, KL>& sh, const 
     float2 xy;
     int32_t t;
     float u;
+    int32_t node = -1;
   };
   auto fetch_list = [&](int j) {
     List l;
@@ -1083,11 +1087,14 @@ __device__ __forceinline__ DPResult dp_forward_few(FewShared<NW, KL>& sh, const 
       f.xy = ro(a.s.xy + n);
       f.t = ro(a.s.t + n);
       f.u = ro(a.U + (long long)j * a.us + n);
+      f.node = n;
     }
     return f;
   };
   auto commit = [&](int j, const Values& f) {
     const int k = f.c.count(), sl = j & 3;
+    if (rec && lane < a.sp.K)
+      rec[j * a.sp.K + lane] = make_float4(f.xy.x, f.xy.y, __int_as_float(f.t), __int_as_float(f.node));
     if (lane < k) {
       sh.cxy[sl][lane] = f.xy;
       sh.ctt[sl][lane] = f.t;
@@ -1356,6 +1363,49 @@ __device__ __forceinline__ void backtrack_wave(const MatchView& a, const float* 
   }
 }
 
+// The same walk with the value tables and the candidates in LDS (dp_forward_few's
+// vtm and rec; no dummies, plain angles): nothing of a step waits for memory.
+template <bool DEGEN>
+__device__ __forceinline__ void backtrack_lds(const MatchView& a, const float* vtm, const float4* rec, int r_end,
+                                              int c_end, int lane, int32_t* out) {
+  const int M = a.m.M, K = a.sp.K, VS = a.vs;
+  const int T = pair_limit(a.sp), TS = span_limit(a.sp);
+  const float INF = __builtin_inff();
+  const int kl = lane < K ? lane : 0;
+  int r = __builtin_amdgcn_readfirstlane(r_end);
+  float4 pc = rec[(M - 1) * K + __builtin_amdgcn_readfirstlane(c_end)], pr = rec[(M - 2) * K + r];
+  float4 pk = rec[(M - 3) * K + kl];
+  if (lane == 0) {
+    out[M - 1] = __float_as_int(pc.w);
+    out[M - 2] = __float_as_int(pr.w);
+  }
+  float2 th_l = a.theta[min(((M - 1) & ~63) + lane, M - 1)];
+  for (int i = M - 1; i >= 2; --i) {
+    if ((i & 63) == 63) th_l = a.theta[min((i & ~63) + lane, M - 1)];
+    const float2 th = make_float2(lane_value(th_l.x, i & 63), lane_value(th_l.y, i & 63));
+    const int tr = __float_as_int(pr.z), nr = __float_as_int(pr.w), tc = __float_as_int(pc.z);
+    const int tk = __float_as_int(pk.z), nk = __float_as_int(pk.w);
+    const bool adm = lane < K && nk >= 0 && consecutive_ok(a.sp, T, nk, tk, nr, tr) && span_ok(tk, tc, TS);
+    float tot = INF;
+    if (adm) {
+      const float v = vtable(vtm, a, i - 1)[lane * VS + r];
+      const float2 xr = make_float2(pr.x, pr.y), xa = make_float2(pc.x, pc.y), xk = make_float2(pk.x, pk.y);
+      const bool same = xa.x == xr.x && xa.y == xr.y;
+      float bm, be;
+      cell_consts<false>(th, neg_dir<DEGEN>(xr, xa), bm, be);
+      tot = relax<DEGEN>(v, neg_dir<DEGEN>(xk, xr), neg_dir<DEGEN>(xk, xa), bm, be, th, same, a.w);
+    }
+    const float4 pn = rec[(i >= 3 ? i - 3 : 0) * K + kl];
+    const float best = wave_min(tot);
+    const int bk = __ffsll(static_cast<long long>(__ballot(tot == best))) - 1;
+    pc = pr;
+    pr = make_float4(lane_value(pk.x, bk), lane_value(pk.y, bk), lane_value(pk.z, bk), lane_value(pk.w, bk));
+    if (lane == 0) out[i - 2] = __float_as_int(pr.w);
+    r = bk;
+    pk = pn;
+  }
+}
+
 // ---- per-offset kernels: one workgroup per offset of a (model, scene) pair ------
 __device__ __forceinline__ int part_of(const DPParts& b, int wg) {
   int q = 0;
@@ -1406,17 +1456,33 @@ void k_dp(DPParts parts) {
   }
 }
 
-template <int NW, bool DEGEN, int KL>
+// HIST: the value tables and the candidates stay in LDS and one wave of the
+// workgroup backtracks from there.
+template <int NW, bool DEGEN, int KL, bool HIST>
 __global__ __launch_bounds__((NW + 1) * 64) void k_dp_few(DPParts parts) {
   __shared__ FewShared<NW, KL> sh;
+  extern __shared__ __align__(16) float hist[];
   const int part = part_of(parts, blockIdx.x), tl = blockIdx.x - parts.first[part];
   const DPLaunch& a = parts.p[part];
   if (DEGEN && a.degen[tl] == 0) return;
-  const DPResult r = dp_forward_few<NW, DEGEN, KL>(sh, view_of(a, tl), scratch_of(a, tl));
+  const MatchView v = view_of(a, tl);
+  float* vt = hist + 4 * a.m.M * a.sp.K;  // behind the candidates
+  float4* rec = reinterpret_cast<float4*>(hist);
+  const DPResult r = HIST ? dp_forward_few<NW, DEGEN, KL>(sh, v, vt, rec)
+                          : dp_forward_few<NW, DEGEN, KL>(sh, v, scratch_of(a, tl), nullptr);
   if (threadIdx.x == 0) {
     a.e32[tl] = r.v;
-    a.last2[tl] = make_int2(r.idx / KL, r.idx % KL);
+    if (!HIST) a.last2[tl] = make_int2(r.idx / KL, r.idx % KL);
     if (!DEGEN) a.degen[tl] = r.flag;
+  }
+  if (HIST && threadIdx.x < 64 && !r.flag) {
+    const int lane = threadIdx.x, M = a.m.M;
+    int32_t* out = a.assign + (long long)tl * M;
+    if (r.v < __builtin_inff()) {
+      backtrack_lds<DEGEN>(v, vt, rec, r.idx / KL, r.idx % KL, lane, out);
+    } else {
+      for (int i = lane; i < M; i += 64) out[i] = -1;
+    }
   }
 }
 
@@ -1750,6 +1816,21 @@ DPParts dp_parts(const DPLaunch* a, int n_parts, int& n) {
   return b;
 }
 
+// LDS of the value tables and candidates where short lists keep them there, 0
+// where they do not fit beside the kernel's own in 64 KB or the launch has more
+// matchings than two per CU, whose other workgroups they would keep out.  20
+// points, lists of 16: 64 us, recursion and backtracking 53 + 27 through memory
+// and a second launch.
+size_t few_hist_bytes(const DPLaunch* a, int n_parts, int n) {
+  const DPLaunch& p = a[0];
+  if (p.dummy || p.sp.uns || p.sp.K > 32 || n > 2 * kCUs) return 0;
+  int m = 0;
+  for (int q = 0; q < n_parts; ++q) m = a[q].m.M > m ? a[q].m.M : m;
+  const size_t bytes = (size_t)(m - 2) * p.sp.K * p.sp.K * sizeof(float) + (size_t)m * p.sp.K * sizeof(float4);
+  const size_t own = p.sp.K <= 16 ? sizeof(FewShared<4, 16>) : sizeof(FewShared<12, 32>);
+  return bytes + own <= 64 * 1024 ? bytes : 0;
+}
+
 template <bool DEGEN>
 hipError_t launch_dp_waves(const DPLaunch* parts, int n_parts, hipStream_t st) {
   int n = 0;
@@ -1771,24 +1852,31 @@ hipError_t launch_dp_waves(const DPLaunch* parts, int n_parts, hipStream_t st) {
       hipLaunchKernelGGL((k_dp<8, DEGEN, 64, false, true>), dim3(n), dim3(8 * 64), 0, st, b);
     return hipGetLastError();
   }
-#define STM_DP_FEW(NW, KL) \
-  hipLaunchKernelGGL((k_dp_few<NW, DEGEN, KL>), dim3(n), dim3((NW + 1) * 64), 0, st, b)
+#define STM_DP_FEW(NW, KL, HIST) \
+  hipLaunchKernelGGL((k_dp_few<NW, DEGEN, KL, HIST>), dim3(n), dim3((NW + 1) * 64), HIST ? hist : 0, st, b)
+  const size_t hist = few_hist_bytes(parts, n_parts, n);
   if (a.sp.K <= 16) {
-    if (n <= 2 * kCUs)
-      STM_DP_FEW(4, 16);
+    if (n <= 2 * kCUs && hist)
+      STM_DP_FEW(4, 16, true);
+    else if (n <= 2 * kCUs)
+      STM_DP_FEW(4, 16, false);
     else if (n <= 8 * kCUs)
-      STM_DP_FEW(3, 16);
+      STM_DP_FEW(3, 16, false);
     else
       hipLaunchKernelGGL((k_dp<1, DEGEN, 16>), dim3(n), dim3(64), 0, st, b);
     return hipGetLastError();
   }
   if (a.sp.K <= 32) {
-    if (n <= kCUs)
-      STM_DP_FEW(12, 32);
+    if (n <= kCUs && hist)
+      STM_DP_FEW(12, 32, true);
+    else if (n <= kCUs)
+      STM_DP_FEW(12, 32, false);
+    else if (n <= 2 * kCUs && hist)
+      STM_DP_FEW(7, 32, true);
     else if (n <= 2 * kCUs)
-      STM_DP_FEW(7, 32);
+      STM_DP_FEW(7, 32, false);
     else
-      STM_DP_FEW(3, 32);
+      STM_DP_FEW(3, 32, false);
     return hipGetLastError();
   }
 #undef STM_DP_FEW
@@ -1883,7 +1971,7 @@ hipError_t launch_rescore_batch(const PairDev* pairs, const int2* items, int n_i
 hipError_t launch_backtrack(const DPLaunch* a, int n_parts, hipStream_t st) {
   int n = 0;
   const DPParts b = dp_parts(a, n_parts, n);
-  if (n <= 0) return hipSuccess;
+  if (n <= 0 || few_hist_bytes(a, n_parts, n)) return hipSuccess;  // the recursion backtracked
   hipLaunchKernelGGL(k_backtrack, dim3(n), dim3(64), 0, st, b);
   return hipGetLastError();
 }
