@@ -354,11 +354,12 @@ __device__ __forceinline__ Cands cands_of(const MatchView& a, int j) {
 }
 
 // Value table of step i (cells V_i(a_{i-1}, a_i), i = 1..M-2) inside the
-// matching's scratch vt [M-2][vs][vs], V_i(r, c) at r * vs + c: the lanes of a
-// chunk run along rows, so a store touches a few lines; by column every lane
-// of it would touch its own (k_dp at 1387 offsets, 75 points, K = 64: 5.51 ms
-// against 5.72).  With dummies, index K holds the epsilon state on
-// either side.
+// matching's scratch vt [M-2][vs][vs], stored by column: V_i(r, c) at c * vs +
+// r, so that backtracking reads the values of one column (every predecessor of
+// the chosen cell) contiguously (with dummies, index K holds the epsilon state
+// on either side).  By row the stores touch fewer lines, but they are hidden:
+// the recursion's launch takes the same 5.50 ms at 1387 offsets x 75 points, K =
+// 64, and the backtracking 157 us instead of 121.
 __device__ __forceinline__ float* vtable(float* vt, const MatchView& a, int i) {
   return vt + (long long)(i - 1) * a.vs * a.vs;
 }
@@ -569,7 +570,7 @@ __device__ __forceinline__ DPResult dp_forward(DPShared<NW, KL, DUMMY, PACKED>& 
         const float q = a.lambda2 * fabsf(static_cast<float>(dtm - (tp - tr)));
         vr[s] = (sh.cu[0][r] + sh.cu[1][col]) + q;
         ar[s] = neg_dir<DEGEN>(xr, xa);
-        if (valid) vt[r * VS + col] = vr[s];
+        if (valid) vt[col * VS + r] = vr[s];
         pi[s] = valid ? r * KL + col : -1;
         if constexpr (PACKED) {
           if (valid) sh.v[1][pi[s]] = vr[s];
@@ -582,12 +583,12 @@ __device__ __forceinline__ DPResult dp_forward(DPShared<NW, KL, DUMMY, PACKED>& 
         if (lane < sh.ck[1]) {
           const float e = cw + sh.cu[1][lane];
           sh.de[1][lane] = e;
-          vt[Kc * VS + lane] = e;
+          vt[lane * VS + Kc] = e;
         }
         if (lane < sh.ck[0]) {
           const float f = sh.cu[0][lane] + cw;
           sh.df[1][lane] = f;
-          vt[lane * VS + Kc] = f;
+          vt[Kc * VS + lane] = f;
         }
         if (lane == 0) {
           sh.dg[1] = cw + cw;
@@ -710,7 +711,7 @@ __device__ __forceinline__ DPResult dp_forward(DPShared<NW, KL, DUMMY, PACKED>& 
             const float v = (sh.cu[i & 3][col] + qw * fabsf(static_cast<float>(dtm - dt[s]))) + best;
             if (pi[s] >= 0) {
               sh.v[vb ^ 1][pi[s] & kCell] = v;
-              if (vt) vt[r * VS + col] = v;
+              if (vt) vt[col * VS + r] = v;
             }
           }
         }
@@ -857,7 +858,7 @@ __device__ __forceinline__ DPResult dp_forward(DPShared<NW, KL, DUMMY, PACKED>& 
           vnew = (sh.cu[s0][col] + q) + best;
           if (pi[s] >= 0) {
             sh.v[vb ^ 1][pi[s] & kCell] = vnew;
-            if (vt) vt[r * VS + col] = vnew;
+            if (vt) vt[col * VS + r] = vnew;
           }
         }
       } else {
@@ -914,7 +915,7 @@ __device__ __forceinline__ DPResult dp_forward(DPShared<NW, KL, DUMMY, PACKED>& 
           }
           const float q = qw * fabsf(static_cast<float>(dtm - (tp - tr)));
           vnew = (sh.cu[s0][col] + q) + best;
-          if (valid && vt) vt[r * VS + col] = vnew;
+          if (valid && vt) vt[col * VS + r] = vnew;
           pi[s] = valid ? r * KL + col : -1;
           vr[s] = vnew;
           ar[s] = anew;
@@ -943,7 +944,7 @@ __device__ __forceinline__ DPResult dp_forward(DPShared<NW, KL, DUMMY, PACKED>& 
         if (r < Kp && sub == 0) {
           const float v = cw + fminf(sh.de[prv][r], m);
           sh.df[cur][r] = v;
-          if (vt) vt[r * VS + Kc] = v;
+          if (vt) vt[Kc * VS + r] = v;
         }
       }
       if (wv == kBuilder) {
@@ -953,7 +954,7 @@ __device__ __forceinline__ DPResult dp_forward(DPShared<NW, KL, DUMMY, PACKED>& 
         if (lane < Kn) {
           const float v = sh.cu[s0][lane] + m;
           sh.de[cur][lane] = v;
-          if (vt) vt[Kc * VS + lane] = v;
+          if (vt) vt[lane * VS + Kc] = v;
         }
         if (lane == 0) {
           sh.dg[cur] = cw + m;
@@ -1221,7 +1222,7 @@ __device__ __forceinline__ DPResult dp_forward_few(FewShared<NW, KL>& sh, const 
         }
         if (valid) {
           sh.va[b][r * KL + col] = make_float2(v, anew);
-          if (vt) vt[r * VS + col] = v;
+          if (vt) vt[col * VS + r] = v;
           const int idx = r * KL + col;
           if (i == M - 1 && (v < bv || (v == bv && idx < bi))) { bv = v; bi = idx; }
         }
@@ -1264,7 +1265,7 @@ __device__ __forceinline__ DPResult dp_forward_few(FewShared<NW, KL>& sh, const 
 // step; a list is read two steps and its nodes' data one step before their
 // use.  The chosen cell is wave-uniform, so its data come from their lanes by
 // readlane and the minimum by DPP: of the step's chain only the read of the
-// chosen cell's values waits for memory.  1387 matchings of 75 points: 157 us,
+// chosen cell's values waits for memory.  1387 matchings of 75 points: 121 us,
 // 228 with the lists' reads in the chain and shuffles.
 struct LaneCand {
   int node;   // scene node of this lane's candidate, -1 past the list
@@ -1331,8 +1332,8 @@ __device__ __forceinline__ void backtrack_wave(const MatchView& a, const float* 
     if (!r_eps) adm = adm && (c_eps ? admissible(Lk.t, tr, T)
                                     : consecutive_ok(a.sp, T, Lk.node, Lk.t, nr, tr) && span_ok(Lk.t, tc, TS));
     float v = INF;
-    if (adm) v = vp[lane * VS + (r_eps ? Kc : r)];
-    if (DUMMY) teps = vp[Kc * VS + (r_eps ? Kc : r)];
+    if (adm) v = vp[(r_eps ? Kc : r) * VS + lane];
+    if (DUMMY) teps = vp[(r_eps ? Kc : r) * VS + Kc];
     // the next lists, fetched while this step runs
     LaneCand Ln;
     if (i >= 3) Ln = lane_cand(a, ln, lane);
@@ -1388,7 +1389,7 @@ __device__ __forceinline__ void backtrack_lds(const MatchView& a, const float* v
     const bool adm = lane < K && nk >= 0 && consecutive_ok(a.sp, T, nk, tk, nr, tr) && span_ok(tk, tc, TS);
     float tot = INF;
     if (adm) {
-      const float v = vtable(vtm, a, i - 1)[lane * VS + r];
+      const float v = vtable(vtm, a, i - 1)[r * VS + lane];
       const float2 xr = make_float2(pr.x, pr.y), xa = make_float2(pc.x, pc.y), xk = make_float2(pk.x, pk.y);
       const bool same = xa.x == xr.x && xa.y == xr.y;
       float bm, be;
