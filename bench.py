@@ -496,7 +496,7 @@ def bench_trellis(ctx, steps: int, t_values=(10, 0), model_counts=(1, 50)):
                                      unit="TOP/s", frac=round(ach * 1e12 / VALU_PEAK_OPS, 4),
                                      ops_per_relax=OPS_PER_RELAX,
                                      kernel=("k_trellis_fused + k_trellis_final" if info["fused"] else
-                                             "k_trellis_first + k_trellis_step x (M-2) + k_trellis_final")),
+                                             "k_trellis_first + k_trellis_step or k_trellis_wide x (M-2) + k_trellis_final")),
                        feasible=int(np.isfinite(e32).sum()))
             out.append(row)
             log(f"  trellis T={T} models={nm}: {ms:.3f} ms per run ({ms / s.n_frames:.5f} ms/frame"

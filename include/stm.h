@@ -404,8 +404,8 @@ STM_API int stm_match_batch(stm_ctx* ctx, const stm_points* models, int32_t n_mo
  * node_end) of one scene: the band, its tiles, the direction tables and the
  * value tables (sum over models of (M - 1) x cells floats).  A run solves
  * every model: the unary tables, the min-sum recursion (forward form of Eq.
- * 10-11) over all models (one launch for all steps, one workgroup per model,
- * when the band fits a workgroup's LDS; else one launch per step), the
+ * 10-11) over all models (one launch for all steps, up to 16 workgroups
+ * per model, when the band fits a workgroup's LDS; else one launch per step), the
  * optimum and backtracking
  * (Eq. 12-13) on the device, and the FP64 re-score (Eq. 1).
  * Outputs: energy32, energy64, energy_u64 [n_models] (nullable: the FP64 ones)
@@ -431,7 +431,7 @@ STM_API int stm_trellis_run(stm_trellis* trellis, float* energy32, double* energ
  * work of one run over all models: dense cells (M - 1) n^2, feasible cells
  * (M - 1) x band cells, dense relaxations (M - 2) n^3, feasible relaxations
  * (admissible triples), the sum of the model sizes, and 1 if every step runs
- * in one launch (one workgroup per model, the band in LDS), 0 if each step is
+ * in one launch (the band in LDS), 0 if each step is
  * a launch of its own. */
 STM_API int stm_trellis_info(const stm_trellis* trellis, int64_t* info);
 /* One-shot: create, run once, destroy (waits for the run). */
