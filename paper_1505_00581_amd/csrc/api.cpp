@@ -151,7 +151,7 @@ int stage(stm_ctx* ctx, DevBuf& b, const T* host, size_t count, hipStream_t st) 
 
 int prepare(stm_ctx* ctx, const stm_points* m, const stm_points* s, const stm_params* p,
             void* hip_stream, Prepared& out, const FixedPrep* fixed,
-            const std::function<int(const Prepared&)>& early) {
+            EarlyWork early) {
   int rc = check_shapes(m, s, p);
   if (rc) return rc;
   if (!(p->flags & STM_DEVICE_PTRS)) {
@@ -204,7 +204,7 @@ int prepare(stm_ctx* ctx, const stm_points* m, const stm_points* s, const stm_pa
   if (out.device) {
     // what is queued behind the validation runs while the host waits for it; it
     // reads the inputs within their bounds whatever they hold
-    rc = early ? early(out) : STM_OK;
+    rc = early.run ? early.run(early.self, out) : STM_OK;
     if (rc) {
       (void)hipStreamSynchronize(out.st);
       return rc;

@@ -9,7 +9,6 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
-#include <functional>
 #include <string>
 #include <vector>
 
@@ -111,12 +110,22 @@ struct FixedPrep {
   int32_t* fstart = nullptr;
 };
 
+// A callable held by reference (nothing to allocate at a C entry).
+struct EarlyWork {
+  int (*run)(const void*, const Prepared&) = nullptr;
+  const void* self = nullptr;
+  EarlyWork() = default;
+  template <class F>
+  EarlyWork(const F& f)
+      : run([](const void* s, const Prepared& p) { return (*static_cast<const F*>(s))(p); }), self(&f) {}
+};
+
 // The inputs of a call checked and on the device.  early (device pointers):
 // queues work that needs the inputs but not their validation, which the host
 // waits for meanwhile; not called for host pointers.
 int prepare(stm_ctx* ctx, const stm_points* m, const stm_points* s, const stm_params* p,
             void* hip_stream, Prepared& out, const FixedPrep* fixed = nullptr,
-            const std::function<int(const Prepared&)>& early = {});
+            EarlyWork early = {});
 
 // Buffers of the split-precision unary table: BF16 descriptors (rows padded to
 // the MFMA tile) and their squared norms.  All null: the context's, grown on
