@@ -135,6 +135,18 @@ __device__ __forceinline__ float lane_value(float x, int l) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), l));
 }
 
+// A cell's value at step 1, (l1 U_0(r) + l1 U_1(c)) + l2 |dt_model - dt_scene|, and
+// at a later step, l1 U_i(c) + q_w |dt_model - dt_scene| + the minimum over the
+// predecessors.  The roundings are spelled out: left to the compiler, a product
+// formed outside the block of its sum (dp_forward_few) is rounded by itself, and
+// the layouts differ in the last bit.
+__device__ __forceinline__ float first_cell(float cr, float cc, float l2, int dtm, int dts) {
+  return fmaf(l2, fabsf(static_cast<float>(dtm - dts)), cr + cc);
+}
+__device__ __forceinline__ float later_cell(float cu, float qw, int dtm, int dts, float best) {
+  return fmaf(qw, fabsf(static_cast<float>(dtm - dts)), cu) + best;
+}
+
 // Cell of lane `lane` in chunk c: row r and column a; false past the last cell.
 __device__ __forceinline__ bool chunk_cell(const Chunk& c, int lane, int& r, int& a) {
   const int e = c.e0 + lane;
@@ -567,8 +579,7 @@ __device__ __forceinline__ DPResult dp_forward(DPShared<NW, KL, DUMMY, PACKED>& 
         const float2 xr = sh.cxy[0][r], xa = sh.cxy[1][col];
         const bool same = xa.x == xr.x && xa.y == xr.y;
         if (!DEGEN && same && valid) sh.flag = 1;
-        const float q = a.lambda2 * fabsf(static_cast<float>(dtm - (tp - tr)));
-        vr[s] = (sh.cu[0][r] + sh.cu[1][col]) + q;
+        vr[s] = first_cell(sh.cu[0][r], sh.cu[1][col], a.lambda2, dtm, tp - tr);
         ar[s] = neg_dir<DEGEN>(xr, xa);
         if (valid) vt[col * VS + r] = vr[s];
         pi[s] = valid ? r * KL + col : -1;
@@ -708,7 +719,7 @@ __device__ __forceinline__ DPResult dp_forward(DPShared<NW, KL, DUMMY, PACKED>& 
             cell_consts<UNS>(th, ar[s], bm, be);
             const float best = packed_min(vb, r, col, (pi[s] >> 12) & 127, (pi[s] >> 19) & 127, longest[s], bm, be,
                                           th, false);
-            const float v = (sh.cu[i & 3][col] + qw * fabsf(static_cast<float>(dtm - dt[s]))) + best;
+            const float v = later_cell(sh.cu[i & 3][col], qw, dtm, dt[s], best);
             if (pi[s] >= 0) {
               sh.v[vb ^ 1][pi[s] & kCell] = v;
               if (vt) vt[col * VS + r] = v;
@@ -854,8 +865,7 @@ __device__ __forceinline__ DPResult dp_forward(DPShared<NW, KL, DUMMY, PACKED>& 
           float bm, be;
           cell_consts<UNS>(th, anew, bm, be);
           const float best = packed_min(vb, r, col, lo, len, longest[s], bm, be, th, same);
-          const float q = qw * fabsf(static_cast<float>(dtm - (tp - tr)));
-          vnew = (sh.cu[s0][col] + q) + best;
+          vnew = later_cell(sh.cu[s0][col], qw, dtm, tp - tr, best);
           if (pi[s] >= 0) {
             sh.v[vb ^ 1][pi[s] & kCell] = vnew;
             if (vt) vt[col * VS + r] = vnew;
@@ -913,8 +923,7 @@ __device__ __forceinline__ DPResult dp_forward(DPShared<NW, KL, DUMMY, PACKED>& 
             const float2 v0 = vcol[k * KL];
             best = fminf(best, relax<DEGEN, UNS>(v0.x, v0.y, ccol[k * KL], bm, be, th, same, w));
           }
-          const float q = qw * fabsf(static_cast<float>(dtm - (tp - tr)));
-          vnew = (sh.cu[s0][col] + q) + best;
+          vnew = later_cell(sh.cu[s0][col], qw, dtm, tp - tr, best);
           if (valid && vt) vt[col * VS + r] = vnew;
           pi[s] = valid ? r * KL + col : -1;
           vr[s] = vnew;
@@ -1180,7 +1189,7 @@ __device__ __forceinline__ DPResult dp_forward_few(FewShared<NW, KL>& sh, const 
       const int tm = __builtin_amdgcn_readlane(tm_l, i & 63);
       const int dtm = tm - tm_prev;
       tm_prev = tm;
-      const float qw = a.lambda2 * (i >= 2 && i <= M - 2 ? 2.f : 1.f);
+      const float qw = a.lambda2 * (i <= M - 2 ? 2.f : 1.f);
       float* vt = i <= M - 2 ? vtable(vtm, a, i) : nullptr;
       const int nch = sh.nch[b];
       for (int ch = wv; ch < nch; ch += NW) {
@@ -1193,10 +1202,9 @@ __device__ __forceinline__ DPResult dp_forward_few(FewShared<NW, KL>& sh, const 
         const bool same = xa.x == xr.x && xa.y == xr.y;
         if (!DEGEN && same && valid) sh.flag = 1;
         const float anew = neg_dir<DEGEN>(xr, xa);
-        const float q = qw * fabsf(static_cast<float>(dtm - (tp - tr)));
         float v;
         if (i == 1) {
-          v = (sh.cu[s1][r] + sh.cu[s0][col]) + q;
+          v = first_cell(sh.cu[s1][r], sh.cu[s0][col], a.lambda2, dtm, tp - tr);
         } else {
           float bm, be;
           cell_consts<false>(th, anew, bm, be);
@@ -1218,7 +1226,7 @@ __device__ __forceinline__ DPResult dp_forward_few(FewShared<NW, KL>& sh, const 
             const float2 v0 = vcol[k * KL];
             best = fminf(best, relax<DEGEN>(v0.x, v0.y, ccol[k * KL], bm, be, th, same, w));
           }
-          v = (sh.cu[s0][col] + q) + best;
+          v = later_cell(sh.cu[s0][col], qw, dtm, tp - tr, best);
         }
         if (valid) {
           sh.va[b][r * KL + col] = make_float2(v, anew);
