@@ -1669,16 +1669,24 @@ __device__ __forceinline__ double wrap64(double x) {
 // The descriptor distances are taken four points at a time, 16 lanes per
 // point striding its descriptor (coalesced reads; partial sums joined by a
 // 16-lane tree); the triangle terms one point per lane.  A chain of dependent
-// reads bounds it, so W = 4 waves share a matching's points where few matchings
-// leave the chip idle (1387 of 75 points: 57 us, 96 with one wave) and one takes
-// each where there are many (34,000 of 30 points: 169 us, 220 with four).
-constexpr int kRescoreMany = 4096;
+// reads bounds it, so four waves share a matching's points while the chip (8192
+// waves) holds all of a launch at once, and one takes each above.  us with four
+// waves / with one, models of 30 and 75 points, descriptors of 162:
+//   matchings     512     1024       1536       2048       2560       4096
+//   30 points   8 / 17   10 / 27   22 / 33    25 / 34    34 / 36    48 / 39
+//   75 points  15 / 39   24 / 65   45 / 71    48 / 72    65 / 77    94 / 85
+// (descriptors of 16 cross at 1500 for 30 points and at 2300 for 75, by 1 to 2 us.)
+//
+// The sums do not depend on W: with four waves the points' terms go through LDS
+// and the first wave adds them as the single wave does, lane 16 g the distances
+// of points g, g + 4, ... and lane l the triangles ending at l, l + 64, ...; fused
+// products are spelled out, since the compiler picks either of two by itself.
+constexpr int kRescoreMany = 2048;
+constexpr int kRescoreBlock = 256;  // points of the terms held in LDS at a time
 template <int W>
 __device__ __forceinline__ void rescore(const ModelView& m, const SceneView& s, const SearchParams& sp, double l1, double l2,
                                         double l3, double wd, const int32_t* __restrict__ z, long long tl,
                                         double* __restrict__ e64, double* __restrict__ eu64) {
-  __shared__ double part_u[W], part_d[W];
-  __shared__ int part_bad[W];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int32_t T = pair_limit(sp), TS = span_limit(sp);
   const int M = m.M, dim = s.dim;
@@ -1690,10 +1698,9 @@ __device__ __forceinline__ void rescore(const ModelView& m, const SceneView& s, 
     }
     return;
   }
-  double su = 0.0, sd = 0.0;
-  int bad = 0;
   const int grp = lane >> 4, gl = lane & 15;
-  for (int i0 = wv * 4; i0 < M; i0 += W * 4) {
+  // the descriptor distance of point i0 + grp, in lane gl = 0 of its 16
+  const auto distance = [&](int i0) {
     const int i = i0 + grp;
     const int n = i < M ? ro(z + i) : kDummyNode;
     double acc = 0.0;
@@ -1706,24 +1713,28 @@ __device__ __forceinline__ void rescore(const ModelView& m, const SceneView& s, 
       }
     }
     for (int off = 8; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
-    if (gl == 0 && i < M) su += n == kDummyNode ? wd : sqrt(acc);
-  }
-  for (int i = threadIdx.x; i < M; i += W * 64) {
+    return n == kDummyNode ? wd : sqrt(acc);
+  };
+  // the terms of the triangle ending at point i, added in this order (the second
+  // one is 0 unless a point is a dummy); false where the assignment is infeasible
+  const auto triangle = [&](int i, double& ta, double& tb) {
+    bool ok = true;
+    ta = tb = 0.0;
     const int n = ro(z + i);
     const int nj = i >= 1 ? ro(z + (i - 1)) : kDummyNode;
     const int nk = i >= 2 ? ro(z + (i - 2)) : kDummyNode;
-    if (n != kDummyNode && nj != kDummyNode && !consecutive_ok(sp, T, nj, ro(s.t + nj), n, ro(s.t + n))) bad = 1;
+    if (n != kDummyNode && nj != kDummyNode && !consecutive_ok(sp, T, nj, ro(s.t + nj), n, ro(s.t + n))) ok = false;
     // the span reading (no dummies): the triangle's first and last frames
-    if (TS > 0 && i >= 2 && !span_ok(ro(s.t + ro(z + (i - 2))), ro(s.t + n), TS)) bad = 1;
+    if (TS > 0 && i >= 2 && !span_ok(ro(s.t + ro(z + (i - 2))), ro(s.t + n), TS)) ok = false;
     if (i >= 2 && (n == kDummyNode || nj == kDummyNode || nk == kDummyNode)) {
       // the Delta terms whose points are both matched; no D^g
       if (n != kDummyNode && nj != kDummyNode) {
         const long d1 = (long)(ro(m.t + i) - ro(m.t + (i - 1))) - (long)(ro(s.t + n) - ro(s.t + nj));
-        sd += (double)(d1 < 0 ? -d1 : d1);
+        ta = (double)(d1 < 0 ? -d1 : d1);
       }
       if (nj != kDummyNode && nk != kDummyNode) {
         const long d2 = (long)(ro(m.t + (i - 1)) - ro(m.t + (i - 2))) - (long)(ro(s.t + nj) - ro(s.t + nk));
-        sd += (double)(d2 < 0 ? -d2 : d2);
+        tb = (double)(d2 < 0 ? -d2 : d2);
       }
     } else if (i >= 2) {
       const long dt1 = (long)(ro(m.t + i) - ro(m.t + (i - 1))) - (long)(ro(s.t + n) - ro(s.t + nj));
@@ -1741,28 +1752,54 @@ __device__ __forceinline__ void rescore(const ModelView& m, const SceneView& s, 
         end_s = fabs(end_s);
       }
       const double d1 = wrap64(mid_m - mid_s), d2 = wrap64(end_m - end_s);
-      sd += (double)(dt1 < 0 ? -dt1 : dt1) + (double)(dt2 < 0 ? -dt2 : dt2) +
-            l3 * sqrt(d1 * d1 + d2 * d2);
+      ta = fma(l3, sqrt(fma(d1, d1, d2 * d2)), (double)(dt1 < 0 ? -dt1 : dt1) + (double)(dt2 < 0 ? -dt2 : dt2));
     }
+    return ok;
+  };
+  double su = 0.0, sd = 0.0;
+  int bad = 0;
+  if constexpr (W == 1) {
+    for (int i0 = 0; i0 < M; i0 += 4) {
+      const double u = distance(i0);
+      if (gl == 0 && i0 + grp < M) su += u;
+    }
+    for (int i = lane; i < M; i += 64) {
+      double ta, tb;
+      if (!triangle(i, ta, tb)) bad = 1;
+      sd += ta;
+      sd += tb;
+    }
+    for (int off = 32; off > 0; off >>= 1) bad |= __shfl_xor(bad, off);
+  } else {
+    __shared__ double tu[kRescoreBlock], ta[kRescoreBlock], tb[kRescoreBlock];
+    for (int b0 = 0; b0 < M; b0 += kRescoreBlock) {
+      const int n = min(kRescoreBlock, M - b0);
+      for (int j0 = wv * 4; j0 < n; j0 += W * 4) {
+        const double u = distance(b0 + j0);
+        if (gl == 0) tu[j0 + grp] = u;  // (past the last point: not read)
+      }
+      for (int j = threadIdx.x; j < n; j += W * 64)
+        if (!triangle(b0 + j, ta[j], tb[j])) bad = 1;
+      bad = __syncthreads_or(bad);
+      if (wv == 0) {
+        if (gl == 0)
+#pragma unroll 4
+          for (int j = grp; j < n; j += 4) su += tu[j];
+        for (int j = lane; j < n; j += 64) {
+          sd += ta[j];
+          sd += tb[j];
+        }
+      }
+      if (b0 + kRescoreBlock < M) __syncthreads();
+    }
+    if (wv != 0) return;
   }
   for (int off = 32; off > 0; off >>= 1) {
     su += __shfl_xor(su, off);
     sd += __shfl_xor(sd, off);
-    bad |= __shfl_xor(bad, off);
   }
   if (lane == 0) {
-    part_u[wv] = su;
-    part_d[wv] = sd;
-    part_bad[wv] = bad;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int q = 1; q < W; ++q) {
-      su += part_u[q];
-      sd += part_d[q];
-      bad |= part_bad[q];
-    }
-    if (e64) e64[tl] = bad ? inf : l1 * su + l2 * sd;
+    if (e64) e64[tl] = bad ? inf : fma(l1, su, l2 * sd);
     if (eu64) eu64[tl] = bad ? inf : l1 * su;
   }
 }

@@ -181,7 +181,7 @@ __device__ __forceinline__ double ang64(double ax, double ay, double bx, double 
                                         double cy) {
   const double ux = ax - bx, uy = ay - by, vx = cx - bx, vy = cy - by;
   if ((ux == 0.0 && uy == 0.0) || (vx == 0.0 && vy == 0.0)) return 0.0;
-  return atan2(ux * vy - uy * vx, ux * vx + uy * vy);
+  return atan2(fma(ux, vy, -(uy * vx)), fma(ux, vx, uy * vy));
 }
 
 // ---- launchers (return hipError_t of the launch) ---------------------------
