@@ -1350,14 +1350,17 @@ __device__ __forceinline__ void backtrack_wave(const MatchView& a, const float* 
       // V_i(eps, .) = ... + min(V_{i-1}(eps, eps), min_k V_{i-1}(k, eps)),
       // V_i(r, eps) = l1 W^d + min(V_{i-1}(eps, r), min_k V_{i-1}(k, r))
       tot = v;
-    } else if (adm) {
+    } else {
+      // the cell's points are read from their lanes (of other lists) with every
+      // lane active, not under the predecessors' mask
       const float2 xr = make_float2(lane_value(Lr.xy.x, r), lane_value(Lr.xy.y, r));
       const float2 xa = make_float2(lane_value(Lc.xy.x, c), lane_value(Lc.xy.y, c));
       const float2 th = ro(a.theta + i);
       const bool same = xa.x == xr.x && xa.y == xr.y;
       float bm, be;
       cell_consts<UNS>(th, neg_dir<DEGEN>(xr, xa), bm, be);
-      tot = relax<DEGEN, UNS>(v, neg_dir<DEGEN>(Lk.xy, xr), neg_dir<DEGEN>(Lk.xy, xa), bm, be, th, same, a.w);
+      if (adm)
+        tot = relax<DEGEN, UNS>(v, neg_dir<DEGEN>(Lk.xy, xr), neg_dir<DEGEN>(Lk.xy, xa), bm, be, th, same, a.w);
     }
     const float best = wave_min(tot);
     int bk = __ffsll(static_cast<long long>(__ballot(tot == best))) - 1;
