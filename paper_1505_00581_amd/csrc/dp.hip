@@ -42,7 +42,7 @@
 // predecessor range; the minima, and so every result, are the same.  Per step
 // the LDS holds the previous V cells with their directions and the (a_{i-2},
 // a_i) direction table; the new cells stay in registers until every wave has
-// finished reading, then replace the old ones (packed: go to a second buffer).
+// finished reading, then replace the old ones (list variant: go to a second buffer).
 // Only admissible cells are ever read back.
 //
 // Degenerate triangles.  A zero-length side gives a scene angle of 0 in the
@@ -288,11 +288,15 @@ struct DummyShared<KL, true> {
 };
 
 // The cells of the previous step, [a_{i-2}][a_{i-1}]: (V_{i-1}, -phi(z_{i-2} ->
-// z_{i-1})).  Packed schedules keep two buffers of values, so that a step that
-// keeps the directions of the one before needs no barrier between reading and
-// publishing, beside the first cell number of every chunk and the step's cell
-// count.
-template <int KL, bool PACKED>
+// z_{i-1})).  The list variant keeps two buffers of values apart from the
+// directions, so that a step that keeps the directions of the one before needs no
+// barrier between reading and publishing; where every step is built anew the third
+// read per term costs more (windowed lists of 64 at one point per frame, 3000
+// offsets x 75 points: 9.13 ms, 8.80 with values and directions side by side), so
+// the variant is taken for explicit lists of which more than five of seven repeat
+// the one before them: 20 models x 678 blocks of 60 nodes whose lists change every
+// 3 points 6.19 ms (5.63 without it), every 4 points 5.36 (5.63), never 2.73 (5.65).
+template <int KL, bool LISTS>
 struct CellShared {
   float2 va[KL * KL];
 };
@@ -300,13 +304,19 @@ template <int KL>
 struct CellShared<KL, true> {
   float v[2][KL * KL];
   float dir[KL * KL];
-  int16_t pstart[2][KL + 1];
-  int32_t ptot[2];
   int32_t same[8];  // list j (at j & 7) holds the nodes of list j - 1
 };
+// Packed schedules: the first cell number of every chunk and the step's cell count.
+template <int KL, bool PACKED>
+struct PackedShared {};
+template <int KL>
+struct PackedShared<KL, true> {
+  int16_t pstart[2][KL + 1];
+  int32_t ptot[2];
+};
 
-template <int NW, int KL, bool DUMMY = false, bool PACKED = false>
-struct DPShared : DummyShared<KL, DUMMY>, CellShared<KL, PACKED> {
+template <int NW, int KL, bool DUMMY = false, bool PACKED = false, bool LISTS = false>
+struct DPShared : DummyShared<KL, DUMMY>, CellShared<KL, LISTS>, PackedShared<KL, PACKED> {
   float ct[KL * KL];    // [a_{i-2}][a_i]: -phi(z_{i-2} -> z_i)
   float2 cxy[4][KL];    // candidate ring: coordinates,
   int32_t ctt[4][KL];   //   frames,
@@ -389,7 +399,7 @@ struct DPResult {
 // Forward pass of one matching by the whole workgroup (NW waves): writes the
 // value tables of steps 1..M-2 to vtm and returns the optimum to every thread.
 template <int NW, bool DEGEN, int KL, bool DUMMY = false, bool PACKED = false, bool UNS = false, bool LISTS = false>
-__device__ __forceinline__ DPResult dp_forward(DPShared<NW, KL, DUMMY, PACKED>& sh, const MatchView& a, float* vtm) {
+__device__ __forceinline__ DPResult dp_forward(DPShared<NW, KL, DUMMY, PACKED, LISTS>& sh, const MatchView& a, float* vtm) {
   static_assert(KL == 16 || KL == 64, "list capacity");
   static_assert(!DUMMY || KL == kMaxList, "dummies use the 64-slot layout");
   static_assert(!PACKED || (KL == kMaxList && !DUMMY), "packed schedules: 64-slot layout, no dummies");
@@ -583,7 +593,7 @@ __device__ __forceinline__ DPResult dp_forward(DPShared<NW, KL, DUMMY, PACKED>& 
         ar[s] = neg_dir<DEGEN>(xr, xa);
         if (valid) vt[col * VS + r] = vr[s];
         pi[s] = valid ? r * KL + col : -1;
-        if constexpr (PACKED) {
+        if constexpr (LISTS) {
           if (valid) sh.v[1][pi[s]] = vr[s];
         }
       }
@@ -649,35 +659,27 @@ __device__ __forceinline__ DPResult dp_forward(DPShared<NW, KL, DUMMY, PACKED>& 
                         bool same) {
     float best = INF;
     if constexpr (PACKED) {
-      const float* vcol = sh.v[vb] + r;
-      const float* dcol = sh.dir + r;
       const float* ccol = sh.ct + col;
       const float w = a.w;
+      const auto term = [&](int o) {  // the predecessor at offset o = k KL
+        float2 c;
+        if constexpr (LISTS) c = make_float2(sh.v[vb][o + r], sh.dir[o + r]);
+        else c = sh.va[o + r];
+        return relax<DEGEN, UNS>(c.x, c.y, ccol[o], bm, be, th, same, w);
+      };
       const int n = longest & (kFew - 1);
       const int end = max(lo + len - 1, 0);  // the lane's last predecessor
       const int k1 = max(end - 3, 0), k0 = min(lo, k1);
       int j = 0;
       for (; j + 2 < n; j += 4) {
         const int o = min(k0 + j, k1) * KL;
-        const float* vk = vcol + o;
-        const float* dk = dcol + o;
-        const float* ck = ccol + o;
-        const float t0 = relax<DEGEN, UNS>(vk[0], dk[0], ck[0], bm, be, th, same, w);
-        const float t1 = relax<DEGEN, UNS>(vk[KL], dk[KL], ck[KL], bm, be, th, same, w);
-        const float t2 = relax<DEGEN, UNS>(vk[2 * KL], dk[2 * KL], ck[2 * KL], bm, be, th, same, w);
-        const float t3 = relax<DEGEN, UNS>(vk[3 * KL], dk[3 * KL], ck[3 * KL], bm, be, th, same, w);
+        const float t0 = term(o), t1 = term(o + KL), t2 = term(o + 2 * KL), t3 = term(o + 3 * KL);
         best = fminf(fminf(best, fminf(fminf(t0, t1), t2)), t3);
       }
-      for (; j < n; ++j) {
-        const int o = min(lo + j, end) * KL;
-        best = fminf(best, relax<DEGEN, UNS>(vcol[o], dcol[o], ccol[o], bm, be, th, same, w));
-      }
+      for (; j < n; ++j) best = fminf(best, term(min(lo + j, end) * KL));
       if (longest & kFew) {
         float few = INF;
-        for (j = 0; j < min(n, 3); ++j) {
-          const int o = min(lo + j, end) * KL;
-          few = fminf(few, relax<DEGEN, UNS>(vcol[o], dcol[o], ccol[o], bm, be, th, same, w));
-        }
+        for (j = 0; j < min(n, 3); ++j) few = fminf(few, term(min(lo + j, end) * KL));
         best = len < 4 ? (len > 0 ? few : INF) : best;
       }
     }
@@ -762,8 +764,8 @@ __device__ __forceinline__ DPResult dp_forward(DPShared<NW, KL, DUMMY, PACKED>& 
       for (int s = 0; s < RPW; ++s) {
         const int ch = wv + NW * s;
         if (ch < nprev && pi[s] >= 0) {
-          if constexpr (PACKED) sh.dir[pi[s] & kCell] = ar[s];
-          else sh.va[pi[s]] = make_float2(vr[s], ar[s]);
+          if constexpr (LISTS) sh.dir[pi[s] & kCell] = ar[s];
+          else sh.va[pi[s] & kCell] = make_float2(vr[s], ar[s]);
         }
       }
     }
@@ -833,7 +835,7 @@ __device__ __forceinline__ DPResult dp_forward(DPShared<NW, KL, DUMMY, PACKED>& 
     float* vt = i <= M - 2 ? vtable(vtm, a, i) : nullptr;
     const float w = a.w;
     const int nch = n_slots(cur);
-    const int vb = (i & 1) ^ 1;  // packed: buffer of V_{i-1}
+    const int vb = (i & 1) ^ 1;  // list variant: buffer of V_{i-1}
 #pragma unroll
     for (int s = 0; s < RPW; ++s) {
       const int ch = wv + NW * s;
@@ -867,9 +869,10 @@ __device__ __forceinline__ DPResult dp_forward(DPShared<NW, KL, DUMMY, PACKED>& 
           const float best = packed_min(vb, r, col, lo, len, longest[s], bm, be, th, same);
           vnew = later_cell(sh.cu[s0][col], qw, dtm, tp - tr, best);
           if (pi[s] >= 0) {
-            sh.v[vb ^ 1][pi[s] & kCell] = vnew;
+            if constexpr (LISTS) sh.v[vb ^ 1][pi[s] & kCell] = vnew;
             if (vt) vt[col * VS + r] = vnew;
           }
+          vr[s] = vnew;
         }
       } else {
         if (ch < nch) {
@@ -987,7 +990,8 @@ __device__ __forceinline__ DPResult dp_forward(DPShared<NW, KL, DUMMY, PACKED>& 
       if constexpr (PACKED) {
         if (ch < nch && pi[s] >= 0) {
           const int idx = pi[s] & kCell;
-          const float v = sh.v[(M - 1) & 1][idx];
+          float v = vr[s];
+          if constexpr (LISTS) v = sh.v[(M - 1) & 1][idx];
           if (v < bv || (v == bv && idx < bi)) { bv = v; bi = idx; }
         }
       } else if (ch < nch) {
@@ -1455,7 +1459,7 @@ template <int NW, bool DEGEN, int KL, bool DUMMY = false, bool PACKED = false, b
 __global__ __launch_bounds__(NW * 64)
 __attribute__((amdgpu_waves_per_eu(KL < kMaxList || NW == 8 ? 4 : 1)))
 void k_dp(DPParts parts) {
-  __shared__ DPShared<NW, KL, DUMMY, PACKED> sh;
+  __shared__ DPShared<NW, KL, DUMMY, PACKED, LISTS> sh;
   const int part = part_of(parts, blockIdx.x), tl = blockIdx.x - parts.first[part];
   const DPLaunch& a = parts.p[part];
   if (DEGEN && a.degen[tl] == 0) return;
@@ -1564,7 +1568,7 @@ template <int NW, bool DEGEN, int KL = kMaxList, bool DUMMY = false, bool PACKED
 __global__ __launch_bounds__(NW * 64)
 __attribute__((amdgpu_waves_per_eu(DUMMY || PACKED ? 4 : (NW >= 8 ? 4 : 3))))
 void k_dp_persistent(BatchLaunch b) {
-  __shared__ DPShared<NW, KL, DUMMY, PACKED> sh;
+  __shared__ DPShared<NW, KL, DUMMY, PACKED, LISTS> sh;
   __shared__ int item_sh;
   __shared__ int bt_item[NW];  // item of each batch slot, -1: not backtracked here
   __shared__ int bt_idx[NW];   // its first minimising final pair, -1: infeasible
@@ -1895,7 +1899,7 @@ hipError_t launch_dp_waves(const DPLaunch* parts, int n_parts, hipStream_t st) {
     return hipGetLastError();
   }
   if (a.packed && a.sp.K > 32) {  // sparse scenes, long lists: packed schedules
-    if (a.cand)
+    if (a.runs)
       hipLaunchKernelGGL((k_dp<8, DEGEN, 64, false, true, false, true>), dim3(n), dim3(8 * 64), 0, st, b);
     else
       hipLaunchKernelGGL((k_dp<8, DEGEN, 64, false, true>), dim3(n), dim3(8 * 64), 0, st, b);
@@ -1960,7 +1964,7 @@ hipError_t launch_persistent_variant(const BatchLaunch& b, int n_wg, hipStream_t
     return hipGetLastError();
   }
   if (b.packed) {  // sparse scenes: packed schedules, 8 waves
-    if (b.lists)
+    if (b.runs)
       hipLaunchKernelGGL((k_dp_persistent<8, DEGEN, kMaxList, false, true, false, true>), dim3(n_wg), dim3(8 * 64), 0,
                          st, b);
     else

@@ -995,7 +995,7 @@ int stm_plan_run_lists(stm_plan* p, const int32_t* const* cand, const int32_t* c
   if (!p->ls_pairs_dev) {
     p->ls_pairs_dev = static_cast<stm::PairDev*>(
         plan_alloc(p, std::max<size_t>(1, p->pairs_host.size()) * sizeof(stm::PairDev), &rc));
-    p->ls_bad = static_cast<int32_t*>(plan_alloc(p, sizeof(int32_t), &rc));
+    p->ls_bad = static_cast<int32_t*>(plan_alloc(p, 2 * sizeof(int32_t), &rc));
     if (rc) return rc;
   }
   const hipStream_t user = static_cast<hipStream_t>(hip_stream);
@@ -1012,14 +1012,14 @@ int stm_plan_run_lists(stm_plan* p, const int32_t* const* cand, const int32_t* c
     ph[q].ccount = count[q];
     ph[q].cstride = kc;
   }
-  int32_t bad = 0;
-  STM_HIP(stm::launch_fill_i32(p->ls_bad, 1, 0, st));
+  int32_t checked[2] = {0, 0};  // error bits, and whether the lists mostly repeat
+  STM_HIP(stm::launch_fill_i32(p->ls_bad, 2, 0, st));
   if (!ph.empty())
     STM_HIP(hipMemcpyAsync(p->ls_pairs_dev, ph.data(), ph.size() * sizeof(stm::PairDev), hipMemcpyHostToDevice, st));
   STM_HIP(stm::launch_check_pair_lists(p->ls_pairs_dev, static_cast<int>(ph.size()), rows_max, kc, p->ls_bad, st));
-  STM_HIP(hipMemcpyAsync(&bad, p->ls_bad, sizeof(bad), hipMemcpyDeviceToHost, st));
+  STM_HIP(hipMemcpyAsync(checked, p->ls_bad, sizeof(checked), hipMemcpyDeviceToHost, st));
   STM_HIP(hipStreamSynchronize(st));
-  if (bad) return fail(STM_EINVAL, "candidate lists: count outside [0, kc], node outside the scene or not ascending");
+  if (checked[0]) return fail(STM_EINVAL, "candidate lists: count outside [0, kc], node outside the scene or not ascending");
 
   float* e32 = p->device ? energy32 : p->o_e32;
   double* e64 = p->device ? energy64 : (energy64 ? p->o_e64 : nullptr);
@@ -1029,7 +1029,7 @@ int stm_plan_run_lists(stm_plan* p, const int32_t* const* cand, const int32_t* c
   STM_HIP(stm::launch_fill_i32(p->counters, 3, 0, st));
   stm::BatchLaunch b = plan_launch(p, p->ls_pairs_dev, p->items_dev, p->n_items, e32, asg);
   b.sp.K = kc;
-  b.lists = 1;
+  b.runs = checked[1] > 0;
   const bool timed = p->ctx->prof;
   if (timed) STM_HIP(hipEventRecord(p->ev_k0, st));
   STM_HIP(stm::launch_dp_persistent(b, p->n_cu * p->wgs_per_cu, st));

@@ -356,8 +356,10 @@ __global__ __launch_bounds__(64) void k_scatter_fallback(const int32_t* __restri
   }
 }
 
-// Caller-given candidate lists: bad |= 1 for a count outside [0, kc], 2 for a
-// node outside [0, S), 4 for a list not strictly ascending.  One pair's lists,
+// Caller-given candidate lists: bad[0] |= 1 for a count outside [0, kc], 2 for a
+// node outside [0, S), 4 for a list not strictly ascending; bad[1] += 2 for a list
+// that holds the nodes of the list before it (of the same offset), -5 for one that
+// does not, over every sixteenth workgroup's lists.  One pair's lists of M points,
 // or (pairs given) those of pair blockIdx.y.  Bound by reading the lists: a wave
 // takes kListRows lists at a time, one entry per lane (kc <= 64), so its reads
 // are contiguous and all in flight together.  Against one thread per list and
@@ -366,13 +368,14 @@ __global__ __launch_bounds__(64) void k_scatter_fallback(const int32_t* __restri
 constexpr int kListRows = 8;
 __global__ __launch_bounds__(256) void k_check_lists(const PairDev* __restrict__ pairs,
                                                     const int32_t* __restrict__ cand,
-                                                    const int32_t* __restrict__ count, long long rows, int kc, int S,
-                                                    int32_t* __restrict__ bad) {
+                                                    const int32_t* __restrict__ count, long long rows, int M, int kc,
+                                                    int S, int32_t* __restrict__ bad) {
   if (pairs) {
     const PairDev& p = pairs[blockIdx.y];
     cand = p.cand;
     count = p.ccount;
-    rows = (long long)p.n_tau * p.m.M;
+    M = p.m.M;
+    rows = (long long)p.n_tau * M;
     S = p.s.S;
   }
   const int lane = threadIdx.x & 63;
@@ -397,6 +400,17 @@ __global__ __launch_bounds__(256) void k_check_lists(const PairDev* __restrict__
     }
   }
   if (b) atomicOr(bad, b);
+  if (blockIdx.x % 16 == 0) {
+    int vote = 0, j = static_cast<int>(r0 % M);  // point of row r0 + q
+#pragma unroll
+    for (int q = 1; q < kListRows; ++q) {
+      j = j + 1 < M ? j + 1 : 0;
+      if (r0 + q >= rows || j == 0) continue;
+      const bool same = n[q] == n[q - 1] && __all(lane >= n[q] || v[q] == v[q - 1]);
+      vote += same ? 2 : -5;
+    }
+    if (lane == 0 && vote != 0) atomicAdd(bad + 1, vote);
+  }
 }
 
 inline int blocks(long long n, int per) { return static_cast<int>((n + per - 1) / per); }
@@ -458,11 +472,11 @@ hipError_t launch_scatter_fallback(const int32_t* taus, int n, int tau0, int M, 
   return hipGetLastError();
 }
 
-hipError_t launch_check_lists(const int32_t* cand, const int32_t* count, long long rows, int kc, int S, int32_t* bad,
-                              hipStream_t st) {
+hipError_t launch_check_lists(const int32_t* cand, const int32_t* count, long long rows, int M, int kc, int S,
+                              int32_t* bad, hipStream_t st) {
   if (rows <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_check_lists, dim3(blocks(rows, 4 * kListRows)), dim3(256), 0, st, nullptr, cand, count, rows, kc,
-                     S, bad);
+  hipLaunchKernelGGL(k_check_lists, dim3(blocks(rows, 4 * kListRows)), dim3(256), 0, st, nullptr, cand, count, rows, M,
+                     kc, S, bad);
   return hipGetLastError();
 }
 
@@ -471,7 +485,7 @@ hipError_t launch_check_pair_lists(const PairDev* pairs, int n_pairs, long long 
   for (int p = 0; rows_max > 0 && p < n_pairs; p += 65535) {  // the grid's limit in y
     const int n = n_pairs - p < 65535 ? n_pairs - p : 65535;
     hipLaunchKernelGGL(k_check_lists, dim3(blocks(rows_max, 4 * kListRows), n), dim3(256), 0, st, pairs + p, nullptr,
-                       nullptr, 0ll, kc, 0, bad);
+                       nullptr, 0ll, 0, kc, 0, bad);
   }
   return hipGetLastError();
 }

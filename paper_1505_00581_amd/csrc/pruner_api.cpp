@@ -637,14 +637,16 @@ int stm_match_lists(stm_ctx* ctx, const stm_points* model, const stm_points* sce
   const long long rows = (long long)n_tau * M;
   const int32_t* d_cand = cand;
   const int32_t* d_cnt = count;
+  long long repeats = 0;  // > 0: more than five of seven lists repeat the one before them
   if (pr.device) {
-    if ((rc = grow(ctx, ctx->val, sizeof(int32_t), pr.st))) return rc;
-    STM_HIP(stm::launch_fill_i32(static_cast<int32_t*>(ctx->val.p), 1, 0, pr.st));
-    STM_HIP(stm::launch_check_lists(cand, count, rows, kc, S, static_cast<int32_t*>(ctx->val.p), pr.st));
-    int32_t bad = 0;
-    STM_HIP(hipMemcpyAsync(&bad, ctx->val.p, sizeof(bad), hipMemcpyDeviceToHost, pr.st));
+    if ((rc = grow(ctx, ctx->val, 2 * sizeof(int32_t), pr.st))) return rc;
+    STM_HIP(stm::launch_fill_i32(static_cast<int32_t*>(ctx->val.p), 2, 0, pr.st));
+    STM_HIP(stm::launch_check_lists(cand, count, rows, M, kc, S, static_cast<int32_t*>(ctx->val.p), pr.st));
+    int32_t checked[2] = {0, 0};
+    STM_HIP(hipMemcpyAsync(checked, ctx->val.p, sizeof(checked), hipMemcpyDeviceToHost, pr.st));
     STM_HIP(hipStreamSynchronize(pr.st));
-    if (bad) return fail(STM_EINVAL, "candidate lists: count outside [0, kc], node outside the scene or not ascending");
+    repeats = checked[1];
+    if (checked[0]) return fail(STM_EINVAL, "candidate lists: count outside [0, kc], node outside the scene or not ascending");
   } else {
     for (long long r = 0; r < rows; ++r) {
       const int n = count[r];
@@ -654,6 +656,8 @@ int stm_match_lists(stm_ctx* ctx, const stm_points* model, const stm_points* sce
         if (v < 0 || v >= S || (a > 0 && v <= cand[r * kc + a - 1]))
           return fail(STM_EINVAL, "candidate lists must hold ascending scene nodes");
       }
+      if (r % M != 0)
+        repeats += n == count[r - 1] && std::equal(cand + r * kc, cand + r * kc + n, cand + (r - 1) * kc) ? 2 : -5;
     }
     if ((rc = grow(ctx, ctx->o_cand, (size_t)rows * kc * sizeof(int32_t), pr.st))) return rc;
     if ((rc = grow(ctx, ctx->o_cnt, (size_t)rows * sizeof(int32_t), pr.st))) return rc;
@@ -673,6 +677,7 @@ int stm_match_lists(stm_ctx* ctx, const stm_points* model, const stm_points* sce
   stm::DPLaunch b = dp_base(ctx, pr, params);
   b.sp.K = kc;
   b.cstride = kc;
+  b.runs = repeats > 0;
   for (int c0 = 0; c0 < n_tau; c0 += chunk) {
     const int nc = std::min(chunk, n_tau - c0);
     b.cand = d_cand + (size_t)c0 * M * kc;

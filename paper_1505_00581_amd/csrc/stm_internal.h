@@ -237,6 +237,7 @@ struct DPLaunch {
   // packed schedules (sparse scenes, long lists; no dummies): every cell of a
   // step on its own lane, chunk after chunk
   int32_t packed = 0;
+  int32_t runs = 0;  // packed, explicit lists: more than five of seven repeat the one before them
 };
 // Several models' matchings in one launch, part after part (same scene,
 // parameters and variant): the last workgroups of one part leave no CU idle
@@ -299,7 +300,7 @@ struct BatchLaunch {
   int32_t dummy = 0;    // dummy assignments (Eq. 2) enabled
   float cw = 0.f;       // lambda1 * W^d in FP32
   int32_t packed = 0;   // packed schedules (sparse scenes; no dummies)
-  int32_t lists = 0;    // every pair has explicit candidate lists
+  int32_t runs = 0;     // packed: explicit lists of which more than five of seven repeat the one before them
   float* e32;           // [rows]
   int32_t* assign;      // [sum over pairs of n_tau * M]
   int32_t waves;        // 4, 8 or 16 waves per workgroup
@@ -475,9 +476,11 @@ struct PrunerInfer {
   float* scores;        // [n_groups][64], nullable
 };
 hipError_t launch_pruner_infer(const PrunerInfer& q, hipStream_t st);
-// Checks caller-given lists [rows][kc] with counts [rows]; ORs error bits into *bad.
-hipError_t launch_check_lists(const int32_t* cand, const int32_t* count, long long rows, int kc, int S, int32_t* bad,
-                              hipStream_t st);
+// Checks caller-given lists [rows][kc] with counts [rows] of an M-point model;
+// ORs error bits into bad[0] and leaves in bad[1] whether more than five of seven
+// lists repeat the one before them (> 0).
+hipError_t launch_check_lists(const int32_t* cand, const int32_t* count, long long rows, int M, int kc, int S,
+                              int32_t* bad, hipStream_t st);
 // The lists of every pair (at most rows_max each, cand and ccount set).
 hipError_t launch_check_pair_lists(const PairDev* pairs, int n_pairs, long long rows_max, int kc, int32_t* bad,
                                    hipStream_t st);
