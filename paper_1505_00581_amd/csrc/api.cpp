@@ -204,11 +204,7 @@ int prepare(stm_ctx* ctx, const stm_points* m, const stm_points* s, const stm_pa
   if (out.device) {
     // what is queued behind the validation runs while the host waits for it; it
     // reads the inputs within their bounds whatever they hold
-    rc = early.run ? early.run(early.self, out) : STM_OK;
-    if (rc) {
-      (void)hipStreamSynchronize(out.st);
-      return rc;
-    }
+    if (early.run && early.run(early.self, out) != STM_OK) err().clear();
     STM_HIP(hipEventSynchronize(ctx->ev_val));
     const int32_t bits = ctx->val_host[0];
     if (bits) {
@@ -422,17 +418,24 @@ int stm_match(stm_ctx* ctx, const stm_points* model, const stm_points* scene,
     if ((rc = grow(ctx, ctx->U, (size_t)q.m.M * q.s.S * sizeof(float), q.st))) return rc;
     part.theta = static_cast<float2*>(ctx->theta.p);
     part.U = static_cast<float*>(ctx->U.p);
+    if ((rc = match_tables(ctx, q, part.theta, part.U, nullptr))) return rc;
     part.tables = true;
-    return match_tables(ctx, q, part.theta, part.U, nullptr);
+    return STM_OK;
   };
-  const bool work = tau_end > tau_begin && energy32 && assign;
+  // (nothing early for a call that is empty or refused whatever the model's span)
+  const bool work = tau_begin >= 0 && tau_end > tau_begin && scene && tau_end <= scene->n_frames && energy32 && assign;
   int rc = work ? prepare(ctx, model, scene, params, hip_stream, pr, nullptr, tables)
                 : prepare(ctx, model, scene, params, hip_stream, pr);
   if (rc) return rc;
-  if ((rc = check_range(pr, tau_begin, tau_end))) return rc;
+  // a refusal from here on waits for what is queued, which reads the caller's arrays
+  const auto refuse = [&](int code) {
+    if (pr.device) (void)hipStreamSynchronize(pr.st);
+    return code;
+  };
+  if ((rc = check_range(pr, tau_begin, tau_end))) return refuse(rc);
   const int n_tau = tau_end - tau_begin;
   if (n_tau == 0) return STM_OK;
-  if (!energy32 || !assign) return fail(STM_EINVAL, "energy32 and assign are required");
+  if (!energy32 || !assign) return refuse(fail(STM_EINVAL, "energy32 and assign are required"));
   if (!part.tables && (rc = tables(pr))) return rc;
   const int M = pr.m.M;
   const hipStream_t st = pr.st;
@@ -462,9 +465,9 @@ int stm_match(stm_ctx* ctx, const stm_points* model, const stm_points* scene,
   MatchScratch sc;
   const size_t per_tau = vt_bytes_per_offset(M, params);
   sc.chunk = static_cast<int>(std::min<size_t>(n_tau, std::max<size_t>(1, ctx->vt_chunk_bytes / per_tau)));
-  if ((rc = grow(ctx, ctx->vt, per_tau * sc.chunk, st))) return rc;
-  if ((rc = grow(ctx, ctx->last2, (size_t)sc.chunk * sizeof(int2), st))) return rc;
-  if ((rc = grow(ctx, ctx->degen, (size_t)sc.chunk * sizeof(int32_t), st))) return rc;
+  if ((rc = grow(ctx, ctx->vt, per_tau * sc.chunk, st))) return refuse(rc);
+  if ((rc = grow(ctx, ctx->last2, (size_t)sc.chunk * sizeof(int2), st))) return refuse(rc);
+  if ((rc = grow(ctx, ctx->degen, (size_t)sc.chunk * sizeof(int32_t), st))) return refuse(rc);
   sc.vt = static_cast<float*>(ctx->vt.p);
   sc.last2 = static_cast<int2*>(ctx->last2.p);
   sc.degen = static_cast<int32_t*>(ctx->degen.p);

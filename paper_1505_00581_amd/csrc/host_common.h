@@ -112,7 +112,7 @@ struct FixedPrep {
 
 // A callable held by reference (nothing to allocate at a C entry).
 struct EarlyWork {
-  int (*run)(const void*, const Prepared&) = nullptr;
+  int (*run)(const void*, const Prepared&) = nullptr;  // STM_OK: queued
   const void* self = nullptr;
   EarlyWork() = default;
   template <class F>
@@ -122,7 +122,9 @@ struct EarlyWork {
 
 // The inputs of a call checked and on the device.  early (device pointers):
 // queues work that needs the inputs but not their validation, which the host
-// waits for meanwhile; not called for host pointers.
+// waits for meanwhile; not called for host pointers.  What early cannot queue is
+// no error here: the caller, who keeps whether it was queued, does it in its own
+// place, so that an invalid input is reported before, say, a lack of memory.
 int prepare(stm_ctx* ctx, const stm_points* m, const stm_points* s, const stm_params* p,
             void* hip_stream, Prepared& out, const FixedPrep* fixed = nullptr,
             EarlyWork early = {});

@@ -39,15 +39,18 @@ int check_pruner(stm_pruner* P) {
 int pair_inputs(stm_pruner* P, const stm_points* m, const stm_points* s, const stm_params* prm, void* stream,
                 Prepared& pr) {
   stm_ctx* ctx = P->ctx;
+  bool queued = false;
   const auto table = [&](const Prepared& q) {
     if (m->dim != P->dim) return STM_OK;  // refused below
-    const int rc = grow(ctx, ctx->U, (size_t)q.m.M * q.s.S * sizeof(float), q.st);
-    return rc ? rc : unary_table(ctx, q, static_cast<float*>(ctx->U.p));
+    int rc = grow(ctx, ctx->U, (size_t)q.m.M * q.s.S * sizeof(float), q.st);
+    if (!rc) rc = unary_table(ctx, q, static_cast<float*>(ctx->U.p));
+    queued = !rc;
+    return rc;
   };
   int rc = prepare(ctx, m, s, prm, stream, pr, nullptr, table);
   if (rc) return rc;
   if (m->dim != P->dim) return fail(STM_EINVAL, "descriptor dimension differs from the pruner's");
-  return pr.device ? STM_OK : table(pr);
+  return queued ? STM_OK : table(pr);
 }
 
 // Host group list (tau, i) checked against the pair and staged on the device.
