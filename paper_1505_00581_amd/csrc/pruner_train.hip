@@ -15,6 +15,8 @@
 //    and dZ2 handed from layer to layer in LDS.
 #include <math.h>
 
+#include <algorithm>
+
 #include "stm_internal.h"
 
 namespace stm {
@@ -329,11 +331,12 @@ __global__ __launch_bounds__(256, 2) void k_train_rows(PrunerTrain t) {
 // latency of the gathered rows against 32 matrix instructions a tile (1,024
 // groups, D = 162: 106 us, 51 TFLOP/s; 412 us as scalar products over all rows).
 constexpr int kGradCols = 64, kGradRows = 32;
+constexpr int kChunkGroups = 8;  // groups of the rows' largest chunk
 constexpr int kZLd = H + 32, kXLd = kGradCols + 32;  // 32 mod 64 banks: the lane halves read different banks
 
 struct GradPlan {
   int tiles2, tilesB, tilesA;  // column tiles of the three products
-  int chunk;                   // rows (groups) of a chunk, a multiple of kGradRows
+  int chunk;                   // rows (groups) of a chunk, a multiple of kRows
   int nch, ncha;               // chunks over the rows and over the groups
   float *part2, *partB, *partA;
 };
@@ -504,14 +507,18 @@ __global__ __launch_bounds__(256) void k_train_reduce(PrunerTrain t, GradPlan p,
 
 inline int ceil_div(long long a, long long b) { return static_cast<int>((a + b - 1) / b); }
 
-// Chunks of 64 ceil(G / 128) rows: at most 128 partial sums per weight, and
-// about five column tiles times 128 chunks of workgroups.
+// Chunks of 64 ceil(G / 128) rows, about five column tiles times 128 chunks of
+// workgroups, but of at most 512 rows: a longer chain of FP32 additions would only
+// cost accuracy (65,536 equal groups: 0.33 of the rounding bound of these sums,
+// 2.2 with chunks of 32,768 rows), and the shorter one costs no more than 2% (8,192
+// groups, D = 162: 1.80 ms against 1.76).  Above 524,280 groups the grid's limit
+// of chunks makes them longer again.
 GradPlan grad_plan(int G, int D, float* part) {
   GradPlan p;
   p.tiles2 = H / kGradCols;
   p.tilesB = ceil_div(D + 8, kGradCols);
   p.tilesA = ceil_div(D, kGradCols);
-  p.chunk = kRows * ceil_div(G, 128);
+  p.chunk = kRows * std::max(std::min(ceil_div(G, 128), kChunkGroups), ceil_div(G, 65535));
   p.nch = ceil_div((long long)G * kRows, p.chunk);
   p.ncha = ceil_div(G, p.chunk);
   p.part2 = part;
