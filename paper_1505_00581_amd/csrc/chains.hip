@@ -87,6 +87,26 @@ namespace {
 // Unary tables of the chains of one launch (a single chain may exceed it).
 constexpr size_t kChainTableBytes = size_t(1) << 30;
 
+// Offsets of a chunk: at most `most`, those whose value tables fit.  Chunks of
+// `most` can leave a last one of a few offsets, whose matchings leave CUs idle,
+// so the cheaper of that cut and of equal chunks is taken, by rounds of two
+// matchings to a CU, a last one of one to a CU counting 0.6 (a matching alone on
+// its CU against two).  Lists of 64, full / equal / chosen cut in ms: 3 chains of
+// 100 points x 1000 offsets 17.4 / 16.0 / 15.9 (17.0 one chain a launch), 3 of 68 x
+// 1400 14.6 / 15.7 / 14.5 (16.3), 4 of 50 x 1400 14.6 / 14.0 / 14.0 (16.3).
+int even_chunk(int n_tau, int chains, int most) {
+  const auto rounds = [&](int offsets) {
+    constexpr int kRound = 2 * stm::kCUs;
+    const long long n = (long long)offsets * chains, rest = n % kRound;
+    const double last = rest > stm::kCUs ? 0.6 + 0.4 * (rest - stm::kCUs) / stm::kCUs : rest > 0 ? 0.6 : 0.0;
+    return static_cast<double>(n / kRound) + last;
+  };
+  const int full = n_tau / most, n = (n_tau + most - 1) / most, even = (n_tau + n - 1) / n;
+  const double cut_full = full * rounds(most) + rounds(n_tau - full * most);
+  const double cut_even = (n - 1) * rounds(even) + rounds(n_tau - (n - 1) * even);
+  return cut_even < cut_full ? even : most;
+}
+
 template <class T>
 int to_device(stm_ctx* ctx, DevBuf& b, const T* src, size_t count, bool src_device, hipStream_t st) {
   int rc = grow(ctx, b, std::max<size_t>(count, 1) * sizeof(T), st);
@@ -195,8 +215,9 @@ extern "C" int stm_match_chains(stm_ctx* ctx, const stm_points* model, const flo
   }
 
   // every chain by the exact matching, at its own offsets, several chains in one
-  // launch: 1387 matchings on 256 CUs end with a round that fills 42% of them,
-  // three chains' 4161 with one that fills 25% of one in seventeen
+  // launch: one chain after the other, each launch ends with a round of matchings
+  // that fills the chip in part (models of 50 points, 1400 offsets, lists of 64:
+  // four chains 16.3 ms one by one, 14.0 together)
   if ((rc = grow(ctx, ctx->ch_e32, (size_t)nc * n_tau * sizeof(float), st))) return rc;
   if ((rc = grow(ctx, ctx->ch_e64, (size_t)nc * n_tau * sizeof(double), st))) return rc;
   if ((rc = grow(ctx, ctx->ch_eu, (size_t)nc * n_tau * sizeof(double), st))) return rc;
@@ -240,7 +261,8 @@ extern "C" int stm_match_chains(stm_ctx* ctx, const stm_points* model, const flo
     const int np = q1 - q0;
     MatchScratch ms;
     if ((rc = grow(ctx, ctx->U, rows * S * sizeof(float), st))) return rc;
-    ms.chunk = static_cast<int>(std::min<size_t>(n_tau, std::max<size_t>(1, ctx->vt_chunk_bytes / per_tau)));
+    ms.chunk = even_chunk(n_tau, np,
+                          static_cast<int>(std::min<size_t>(n_tau, std::max<size_t>(1, ctx->vt_chunk_bytes / per_tau))));
     if ((rc = grow(ctx, ctx->vt, per_tau * ms.chunk, st))) return rc;
     if ((rc = grow(ctx, ctx->last2, (size_t)np * ms.chunk * sizeof(int2), st))) return rc;
     if ((rc = grow(ctx, ctx->degen, (size_t)np * ms.chunk * sizeof(int32_t), st))) return rc;

@@ -1855,8 +1855,6 @@ __global__ __launch_bounds__(W * 64) void k_rescore_batch(const PairDev* __restr
 //     15 working waves       617   1007
 // The arithmetic of every cell is the same, so the results do not depend on the
 // variant.
-constexpr int kCUs = 256;
-
 DPParts dp_parts(const DPLaunch* a, int n_parts, int& n) {
   DPParts b;
   b.n = n_parts;

@@ -239,6 +239,7 @@ struct DPLaunch {
   int32_t packed = 0;
   int32_t runs = 0;  // packed, explicit lists: more than five of seven repeat the one before them
 };
+constexpr int kCUs = 256;  // compute units of the chip
 // Several models' matchings in one launch, part after part (same scene,
 // parameters and variant): the last workgroups of one part leave no CU idle
 // while another part has matchings left.
