@@ -582,10 +582,10 @@ __global__ __launch_bounds__(kFusedThreads) void k_trellis_fused(TrellisRun a) {
   for (int32_t q = tid; q < n_pairs; q += kFusedThreads) C[q] = cb.Ct[x0 + q];
 
   // the thread's cells and step 1: V_1(r, c) = l1 (U_0(r) + U_1(c)) + l2 |dt|.
-  // Packed in 16 bits each (at most 8192 cells, 40.8k pairs and 32,767 nodes): the
-  // places of the first predecessor's cell (k, r) in VA and pair (k, c) in C, the
-  // cell's own place in VA, the number of predecessors.  Cells outside the part's
-  // columns have column -1.
+  // Packed in 16 bits each (at most 8192 cells and 40.8k pairs): the places of
+  // the first predecessor's cell (k, r) in VA and pair (k, c) in C, the cell's own
+  // place in VA, the number of predecessors.  Cells outside the part's columns
+  // have column -1.
   uint32_t at[kFusedSlots], me[kFusedSlots];
   int32_t cc[kFusedSlots], dt[kFusedSlots];
   float arc[kFusedSlots], nv[kFusedSlots];

@@ -367,8 +367,7 @@ int stm_trellis_create(stm_ctx* ctx, const stm_points* models, int32_t n_models,
   TR_HIP(hipStreamSynchronize(st));
   p->Q = ends[0];
   p->QC = ends[1];
-  p->fused = !(params->flags & STM_TRELLIS_STEPWISE) && n <= 32767 &&
-             stm::trellis_fits_fused(p->Q, p->QC, p->m_max);
+  p->fused = !(params->flags & STM_TRELLIS_STEPWISE) && stm::trellis_fits_fused(p->Q, p->QC, p->m_max);
   // Tiling of the step launches (us per run of M = 30 models on the 754-node
   // video or its first 200 nodes, staged cells / 8 rows / 4 rows by 64 columns):
   //  * launches of few workgroups wait for the staging, whatever the width: 4 x
