@@ -196,20 +196,18 @@ void cut_parts(const std::vector<int32_t>& pb, const std::vector<int32_t>& plo, 
                std::vector<int2>& own, std::vector<int32_t>& lim) {
   const int32_t n = static_cast<int32_t>(plo.size());
   const int depth = std::max(1, m_max - 1);  // steps 1..M-1
-  const auto limits = [&](int32_t c0) {
-    std::vector<int32_t> l(depth);
-    for (int d = 0; d < depth; ++d) l[d] = d == 0 ? c0 : plo[l[d - 1]];
-    return l;
-  };
+  std::vector<int32_t> l(depth);
   // cuts with at most `budget` cells a part; false when that takes too many parts
   const auto cut = [&](long long budget) {
     own.clear();
     lim.clear();
     for (int32_t c0 = 0; c0 < n;) {
       if ((int)own.size() == n_parts) return false;
-      const std::vector<int32_t> l = limits(c0);
       long long before = 0;
-      for (int32_t x : l) before += pb[x];
+      for (int d = 0; d < depth; ++d) {
+        l[d] = d == 0 ? c0 : plo[l[d - 1]];
+        before += pb[l[d]];
+      }
       int32_t c1 = c0 + 1;
       while (c1 < n && (long long)depth * pb[c1 + 1] - before <= budget) ++c1;
       own.push_back(make_int2(c0, c1));
@@ -386,10 +384,11 @@ int stm_trellis_create(stm_ctx* ctx, const stm_points* models, int32_t n_models,
   //    step kernel has the registers to issue a chunk's reads in one round).
   constexpr long long kFewTiles = 1024, kFewWide = 1280;
   using stm::TrellisTiling;
-  const std::vector<stm::TrellisTile> tall = make_wide_tiles(slo, shi, plo, phi, 8);
-  std::vector<stm::TrellisTile> tiles = make_wide_tiles(slo, shi, plo, phi, 4);
-  const long long n_tall = (long long)tall.size() * n_models, n_flat = (long long)tiles.size() * n_models;
+  std::vector<stm::TrellisTile> tiles = make_wide_tiles(slo, shi, plo, phi, 4), tall;
+  const long long n_flat = (long long)tiles.size() * n_models;
   const bool full_rows = p->Q >= 128LL * n;
+  if (n_flat >= kFewWide && p->Q >= 64LL * n) tall = make_wide_tiles(slo, shi, plo, phi, 8);
+  const long long n_tall = (long long)tall.size() * n_models;
   if (n_flat < kFewWide) {
     p->tiling = TrellisTiling::kWide4;
   } else if (full_rows || (p->Q >= 64LL * n && n_tall < 4096)) {
@@ -447,19 +446,19 @@ int stm_trellis_create(stm_ctx* ctx, const stm_points* models, int32_t n_models,
   TR_HIP(hipStreamSynchronize(st));
   p->degen = flag != 0;
 
+  std::vector<int32_t> cols_host;  // (copied from until the last synchronisation)
   if (p->fused) {
     // the band by column and its parts: one workgroup per part and model, as many
     // as the chip has CUs (more parts than kMaxParts recompute more than they gain)
     constexpr int kMaxParts = 16;
     const long long T = stm::pair_limit(p->sp);
     std::vector<int32_t> pb(n + 1, 0), qb(n + 1, 0), qpl(n);
-    for (int32_t c = 0; c < n; ++c) {
+    for (int32_t c = 0, first = 0, end = 0; c < n; ++c) {  // two-step predecessors [first, end), frames ascend
       pb[c + 1] = pb[c] + std::max(0, phi[c] - plo[c]);
-      const auto at = [&](long long t) {  // first node with frame >= t
-        return static_cast<int32_t>(std::lower_bound(th.begin(), th.end(), t) - th.begin());
-      };
-      qpl[c] = T > 0 ? at(th[c] - 2 * T + 2) : 0;
-      qb[c + 1] = qb[c] + std::max(0, at((long long)th[c] - 1) - qpl[c]);
+      while (T > 0 && first < n && th[first] < th[c] - 2 * T + 2) ++first;
+      while (end < n && th[end] < (long long)th[c] - 1) ++end;
+      qpl[c] = first;
+      qb[c + 1] = qb[c] + std::max(0, end - first);
     }
     if (pb[n] != p->Q || qb[n] != p->QC) return bail(fail(STM_EHIP, "band by row and by column differ"));
     int n_cu = 0;
@@ -467,35 +466,32 @@ int stm_trellis_create(stm_ctx* ctx, const stm_points* models, int32_t n_models,
     std::vector<int2> own;
     std::vector<int32_t> lim;
     cut_parts(pb, plo, p->m_max, std::max(1, std::min(kMaxParts, n_cu / n_models)), own, lim);
-    std::vector<int32_t> row;
-    row.reserve(p->Q);
-    for (int32_t r = 0; r < n; ++r) row.insert(row.end(), std::max(0, shi[r] - slo[r]), r);
-    int32_t *d_pb, *d_qb, *d_qpl, *d_lim, *d_row;
-    int2* d_own;
-    TR_ALLOC(d_pb, int32_t, (size_t)n + 1);
-    TR_ALLOC(d_qb, int32_t, (size_t)n + 1);
-    TR_ALLOC(d_qpl, int32_t, n);
-    TR_ALLOC(d_row, int32_t, row.size());
-    TR_ALLOC(d_own, int2, own.size());
-    TR_ALLOC(d_lim, int32_t, lim.size());
-    TR_ALLOC(p->cols.At, float, std::max(1LL, p->Q));
-    TR_ALLOC(p->cols.Ct, float, std::max(1LL, p->QC));
-    TR_HIP(hipMemcpyAsync(d_pb, pb.data(), sizeof(int32_t) * pb.size(), hipMemcpyHostToDevice, st));
-    TR_HIP(hipMemcpyAsync(d_qb, qb.data(), sizeof(int32_t) * qb.size(), hipMemcpyHostToDevice, st));
-    TR_HIP(hipMemcpyAsync(d_qpl, qpl.data(), sizeof(int32_t) * qpl.size(), hipMemcpyHostToDevice, st));
-    TR_HIP(hipMemcpyAsync(d_own, own.data(), sizeof(int2) * own.size(), hipMemcpyHostToDevice, st));
-    TR_HIP(hipMemcpyAsync(d_lim, lim.data(), sizeof(int32_t) * lim.size(), hipMemcpyHostToDevice, st));
-    TR_HIP(hipMemcpyAsync(d_row, row.data(), sizeof(int32_t) * row.size(), hipMemcpyHostToDevice, st));
-    p->cols.row = d_row;
-    p->cols.pb = d_pb;
-    p->cols.qb = d_qb;
-    p->cols.qp_lo = d_qpl;
-    p->cols.own = d_own;
-    p->cols.lim = d_lim;
-    p->cols.parts = static_cast<int32_t>(own.size());
-    p->cols.lim_stride = static_cast<int32_t>(lim.size() / own.size());
+    // one allocation and one copy of all of them (a call of its own each took 0.1
+    // ms of a creation of 0.4); then the direction tables
+    const size_t n_own = own.size();
+    cols_host.reserve(2 * n_own + 3 * (size_t)n + 2 + lim.size() + p->Q);
+    for (const int2& o : own) cols_host.insert(cols_host.end(), {o.x, o.y});
+    const auto put = [&](const std::vector<int32_t>& v) {
+      const size_t at = cols_host.size();
+      cols_host.insert(cols_host.end(), v.begin(), v.end());
+      return at;
+    };
+    const size_t at_pb = put(pb), at_qb = put(qb), at_qpl = put(qpl), at_lim = put(lim), at_row = cols_host.size();
+    for (int32_t r = 0; r < n; ++r) cols_host.insert(cols_host.end(), std::max(0, shi[r] - slo[r]), r);
+    int32_t* d = nullptr;
+    TR_ALLOC(d, int32_t, cols_host.size() + p->Q + p->QC);
+    TR_HIP(hipMemcpyAsync(d, cols_host.data(), sizeof(int32_t) * cols_host.size(), hipMemcpyHostToDevice, st));
+    p->cols.own = reinterpret_cast<const int2*>(d);
+    p->cols.pb = d + at_pb;
+    p->cols.qb = d + at_qb;
+    p->cols.qp_lo = d + at_qpl;
+    p->cols.lim = d + at_lim;
+    p->cols.row = d + at_row;
+    p->cols.At = reinterpret_cast<float*>(d + cols_host.size());
+    p->cols.Ct = p->cols.At + p->Q;
+    p->cols.parts = static_cast<int32_t>(n_own);
+    p->cols.lim_stride = static_cast<int32_t>(lim.size() / n_own);
     TR_HIP(stm::launch_trellis_columns(b, p->cols, n, st));
-    TR_HIP(hipStreamSynchronize(st));  // the host arrays above go out of scope
   }
 
   // unary tables, value tables, the model table and the re-score's pair table
