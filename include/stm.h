@@ -610,9 +610,12 @@ STM_API int stm_plan_run_pruned(stm_plan* plan, stm_pruner* pruner, int32_t topk
 
 /* ---- tuning ----------------------------------------------------------------- */
 
-/* Waves per workgroup of the recursion kernel (one workgroup per matching):
- * 4, 8 or 16; 0 restores the default (8, or 16 where a call has at most one
- * matching per CU).  Results do not depend on it. */
+/* Waves per workgroup of the recursion kernel (one workgroup per matching) where
+ * lists may hold more than 32 candidates and take no variant of their own (dummy
+ * assignments, unsigned angles and sparse scenes run 8 waves): 4, 8 or 16; 0
+ * restores the default (8, or 16 where a call has at most one matching per CU).
+ * Shorter lists take 1 to 13 waves by the number of matchings, whatever is set.
+ * Results do not depend on it. */
 STM_API int stm_set_dp_waves(stm_ctx* ctx, int waves);
 
 /* ---- kernel timing for benchmarks -------------------------------------------- */

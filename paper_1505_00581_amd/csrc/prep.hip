@@ -276,7 +276,9 @@ hipError_t launch_unary_f32(const ModelView& m, const SceneView& s, float* U, hi
   if (s.dim > kUnaryMaxDim) return hipErrorInvalidValue;
   // Few tiles (a short scene, a block of one): 16 x 16 distances per workgroup
   // and 64 dimensions at a time, since the chain of tiles bounds it, not the
-  // arithmetic.  Otherwise the fewest row tiles times (R + 1): the arithmetic
+  // arithmetic.  us small / large by tiles of the large kind, 75 rows at 162
+  // dimensions: 63 9.5 / 23.2, 125 14.1 / 23.8, 188 19.4 / 24.6, 250 24.5 / 25.6,
+  // 500 45.5 / 31.6; at 16 dimensions 125 6.2 / 7.0, 188 8.2 / 7.4.  Otherwise the fewest row tiles times (R + 1): the arithmetic
   // of a tile grows with R, its reads of the scene do not.
   const auto blocks = [&](int rows, int pts) { return (long long)((m.M + rows - 1) / rows) * ((s.S + pts - 1) / pts); };
   int best = 5;

@@ -396,7 +396,8 @@ void k_trellis_step(TrellisRun a, int32_t i) {
 // up to 2.3 ms.  Eight C values ahead instead of four: 35.4 and 1.31 ms.
 template <bool DEGEN, int R, int NW>
 __global__ __launch_bounds__(NW * 64) void k_trellis_wide(TrellisRun a, int32_t i) {
-  // per wave: V and A of 64 predecessors of the R rows; at the end its minima
+  // per wave: V and A of 64 predecessors of the R rows; at the end, behind a barrier,
+  // the minima of all waves
   __shared__ __align__(16) float stage[NW][64][2 * R];
   const TrellisModel md = a.models[blockIdx.y];
   const int32_t M = md.m.M;
@@ -502,7 +503,7 @@ __global__ __launch_bounds__(NW * 64) void k_trellis_wide(TrellisRun a, int32_t 
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
   }
-  float* part = &stage[0][0][0];  // [NW][R][64]: each wave's own rows hold its minima
+  float* part = &stage[0][0][0];  // [NW][R][64]
   static_assert(sizeof(stage) >= sizeof(float) * NW * R * 64, "minima in the staging rows");
   __syncthreads();
 #pragma unroll

@@ -371,7 +371,9 @@ int stm_trellis_create(stm_ctx* ctx, const stm_points* models, int32_t n_models,
   //  * launches of few workgroups wait for the staging, whatever the width: 4 x
   //    64 tiles split the predecessors over 8 waves (1 model, no limit 3710 /
   //    3842 / 1270; T = 20 456 / 629 / 259; 8 models, 200 nodes, T = 40 721 / 868
-  //    / 503);
+  //    / 503).  Blocks of 200 to 6000 nodes with rows of 4 to 39 cells, 4 x 64 by
+  //    staged: 0.56 to 0.76 at 400 tiles a launch, 0.62 to 0.93 at 800, 0.87 to
+  //    1.20 at 1500, 0.9 to 1.6 at 3000;
   //  * rows of 128 and more successors fill the 64 columns: 36225 / 34310 / 39067
   //    (50 models, no limit), 9766 / 8191 / 6592 (8 models, which still want the
   //    shorter tiles); rows of 64 only while the chip is not full (200 nodes, 50
