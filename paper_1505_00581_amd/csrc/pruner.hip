@@ -359,7 +359,8 @@ __global__ __launch_bounds__(64) void k_scatter_fallback(const int32_t* __restri
 // Caller-given candidate lists: bad[0] |= 1 for a count outside [0, kc], 2 for a
 // node outside [0, S), 4 for a list not strictly ascending; bad[1] += 2 for a list
 // that holds the nodes of the list before it (of the same offset), -5 for one that
-// does not, over every sixteenth workgroup's lists.  One pair's lists of M points,
+// does not, over the lists of at most 512 workgroups spread over the launch (one
+// addition a wave: over a sixteenth of the workgroups they took 50 us below).  One pair's lists of M points,
 // or (pairs given) those of pair blockIdx.y.  Bound by reading the lists: a wave
 // takes kListRows lists at a time, one entry per lane (kc <= 64), so its reads
 // are contiguous and all in flight together.  Against one thread per list and
@@ -400,7 +401,8 @@ __global__ __launch_bounds__(256) void k_check_lists(const PairDev* __restrict__
     }
   }
   if (b) atomicOr(bad, b);
-  if (blockIdx.x % 16 == 0) {
+  const uint32_t every = max(1u, gridDim.x * gridDim.y / 256);
+  if ((blockIdx.y * gridDim.x + blockIdx.x) % every == 0) {
     int vote = 0, j = static_cast<int>(r0 % M);  // point of row r0 + q
 #pragma unroll
     for (int q = 1; q < kListRows; ++q) {
