@@ -1046,7 +1046,7 @@ __device__ __forceinline__ DPResult dp_forward(DPShared<NW, KL, DUMMY, PACKED, L
 // meanwhile (at step i the ring of four holds lists i - 1 .. i + 1 in use).  Every
 // term, minimum and sum is the one dp_forward takes.  The second buffers cost 64-slot
 // lists a workgroup per CU, so those stay with dp_forward.  20 points, lists of
-// 16, 40 matchings: 53 us, 79 with four waves and two barriers, 146 with one
+// 16, 70 matchings: 53 us, 79 with four waves and two barriers, 146 with one
 // wave.
 template <int NW, int KL>
 struct FewShared {

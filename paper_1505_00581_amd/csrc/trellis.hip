@@ -389,7 +389,8 @@ void k_trellis_step(TrellisRun a, int32_t i) {
 // predecessors at once and holds them in LDS rows of its own, read back as
 // broadcasts; a lane reads one C(k, c) for its R cells.  No barrier but the one
 // before the waves' minima meet.  8 rows by 4 waves is bound by the VALU (50 models on
-// the whole video without a closeness limit 34.3 ms, 78% of its issue rate; 36.2
+// the whole video without a closeness limit 34.1 ms, one wave instruction per CU
+// and cycle (13.7 lane-instructions a relaxation, 10 of them the term's); 36.2
 // staged), 4 rows by 8 waves by latency (one model there 1.27 ms; 4.06 staged).
 // As scalar loads instead, V and A gave 33.9 and 1.17 ms, but the predecessors of
 // only some rows then need a loop of their own, whose chain of scalar loads took
@@ -693,7 +694,7 @@ __global__ __launch_bounds__(64) void k_trellis_columns(TrellisBand b, TrellisCo
 // from the lane that chose it, and only the predecessors' values and directions
 // are read from memory.  One wave walks bands of at most 64 predecessors per
 // node; wider ones are split over the workgroup's waves (one model on the whole
-// video without a closeness limit: 378 -> 75 us; 50 models at T = 10: 53 -> 27).
+// video without a closeness limit: 378 -> 108 us; 50 models at T = 10: 53 -> 31).
 constexpr int kFinalThreads = 1024;
 constexpr int kFinalNodes = 4096;
 
